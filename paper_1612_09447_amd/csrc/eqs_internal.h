@@ -34,7 +34,8 @@ constexpr int kSlice = 64;   // SELL slice height = wavefront size
 constexpr int kTetBlock = 256;  // threads per element-pass workgroup
 constexpr int kMaxTetsPerThread = 8;  // element blocks hold kTetBlock * tpt tets, tpt in {1, 2, 4, 8}
 constexpr int kMaxBlockNodes = 1360;  // distinct nodes per element block: 48 B of LDS each (<= 64 KiB)
-constexpr int64_t kMaxCoarseR = 4 << 20;  // entries of the fused restriction + coarse solve matrix
+constexpr int64_t kMaxCoarseR = 4 << 20;  // entries of the fused restriction + bottom solve matrix
+constexpr int32_t kMaxBottom = 1024;      // unknowns of a dense bottom level above the coarsest
 constexpr int kBlock = 256;  // threads per block for streaming kernels
 
 // ---------------------------------------------------------------- errors
@@ -150,30 +151,27 @@ struct Level {
     int32_t n = 0;
     SpMat<T> A, P, R;  // P, R unused on the coarsest level
     T* dinv = nullptr;
-    T* sval = nullptr;  // values of A omega D^{-1} in A's storage order (pre-smoothing); not on the coarsest level
+    T* sval = nullptr;  // values of A omega D^{-1} in A's storage order (pre-smoothing); folded cycle: A's only values
     double omega = 0;   // damped Jacobi weight
     T *b = nullptr, *x = nullptr, *xs = nullptr, *res = nullptr;
-    T* dense_inv = nullptr;  // coarsest level only: n x n, column-major
-    // coarsest level only, when small enough: the dense matrix that maps the
-    // level above to the coarse solution in one product (n x coarse_R_cols,
-    // row-major): A^{-1} R r of its residual, or, with `tail` set on the level
-    // above, A^{-1} R (I - A w D^{-1}) b of its right-hand side
+    T* dense_inv = nullptr;  // the bottom level's dense operator (symmetric, n x n)
+    // Folded cycle (see upload_folded in setup.cpp): with Q = (I - w D^-1 A) P,
+    // a V(1,1) visit of a level is b_next = Q^T b, then out = G b + Q x_next.
+    SpMat<T> GQ;  // levels between the finest and the bottom: [G Q] on the stacked [b; x_next]
+    SpMat<T> Q;   // finest level
+    // bottom level, when small enough: dense n x coarse_R_cols matrix from the
+    // level above's input (its b; the finest level's residual or right-hand
+    // side) straight to the bottom's solution, row-major
     T* coarse_R = nullptr;
     int32_t coarse_R_cols = 0;
-    // level above the coarsest, when folded (`tail`): its V(1,1) visit is
-    // xs = [G Q] [b; x_coarse] after the coarse product (b and the coarsest x
-    // share one buffer)
-    bool tail = false;
-    SpMat<T> GQ;
-    // pre-smoother folded into the restriction: R holds R (I - A w D^-1), so
-    // the descent restricts b directly and the prolongation stores
-    // x = w D^-1 b + P x_coarse (levels other than the finest and the tail)
-    bool fold_pre = false;
 };
 
 template <typename T>
 struct Hierarchy {
     std::vector<Level<T>> lv;
+    bool folded = false;  // the folded cycle; levels past `bottom` have no device data then
+    int bottom = 0;       // the level solved by its dense operator
+    bool direct = false;  // folded: the finest restriction acts on r itself (no pre-smoothing kernel)
 };
 
 // Start-vector estimator state (guess.hip).
@@ -358,7 +356,9 @@ struct eqs_ctx {
 
     // per-kernel-class timing (HIP event pairs around launches)
     uint32_t prof_mask = 0;
-    std::vector<hipEvent_t> prof_ev[EQS_KCLASS_COUNT];
+    std::vector<hipEvent_t> prof_pool;  // owned events, handed out in order
+    size_t prof_next = 0;
+    std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_ev[EQS_KCLASS_COUNT];  // start/stop of every launch
     int64_t prof_used[EQS_KCLASS_COUNT] = {};
 };
 
@@ -371,8 +371,9 @@ struct AmgHost {
     std::vector<Csr<double>> A, P, R;
     std::vector<double> omega;
     std::vector<double> coarse_inv;  // dense inverse of A.back(), column-major
+    std::vector<Csr<double>> AP;     // A P of every level but the coarsest, when asked for
 };
-AmgHost build_sa_amg(const Csr<double>& M, const eqs_amg_params& p);
+AmgHost build_sa_amg(const Csr<double>& M, const eqs_amg_params& p, bool keep_AP = false);
 void rkc_coefficients(int s, std::vector<double>& mu, std::vector<double>& nu, std::vector<double>& mut,
                       std::vector<double>& gmt, std::vector<double>& c);
 double rkc_beta(int s);
@@ -403,8 +404,10 @@ double time_mv(eqs_ctx* c, const SpMat<T>& A, const T* x, T* y, int reps);
 void upload(eqs_ctx* c);
 void build_element_blocks(eqs_ctx* c, const std::vector<int32_t>& u2i, const double* yfree, double* out);
 void free_device(eqs_ctx* c);
+// sorted: rows longest first within 256-thread windows; key (may be NULL): the
+// matrix whose row lengths sort them instead (two operators then share an order)
 template <typename T>
-Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted = false);
+Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted = false, const Csr<double>* key = nullptr);
 template <typename T>
 SpMat<T> to_spmat(eqs_ctx* c, const Csr<double>& A);
 
@@ -544,8 +547,9 @@ void guess_load_state(eqs_ctx* c, StateReader& r);
 // per-kernel timing (profile.cpp)
 void prof_begin(eqs_ctx* c, int cls, hipStream_t s);
 void prof_end(eqs_ctx* c, int cls, hipStream_t s);
-// next start/stop pair of a profiled single-kernel class (false: not profiled)
-bool prof_pair(eqs_ctx* c, int cls, hipEvent_t* e0, hipEvent_t* e1);
+// next start/stop pair of a profiled single-kernel class (false: not profiled);
+// cls2 (or -1): a second class whose work the launch does too
+bool prof_pair(eqs_ctx* c, int cls, hipEvent_t* e0, hipEvent_t* e1, int cls2 = -1);
 void prof_release(eqs_ctx* c);
 
 // drivers (solver.cpp)

@@ -15,6 +15,7 @@
 //  * RKC stage combination (the paper's ref. [9]).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -27,10 +28,12 @@ namespace eqs {
 
 // Launch `kernel`; when kernel class `cls` is being profiled the launch carries
 // its own start/stop events, so the class time is the kernel's execution.
-#define EQS_LAUNCH_TIMED(ctx, cls, kernel, grid, block, shmem, stream, ...)                                    \
+#define EQS_LAUNCH_TIMED(ctx, cls, ...) EQS_LAUNCH_TIMED2(ctx, cls, -1, __VA_ARGS__)
+// cls2: a second class whose work the launch does too (-1: none)
+#define EQS_LAUNCH_TIMED2(ctx, cls, cls2, kernel, grid, block, shmem, stream, ...)                             \
     do {                                                                                                      \
         hipEvent_t e0_, e1_;                                                                                  \
-        if (prof_pair((ctx), (cls), &e0_, &e1_))                                                              \
+        if (prof_pair((ctx), (cls), &e0_, &e1_, (cls2)))                                                              \
             hipExtLaunchKernelGGL(kernel, grid, block, shmem, stream, e0_, e1_, 0, __VA_ARGS__);              \
         else                                                                                                  \
             hipLaunchKernelGGL(kernel, grid, block, shmem, stream, __VA_ARGS__);                              \
@@ -941,73 +944,48 @@ static unsigned sell_grid(const Sell<T>& A) {
     return (unsigned)(((int64_t)A.n_slices * kSlice + kBlock - 1) / kBlock);
 }
 
-// Epilogue of a product y = A x: acc 0 stores A x, 1 adds it to y, 2 stores
-// omega dinv[row] b[row] + A x (the pre-smoothed x = omega D^-1 b of a level
-// whose pre-smoother is folded into its restriction, plus the prolonged
-// correction).
-template <typename T>
-struct MvInit {
-    const T* __restrict__ dinv;
-    const T* __restrict__ b;
-    T omega;
-};
-template <typename T>
-__device__ __forceinline__ void mv_store(T* __restrict__ y, int32_t row, T v, int acc, const MvInit<T>& in) {
-    if (acc == 2) y[row] = in.omega * in.dinv[row] * in.b[row] + v;
-    else y[row] = acc ? y[row] + v : v;
-}
-
-// y = A x with the epilogue above (L lanes per row, groups of U entries). The
-// epilogue's own loads are issued before the row sum, so they wait together
-// with the operator's loads instead of after the gathers.
-template <int L, int U, typename T>
-__device__ __forceinline__ void sell_mv(const SellView<T>& A, const T* __restrict__ x, T* __restrict__ y, int acc,
-                                        const MvInit<T>& in) {
+// y = A x (acc 0) or y += A x (acc 1), L lanes per row, groups of U entries;
+// x may be wider than the operator (the finest right-hand side). The
+// epilogue's own load is issued before the row sum, so it waits together with
+// the operator's loads instead of after the gathers.
+template <int L, int U, typename T, typename TX>
+__device__ __forceinline__ void sell_mv(const SellView<T>& A, const TX* __restrict__ x, T* __restrict__ y, int acc) {
     const int64_t g = row_block(A.xcd) * blockDim.x + threadIdx.x;
     if (g >= (int64_t)A.n_slices * 64) return;  // whole wavefronts leave together
     const int32_t row = sell_perm_row<L>(A.perm, g);
     const bool writer = (g & (L - 1)) == 0 && row < A.n_rows;
-    T y0 = T(0), d = T(0), bb = T(0);
-    if (writer) {
-        if (acc == 1) y0 = y[row];
-        else if (acc == 2) {
-            d = in.dinv[row];
-            bb = in.b[row];
-        }
-    }
+    T y0 = T(0);
+    if (writer && acc) y0 = y[row];
     const T v = sell_row<L, U>(A, g, row, x);
-    if (writer) {
-        if (acc == 2) y[row] = in.omega * d * bb + v;
-        else y[row] = acc ? y0 + v : v;
-    }
+    if (writer) y[row] = acc ? y0 + v : v;
 }
 
 // The same product under three names, so that traces tell the V-cycle's
 // restrictions (k_restrict) and prolongations (k_prolong) from other SELL
 // products (k_sell_mv). Groups of 16 entries hold their loads in up to 128
 // registers (4 waves per SIMD instead of 8).
-#define EQS_SELL_MV_ARGS \
-    SellView<T> A, const T* __restrict__ x, T* __restrict__ y, int acc, MvInit<T> in
-template <int L, int U, typename T>
+#define EQS_SELL_MV_ARGS SellView<T> A, const TX* __restrict__ x, T* __restrict__ y, int acc
+template <int L, int U, typename T, typename TX>
 __global__ __launch_bounds__(256, (U >= 16 ? 4 : kSparseWaves)) void k_sell_mv(EQS_SELL_MV_ARGS) {
-    sell_mv<L, U, T>(A, x, y, acc, in);
+    sell_mv<L, U, T, TX>(A, x, y, acc);
 }
-template <int L, int U, typename T>
+template <int L, int U, typename T, typename TX>
 __global__ __launch_bounds__(256, (U >= 16 ? 4 : kSparseWaves)) void k_restrict(EQS_SELL_MV_ARGS) {
-    sell_mv<L, U, T>(A, x, y, acc, in);
+    sell_mv<L, U, T, TX>(A, x, y, acc);
 }
-template <int L, int U, typename T>
+template <int L, int U, typename T, typename TX>
 __global__ __launch_bounds__(256, (U >= 16 ? 4 : kSparseWaves)) void k_prolong(EQS_SELL_MV_ARGS) {
-    sell_mv<L, U, T>(A, x, y, acc, in);
+    sell_mv<L, U, T, TX>(A, x, y, acc);
 }
 #undef EQS_SELL_MV_ARGS
 
 enum MvRole { MV_PLAIN = 0, MV_RESTRICT = 1, MV_PROLONG = 2 };
-template <int L, int U, typename T>
-using SellMvKernel = void (*)(SellView<T>, const T*, T*, int, MvInit<T>);
-template <int L, int U, typename T>
-static SellMvKernel<L, U, T> sell_mv_kernel(int role) {
-    return role == MV_RESTRICT ? k_restrict<L, U, T> : role == MV_PROLONG ? k_prolong<L, U, T> : k_sell_mv<L, U, T>;
+template <int L, int U, typename T, typename TX>
+using SellMvKernel = void (*)(SellView<T>, const TX*, T*, int);
+template <int L, int U, typename T, typename TX>
+static SellMvKernel<L, U, T, TX> sell_mv_kernel(int role) {
+    if constexpr (!std::is_same_v<T, TX>) return k_restrict<L, U, T, TX>;
+    else return role == MV_RESTRICT ? k_restrict<L, U, T, T> : role == MV_PROLONG ? k_prolong<L, U, T, T> : k_sell_mv<L, U, T, T>;
 }
 
 __global__ __launch_bounds__(256, kSparseWaves) void k_spmv64(SellView<double> A, const double* __restrict__ x,
@@ -1079,6 +1057,71 @@ __global__ __launch_bounds__(256, (U >= 16 ? 4 : kSparseWaves)) void k_postsmoot
     }
 }
 
+// ---- finest level of the folded cycle (see upload_folded) ----------------
+// Pre-smoothing kernel of large finest levels: As = A w D^-1 gathers r only;
+//   res = r - As r,   u = w D^-1 (r + res) = G r.
+template <typename T, int U = 8>
+__global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(SellView<T> As, const T* __restrict__ dinv, T omega,
+                                                                   const double* __restrict__ r, T* __restrict__ u,
+                                                                   T* __restrict__ res) {
+    const int64_t g = row_block(As.xcd) * blockDim.x + threadIdx.x;
+    if (g >= (int64_t)As.n_slices * 64) return;
+    const int32_t row = sell_perm_row<1>(As.perm, g);
+    const T acc = sell_row<1, U>(As, g, row, r);
+    if (row < As.n_rows) {
+        const T ri = (T)r[row], rs = ri - acc;
+        u[row] = omega * dinv[row] * (ri + rs);
+        res[row] = rs;
+    }
+}
+
+// Last kernel of the cycle: z = G r + Q x_1 (CG's FP64 z) with the block
+// partials of r.z and r.z_old as in k_postsmooth. DIRECT: G r is formed here,
+// w D^-1 (2 r - As r), from As and Q in one row order; else it is read (u).
+template <typename T, bool DOT, bool DIRECT, int U = 8>
+__global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, SellView<T> As,
+                                                                 const T* __restrict__ dinv, T omega,
+                                                                 const T* __restrict__ u, const double* __restrict__ r,
+                                                                 const T* __restrict__ x1, double* __restrict__ z,
+                                                                 InstMap m, double* __restrict__ part_rz,
+                                                                 double* __restrict__ part_rzold) {
+    __shared__ double sh[kPairSh];
+    const int64_t B = row_block(Q.xcd);
+    const int64_t g = B * blockDim.x + threadIdx.x;
+    const int32_t row = sell_perm_row<1>(Q.perm, g);
+    double rz = 0.0, rzo = 0.0;
+    if (g < (int64_t)Q.n_slices * 64) {
+        const bool in = row < Q.n_rows;
+        T ui = T(0);
+        double ri = 0.0, zo = 0.0;
+        if (in) {  // issued ahead of the row sums
+            ri = r[row];
+            if (DOT) zo = z[row];
+            ui = DIRECT ? dinv[row] : u[row];
+        }
+        const T qx = sell_row<1, U>(Q, g, row, x1);
+        if constexpr (DIRECT) {
+            const T ar = sell_row<1, U>(As, g, row, r);
+            ui = omega * ui * (T(2) * (T)ri - ar);
+        }
+        if (in) {
+            const T v = ui + qx;
+            if (DOT) {
+                rzo = ri * zo;
+                rz = ri * (double)v;
+            }
+            z[row] = (double)v;
+        }
+    }
+    if (DOT) {
+        int32_t lo, bound;
+        block_instances(m, lo, bound, B);
+        double* const parts[2] = {part_rz, part_rzold};
+        const double vals[2] = {rz, rzo};
+        store_pairs<2>(parts, vals, row >= bound, bound, sh, B);
+    }
+}
+
 // ---- CSR with L lanes per row (long rows of coarse operators) ----------
 template <typename T>
 struct CsrView {
@@ -1134,15 +1177,15 @@ __device__ __forceinline__ T csr_row(const CsrView<T>& A, int32_t row, int lane,
     return group_sum<L>(acc);
 }
 
-template <int L, typename T>
-__global__ __launch_bounds__(256, kSparseWaves) void k_csr_mv(CsrView<T> A, const T* __restrict__ x, T* __restrict__ y, int acc,
-                                                 MvInit<T> in) {
+template <int L, typename T, typename TX>
+__global__ __launch_bounds__(256, kSparseWaves) void k_csr_mv(CsrView<T> A, const TX* __restrict__ x,
+                                                              T* __restrict__ y, int acc) {
     const int64_t g = row_block(0) * blockDim.x + threadIdx.x;
     const int32_t row = (int32_t)(g / L);
     const int lane = (int)(g % L);
     if (row >= A.n_rows) return;  // whole groups leave together
-    const T v = csr_row<L>(A, row, lane, [&](int32_t j) { return x[j]; });
-    if (lane == 0) mv_store(y, row, v, acc, in);
+    const T v = csr_row<L>(A, row, lane, [&](int32_t j) { return (T)x[j]; });
+    if (lane == 0) y[row] = acc ? y[row] + v : v;
 }
 
 template <int L, typename T, typename TB>
@@ -1205,35 +1248,19 @@ static unsigned csr_grid(const SpMat<T>& A) {
         default: { constexpr int L_ = 64; CALL; } break; \
     }
 
-template <typename T>
-static void launch_mv(hipStream_t s, const SpMat<T>& A, const T* x, T* y, int acc,
-                      MvInit<T> in = MvInit<T>{nullptr, nullptr, T(0)}, int role = MV_PLAIN) {
+// One product, timed as the kernel classes `cls` and `cls2` where those are profiled.
+template <typename T, typename TX>
+static void launch_mv(hipStream_t s, eqs_ctx* c, int cls, int cls2, const SpMat<T>& A, const TX* x, T* y, int acc,
+                      int role) {
     if (A.fmt == FMT_SELL) {
         EQS_SELL_LANES_SWITCH(A.sell.lanes,
                               EQS_UNROLL_SWITCH(A.sell.unroll,
-                                                hipLaunchKernelGGL((sell_mv_kernel<L_, U_, T>(role)),
-                                                                   dim3(sell_grid(A.sell)), dim3(kBlock), 0, s,
-                                                                   view(A.sell), x, y, acc, in)));
+                                                EQS_LAUNCH_TIMED2(c, cls, cls2, (sell_mv_kernel<L_, U_, T, TX>(role)),
+                                                                  dim3(sell_grid(A.sell)), dim3(kBlock), 0, s,
+                                                                  view(A.sell), x, y, acc)));
     } else {
-        EQS_LANES_SWITCH(A.lanes, hipLaunchKernelGGL((k_csr_mv<L_, T>), dim3(csr_grid(A)), dim3(kBlock), 0, s,
-                                                     cview(A), x, y, acc, in));
-    }
-}
-
-// launch_mv with the launch's own events when kernel class `cls` is profiled
-template <typename T>
-static void launch_mv_timed(hipStream_t s, eqs_ctx* c, int cls, const SpMat<T>& A, const T* x, T* y, int acc,
-                            int role) {
-    const MvInit<T> in{nullptr, nullptr, T(0)};
-    if (A.fmt == FMT_SELL) {
-        EQS_SELL_LANES_SWITCH(A.sell.lanes,
-                              EQS_UNROLL_SWITCH(A.sell.unroll,
-                                                EQS_LAUNCH_TIMED(c, cls, (sell_mv_kernel<L_, U_, T>(role)),
-                                                                 dim3(sell_grid(A.sell)), dim3(kBlock), 0, s,
-                                                                 view(A.sell), x, y, acc, in)));
-    } else {
-        EQS_LANES_SWITCH(A.lanes, EQS_LAUNCH_TIMED(c, cls, (k_csr_mv<L_, T>), dim3(csr_grid(A)), dim3(kBlock), 0, s,
-                                                   cview(A), x, y, acc, in));
+        EQS_LANES_SWITCH(A.lanes, EQS_LAUNCH_TIMED2(c, cls, cls2, (k_csr_mv<L_, T, TX>), dim3(csr_grid(A)),
+                                                    dim3(kBlock), 0, s, cview(A), x, y, acc));
     }
 }
 
@@ -1287,7 +1314,7 @@ double time_mv(eqs_ctx* c, const SpMat<T>& A, const T* x, T* y, int reps) {
     std::vector<float> ms;
     for (int r = 0; r < reps + 1; ++r) {
         EQS_HIP(hipEventRecord(e0, c->stream));
-        for (int k = 0; k < kBatch; ++k) launch_mv<T>(c->stream, A, x, y, 0);
+        for (int k = 0; k < kBatch; ++k) launch_mv<T, T>(c->stream, c, -1, -1, A, x, y, 0, MV_PLAIN);
         EQS_HIP(hipEventRecord(e1, c->stream));
         EQS_HIP(hipEventSynchronize(e1));
         float t = 0.0f;
@@ -1302,29 +1329,39 @@ double time_mv(eqs_ctx* c, const SpMat<T>& A, const T* x, T* y, int reps) {
 template double time_mv<double>(eqs_ctx*, const SpMat<double>&, const double*, double*, int);
 template double time_mv<float>(eqs_ctx*, const SpMat<float>&, const float*, float*, int);
 
-// Coarsest level: x = A^{-1} b with the dense inverse. The inverse is
-// symmetric, so row i is stored contiguously (column i); one wavefront per row
-// splits the dot product over its 64 lanes.
+// Bottom level: x = B b with the dense symmetric operator; one wavefront per
+// row splits the dot product over its 64 lanes, eight terms of a lane in flight
+// together (a row of 894 waits for memory twice).
 template <typename T>
-__global__ __launch_bounds__(256) void k_coarse(const T* __restrict__ inv, const T* __restrict__ b,
-                                                 T* __restrict__ x, int32_t n) {
+__global__ __launch_bounds__(256) void k_coarse(const T* __restrict__ B, const T* __restrict__ b, T* __restrict__ x,
+                                                int32_t n) {
     const int32_t i = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (i >= n) return;
+    const T* row = B + (int64_t)i * n;
     T acc = T(0);
-    for (int32_t k = lane; k < n; k += 64) acc += inv[(int64_t)i * n + k] * b[k];
+    for (int32_t k0 = lane; k0 < n; k0 += 64 * 8) {
+        T t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int32_t k = min(k0 + 64 * u, n - 1);
+            t[u] = row[k] * b[k];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += (k0 + 64 * u < n) ? t[u] : T(0);
+    }
     acc = group_sum<64>(acc);
     if (lane == 0) x[i] = acc;
 }
 
-// Coarsest level with the restriction folded in: x = (A^{-1} R) r, one
-// workgroup of kCoarseThreads threads per coarse row of the dense row-major
-// product matrix C. Each thread sums its columns j = t, t + kCoarseThreads, ...
-// eight at a time (loads in flight together: one round covers 8192 columns),
-// then the block sums in a fixed order.
+// Bottom level with the restriction folded in: x = (B R) r, one workgroup of
+// kCoarseThreads threads per bottom row of the dense row-major product matrix
+// C. Each thread sums its columns j = t, t + kCoarseThreads, ... eight at a
+// time (loads in flight together: one round covers 8192 columns), then the
+// block sums in a fixed order.
 constexpr int kCoarseThreads = 1024;
-template <typename T>
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_restrict(const T* __restrict__ C, const T* __restrict__ r,
+template <typename T, typename TX>
+__global__ __launch_bounds__(kCoarseThreads) void k_coarse_restrict(const T* __restrict__ C, const TX* __restrict__ r,
                                                                      T* __restrict__ x, int32_t n, int32_t nf) {
     __shared__ double sh[kCoarseThreads / 64];
     const int32_t i = blockIdx.x;
@@ -1335,7 +1372,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_restrict(const T* __r
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int32_t j = min(j0 + u * kCoarseThreads, nf - 1);
-            t[u] = row[j] * r[j];
+            t[u] = row[j] * (T)r[j];
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc += (j0 + u * kCoarseThreads < nf) ? t[u] : T(0);
@@ -1382,6 +1419,61 @@ static InstMap inst_map(const eqs_ctx* c) {
     return InstMap{c->d_inst_row, c->d_blk_inst, (int32_t)c->n_inst, c->n_inst == 1 ? (int32_t)c->n_free : -1};
 }
 
+// The folded cycle. Kernel classes: a launch that does the work of two classes
+// counts in both (the direct restriction: pre-smoothing and restriction; the
+// last kernel: prolongation and post-smoothing; [G Q] of level 1: its
+// post-smoothing).
+template <typename T>
+static void vcycle_folded(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* r, double* z, double* part_rz,
+                          double* part_rzold) {
+    const dim3 b(kBlock);
+    const int t = h.bottom;
+    Level<T>& l0 = h.lv[0];
+    Level<T>& bot = h.lv[t];
+    if (!h.direct)
+        EQS_LAUNCH_TIMED(c, EQS_KCLASS_PRESMOOTH0, (k_presmooth_u<T>), dim3(sell_grid(l0.A.sell)), b, 0, s, sview(l0),
+                         (const T*)l0.dinv, (T)l0.omega, r, l0.x, l0.res);
+    const bool whole = t == 1 && bot.coarse_R;  // the finest restriction is part of the bottom's product
+    if (whole) {
+        prof_begin(c, EQS_KCLASS_VCOARSE, s);
+    } else {
+        if (h.direct)
+            launch_mv<T, double>(s, c, EQS_KCLASS_RESTRICT0, EQS_KCLASS_PRESMOOTH0, l0.R, r, h.lv[1].b, 0, MV_RESTRICT);
+        else
+            launch_mv<T, T>(s, c, EQS_KCLASS_RESTRICT0, -1, l0.R, (const T*)l0.res, h.lv[1].b, 0, MV_RESTRICT);
+        prof_begin(c, EQS_KCLASS_VCOARSE, s);
+    }
+    for (int l = 1; l < (bot.coarse_R ? t - 1 : t); ++l)
+        launch_mv<T, T>(s, c, -1, -1, h.lv[l].R, (const T*)h.lv[l].b, h.lv[l + 1].b, 0, MV_RESTRICT);
+    if (!bot.coarse_R)
+        hipLaunchKernelGGL(k_coarse<T>, dim3(grid_for((int64_t)bot.n * 64)), b, 0, s, (const T*)bot.dense_inv,
+                           (const T*)bot.b, bot.xs, bot.n);
+    else if (whole && h.direct)
+        hipLaunchKernelGGL((k_coarse_restrict<T, double>), dim3((unsigned)bot.n), dim3(kCoarseThreads), 0, s,
+                           (const T*)bot.coarse_R, r, bot.xs, bot.n, bot.coarse_R_cols);
+    else
+        hipLaunchKernelGGL((k_coarse_restrict<T, T>), dim3((unsigned)bot.n), dim3(kCoarseThreads), 0, s,
+                           (const T*)bot.coarse_R, (const T*)(whole ? l0.res : h.lv[t - 1].b), bot.xs, bot.n,
+                           bot.coarse_R_cols);
+    for (int l = t - 1; l >= 1; --l)
+        launch_mv<T, T>(s, c, l == 1 ? EQS_KCLASS_POSTSMOOTH1 : -1, -1, h.lv[l].GQ, (const T*)h.lv[l].b, h.lv[l].xs, 0,
+                        MV_PLAIN);
+    prof_end(c, EQS_KCLASS_VCOARSE, s);
+    const InstMap m = part_rz ? inst_map(c) : InstMap{nullptr, nullptr, 0, -1};
+#define EQS_POST_FOLD(DOT_, DIRECT_)                                                                                   \
+    EQS_LAUNCH_TIMED2(c, EQS_KCLASS_POSTSMOOTH0, EQS_KCLASS_PROLONG0, (k_post_fold<T, DOT_, DIRECT_>),                 \
+                      dim3(sell_grid(l0.Q.sell)), b, 0, s, view(l0.Q.sell), sview(l0), (const T*)l0.dinv, (T)l0.omega, \
+                      (const T*)l0.x, r, (const T*)h.lv[1].xs, z, m, part_rz, part_rzold)
+    if (h.direct) {
+        if (part_rz) EQS_POST_FOLD(true, true);
+        else EQS_POST_FOLD(false, true);
+    } else {
+        if (part_rz) EQS_POST_FOLD(true, false);
+        else EQS_POST_FOLD(false, false);
+    }
+#undef EQS_POST_FOLD
+}
+
 // V(1,1) cycle z = B r. r and z are FP64 (CG's vectors); the hierarchy is T.
 // With part_rz the finest post-smoothing also writes the r.z and r.z_old
 // partials (pair layout). Its kernels do not test CG's stop flag: a test on a
@@ -1407,59 +1499,33 @@ void vcycle(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* r, double*
                                z, lv.n, inst_map(c), part_rz, part_rzold);
         return;
     }
+    if (h.folded) {
+        vcycle_folded<T>(s, c, h, r, z, part_rz, part_rzold);
+        return;
+    }
     // descend
     for (int l = 0; l < L - 1; ++l) {
         Level<T>& lv = h.lv[l];
-        if (lv.tail) break;  // folded into the coarse product and [G Q] (the last level above the coarsest)
-        if (lv.fold_pre) {  // R holds R (I - A w D^-1): restrict b itself
-            launch_mv<T>(s, lv.R, (const T*)lv.b, h.lv[l + 1].b, 0, MvInit<T>{nullptr, nullptr, T(0)},
-                         MV_RESTRICT);
-            continue;
-        }
-        if (l == 0) {
-            // the finest operator is always SELL-64 (see tuned_spmat)
+        if (l == 0)  // the finest operator is always SELL-64 (see tuned_spmat)
             EQS_LAUNCH_TIMED(c, EQS_KCLASS_PRESMOOTH0, (k_presmooth_res<1, T, double>), dim3(sell_grid(lv.A.sell)), b, 0,
                              s, sview(lv), (const T*)lv.dinv, (T)lv.omega, r, lv.x, lv.res);
-        } else {
+        else
             launch_presmooth<T, T>(s, lv, (const T*)lv.b);
-        }
-        if (l + 1 < L - 1 || !h.lv[L - 1].coarse_R) {
-            if (l == 0)
-                launch_mv_timed<T>(s, c, EQS_KCLASS_RESTRICT0, lv.R, (const T*)lv.res, h.lv[1].b, 0,
-                                   MV_RESTRICT);
-            else
-                launch_mv<T>(s, lv.R, (const T*)lv.res, h.lv[l + 1].b, 0, MvInit<T>{nullptr, nullptr, T(0)},
-                             MV_RESTRICT);
-        }
+        launch_mv<T, T>(s, c, l == 0 ? EQS_KCLASS_RESTRICT0 : -1, -1, lv.R, (const T*)lv.res, h.lv[l + 1].b, 0,
+                        MV_RESTRICT);
         if (l == 0) prof_begin(c, EQS_KCLASS_VCOARSE, s);
     }
     {
         Level<T>& lc = h.lv[L - 1];
-        const Level<T>& la = h.lv[L - 2];
-        if (lc.coarse_R)  // restriction (and, folded, the level above's pre-smoothing) and coarse solve in one product
-            hipLaunchKernelGGL(k_coarse_restrict<T>, dim3((unsigned)lc.n), dim3(kCoarseThreads), 0, s,
-                               (const T*)lc.coarse_R, (const T*)(la.tail ? la.b : la.res), lc.x, lc.n,
-                               lc.coarse_R_cols);
-        else
-            hipLaunchKernelGGL(k_coarse<T>, dim3(grid_for((int64_t)lc.n * 64)), b, 0, s, (const T*)lc.dense_inv,
-                               (const T*)lc.b, lc.x, lc.n);
+        hipLaunchKernelGGL(k_coarse<T>, dim3(grid_for((int64_t)lc.n * 64)), b, 0, s, (const T*)lc.dense_inv,
+                           (const T*)lc.b, lc.x, lc.n);
     }
     // ascend
     for (int l = L - 2; l >= 0; --l) {
         Level<T>& lv = h.lv[l];
-        if (lv.tail) {  // xs = G b + Q x_coarse on the stacked [b; x_coarse]
-            launch_mv<T>(s, lv.GQ, (const T*)lv.b, lv.xs, 0);
-            continue;
-        }
         const T* xc = (l + 1 == L - 1) ? h.lv[l + 1].x : h.lv[l + 1].xs;
         if (l == 0) prof_end(c, EQS_KCLASS_VCOARSE, s);
-        if (lv.fold_pre)  // x = w D^-1 b (the folded pre-smoother's result) + P xc
-            launch_mv<T>(s, lv.P, xc, lv.x, 2, MvInit<T>{(const T*)lv.dinv, (const T*)lv.b, (T)lv.omega},
-                         MV_PROLONG);
-        else if (l == 0)
-            launch_mv_timed<T>(s, c, EQS_KCLASS_PROLONG0, lv.P, xc, lv.x, 1, MV_PROLONG);
-        else
-            launch_mv<T>(s, lv.P, xc, lv.x, 1, MvInit<T>{nullptr, nullptr, T(0)}, MV_PROLONG);
+        launch_mv<T, T>(s, c, l == 0 ? EQS_KCLASS_PROLONG0 : -1, -1, lv.P, xc, lv.x, 1, MV_PROLONG);
         if (l > 0) {
             launch_postsmooth<T>(s, c, l == 1 ? EQS_KCLASS_POSTSMOOTH1 : -1, lv, (const T*)lv.b, (const T*)lv.x,
                                  lv.xs);

@@ -407,7 +407,7 @@ static std::vector<double> dense_spd_inverse(const Csr<double>& A) {
     return inv;
 }
 
-AmgHost build_sa_amg(const Csr<double>& M, const eqs_amg_params& p) {
+AmgHost build_sa_amg(const Csr<double>& M, const eqs_amg_params& p, bool keep_AP) {
     AmgHost h;
     Csr<double> A = M;
     for (;;) {
@@ -470,6 +470,7 @@ AmgHost build_sa_amg(const Csr<double>& M, const eqs_amg_params& p) {
         h.A.push_back(std::move(A));
         h.P.push_back(std::move(P));
         h.R.push_back(std::move(R));
+        if (keep_AP) h.AP.push_back(std::move(AP));
         A = std::move(Ac);
     }
     return h;
@@ -621,6 +622,7 @@ static void visit_hierarchy(Hierarchy<T>& h, const std::function<void(void**)>& 
         visit_spmat(lv.P, f);
         visit_spmat(lv.R, f);
         visit_spmat(lv.GQ, f);
+        visit_spmat(lv.Q, f);
         for (T** q : {&lv.dinv, &lv.sval, &lv.b, &lv.x, &lv.xs, &lv.res, &lv.dense_inv, &lv.coarse_R}) f((void**)q);
     }
 }
@@ -741,7 +743,7 @@ static T* upload_vec(eqs_ctx* c, const std::vector<T>& v) {
 }
 
 template <typename T>
-Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted) {
+Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const Csr<double>* key) {
     if (lanes != 1 && lanes != 2 && lanes != 4 && lanes != 8) fail(EQS_ERR_STATE, "SELL lanes per row must be 1, 2, 4 or 8");
     const int32_t rows_per = kSlice / lanes;  // rows of one slice
     const int32_t window = 4 * rows_per;      // rows of one 256-thread window
@@ -756,11 +758,12 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted) {
     std::vector<int32_t> pos2row((size_t)n_pos);
     for (int32_t k = 0; k < n_pos; ++k) pos2row[(size_t)k] = k;
     auto len = [&](int32_t r) { return r < A.n_rows ? A.ptr[r + 1] - A.ptr[r] : 0; };
+    auto key_len = [&](int32_t r) { return !key ? len(r) : r < A.n_rows ? key->ptr[r + 1] - key->ptr[r] : 0; };
     if (sorted)
         for (int32_t w0 = 0; w0 < n_pos; w0 += window) {
             const int32_t w1 = std::min(n_pos, w0 + window);
             std::stable_sort(pos2row.begin() + w0, pos2row.begin() + w1,
-                             [&](int32_t a, int32_t b) { return len(a) > len(b); });
+                             [&](int32_t a, int32_t b) { return key_len(a) > key_len(b); });
         }
     std::vector<int32_t> sptr(S.n_slices + 1, 0);
     for (int32_t s = 0; s < S.n_slices; ++s) {
@@ -829,8 +832,8 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted) {
     return S;
 }
 
-template Sell<double> to_sell<double>(eqs_ctx*, const Csr<double>&, int, bool);
-template Sell<float> to_sell<float>(eqs_ctx*, const Csr<double>&, int, bool);
+template Sell<double> to_sell<double>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*);
+template Sell<float> to_sell<float>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*);
 
 // CSR column ids: 16-bit offsets from offset_base(row) when every entry
 // allows, else absolute.
@@ -1115,186 +1118,218 @@ static T* scaled_values(eqs_ctx* c, const SpMat<T>& S, const Csr<double>& A, con
     return upload_vec(c, v);
 }
 
+// The finest level's Q: one lane per row (its kernel writes the CG partials of
+// 256-row blocks). With `direct` it takes A_0's row order (or none), because
+// one kernel walks both; else its own where that pays.
 template <typename T>
-static void upload_coarse_tail(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h);
-
-// Whether the level above the coarsest is folded with it (see upload_coarse_tail).
-static bool coarse_tail_applies(const eqs_ctx* c, const AmgHost& ah) {
-    const size_t L = ah.A.size();
-    return c->fold && L >= 3 && (int64_t)ah.A[L - 1].n_rows * ah.A[L - 2].n_rows <= kMaxCoarseR;
+static SpMat<T> finest_Q(eqs_ctx* c, const Csr<double>& Q, const Csr<double>& A0, bool direct, bool a0_sorted) {
+    SpMat<T> S;
+    S.n_rows = Q.n_rows; S.n_cols = Q.n_cols; S.nnz = Q.nnz();
+    S.fmt = FMT_SELL;
+    const bool sorted = direct ? a0_sorted : row_order_pays(Q);
+    S.sell = to_sell<T>(c, Q, 1, sorted, direct ? &A0 : nullptr);
+    S.sell.xcd = 1;  // with the finest smoothers' block order
+    char line[160];
+    std::snprintf(line, sizeof line, "Q0: %d x %d, %lld nonzeros, sell64%s (finest level), %s, stored/nnz %.2f\n", Q.n_rows,
+                  Q.n_cols, (long long)Q.nnz(), sorted ? "s" : "", S.sell.d16 ? "16-bit column offsets" : "32-bit columns",
+                  Q.nnz() ? (double)S.sell.stored / (double)Q.nnz() : 1.0);
+    c->tune_log += line;
+    return S;
 }
 
-// R (I - A w D^-1) = R - w (R A) D^-1 (rows in column order): the restriction
-// of a level whose pre-smoother x = w D^-1 b, res = b - A x is folded into it.
-static Csr<double> fold_presmoother(const Csr<double>& R, const Csr<double>& A, const std::vector<double>& d,
-                                    double w) {
-    Csr<double> out;
-    out.n_rows = R.n_rows;
-    out.n_cols = R.n_cols;
-    out.ptr.assign((size_t)R.n_rows + 1, 0);
-    std::vector<double> acc((size_t)R.n_cols, 0.0);
-    std::vector<char> seen((size_t)R.n_cols, 0);
-    std::vector<int32_t> cols;
-    auto touch = [&](int32_t j) {
-        if (!seen[j]) {
-            seen[j] = 1;
-            cols.push_back(j);
+// Q = P - w D^-1 (A P) = (I - w D^-1 A) P of a level (columns sorted per row):
+// the prolongation with the post-smoother folded in, and, transposed, the
+// restriction with the pre-smoother folded in, P^T (I - w A D^-1) (A symmetric).
+static Csr<double> smoothed_prolongation(const Csr<double>& P, const Csr<double>& AP, const std::vector<double>& d,
+                                         double w) {
+    Csr<double> Q = AP;  // AP's pattern holds P's (A has its diagonal)
+    for (int32_t i = 0; i < Q.n_rows; ++i) {
+        int32_t e = P.ptr[i];
+        for (int32_t k = Q.ptr[i]; k < Q.ptr[i + 1]; ++k) {
+            double v = -w * AP.val[k] / d[i];
+            if (e < P.ptr[i + 1] && P.col[e] == AP.col[k]) v += P.val[e++];
+            Q.val[k] = v;
         }
-    };
-    for (int32_t i = 0; i < R.n_rows; ++i) {
-        cols.clear();
-        for (int32_t e = R.ptr[i]; e < R.ptr[i + 1]; ++e) {
-            touch(R.col[e]);
-            acc[R.col[e]] += R.val[e];
-        }
-        for (int32_t e = R.ptr[i]; e < R.ptr[i + 1]; ++e) {
-            const int32_t k = R.col[e];
-            const double rk = w * R.val[e];
-            for (int32_t f = A.ptr[k]; f < A.ptr[k + 1]; ++f) {
-                const int32_t j = A.col[f];
-                touch(j);
-                acc[j] -= rk * A.val[f] / d[j];
-            }
-        }
-        std::sort(cols.begin(), cols.end());
-        for (int32_t j : cols) {
-            out.col.push_back(j);
-            out.val.push_back(acc[j]);
-            acc[j] = 0.0;
-            seen[j] = 0;
-        }
-        out.ptr[(size_t)i + 1] = (int32_t)out.col.size();
+        if (e != P.ptr[i + 1]) fail(EQS_ERR_INVALID_ARG, "AMG: prolongator entries outside A P");
     }
-    return out;
+    return Q;
 }
 
+// Plain cycle: every level's A, P and R, the coarsest level's dense inverse.
 template <typename T>
-static void upload_hierarchy(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h, const double* level0_M_vals_hint) {
-    (void)level0_M_vals_hint;
+static void upload_plain(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
     const size_t L = ah.A.size();
-    const bool tail_ok = coarse_tail_applies(c, ah);
-    h.lv.resize(L);
+    h.bottom = (int)L - 1;
     for (size_t l = 0; l < L; ++l) {
         Level<T>& lv = h.lv[l];
-        lv.n = ah.A[l].n_rows;
         // coarse operators may take a row order too: their smoothers write only rows of their own window
         lv.A = tuned_spmat<T>(c, ah.A[l], ("A" + std::to_string(l)).c_str(), l == 0, l > 0);
         std::vector<double> d = diagonal(ah.A[l]);
         std::vector<T> dinv(lv.n);
         for (int32_t i = 0; i < lv.n; ++i) dinv[i] = (T)(1.0 / d[i]);
         lv.dinv = upload_vec(c, dinv);
-        lv.omega = ah.omega[l];
-        lv.b = (T*)dev_alloc(c, sizeof(T) * lv.n);
-        lv.x = (T*)dev_alloc(c, sizeof(T) * lv.n);
-        lv.xs = (T*)dev_alloc(c, sizeof(T) * lv.n);
-        lv.res = (T*)dev_alloc(c, sizeof(T) * lv.n);
+        for (T** q : {&lv.b, &lv.x, &lv.xs, &lv.res}) *q = (T*)dev_alloc(c, sizeof(T) * lv.n);
         if (l + 1 < L) {
-            // levels other than the finest (whose smoothers feed CG) and the
-            // folded tail restrict b through R (I - A w D^-1)
-            const bool tail_level = tail_ok && l == (int)L - 2;
-            lv.fold_pre = c->fold && l >= 1 && !tail_level;
-            if (!lv.fold_pre) lv.sval = scaled_values<T>(c, lv.A, ah.A[l], d, lv.omega);
+            lv.sval = scaled_values<T>(c, lv.A, ah.A[l], d, lv.omega);
             lv.P = tuned_spmat<T>(c, ah.P[l], ("P" + std::to_string(l)).c_str(), false, true);
-            if (lv.fold_pre)
-                lv.R = tuned_spmat<T>(c, fold_presmoother(ah.R[l], ah.A[l], d, lv.omega),
-                                      ("R" + std::to_string(l) + "(I-AwD^-1)").c_str(), false, true);
-            else
-                lv.R = tuned_spmat<T>(c, ah.R[l], ("R" + std::to_string(l)).c_str(), false, true);
+            lv.R = tuned_spmat<T>(c, ah.R[l], ("R" + std::to_string(l)).c_str(), false, true);
         } else {
-            std::vector<T> inv(ah.coarse_inv.size());
-            for (size_t k = 0; k < inv.size(); ++k) inv[k] = (T)ah.coarse_inv[k];
-            lv.dense_inv = upload_vec(c, inv);
+            lv.dense_inv = upload_vec(c, std::vector<T>(ah.coarse_inv.begin(), ah.coarse_inv.end()));
         }
     }
-    upload_coarse_tail<T>(c, ah, h);
 }
 
-// The two lowest levels folded into two products (formed in FP64 here). With
-// t = L-2 (the level above the coarsest c = L-1), S = I - w D^-1 A_t and
-// T = I - A_t w D^-1, one V(1,1) visit of t with the exact coarse solve is
-//   x_c = C' b_t,            C' = A_c^-1 R_t T       (dense n_c x n_t)
-//   xs_t = G b_t + Q x_c,    G = (S + I) w D^-1 (A_t's pattern), Q = S P_t
-// so the pre-smoother, restriction, coarse solve, prolongation and
-// post-smoother of t become one dense and one sparse product, [G Q] acting on
-// the stacked vector [b_t; x_c]. Only when t is not the finest level (whose
-// post-smoother produces CG partials) and C' is small; with two levels only
-// the restriction is folded into the coarse solve (x_c = A_c^-1 R_0 r_0).
+// Up to this many finest rows the restriction is the folded Q_0^T on r itself:
+// 8.8 entries per fine row (first-order stencil) against 7 + 3.6 in the
+// pre-smoothing kernel and R_0, but one launch instead of two and one more
+// product inside the last kernel. The smaller cycles are bound by the launches
+// (4-6 us each), the larger by the entries' bytes.
+constexpr int32_t kDirectRows = 500000;
+
+// Folded cycle, formed here in FP64. A V(1,1) visit of a level l that is not
+// the bottom is, with x = w D^-1 b, res = b - A x, x += P x_next,
+// out = x + w D^-1 (b - A x):
+//   b_next = P^T res = Q^T b,    out = G b + Q x_next,
+//   Q = (I - w D^-1 A) P,        G = (2 I - w D^-1 A) w D^-1  (A's pattern),
+// so two products replace pre-smoother, restriction, prolongation and
+// post-smoother. Levels between the finest and the bottom hold Q^T and [G Q]
+// (on the stacked vector [b; x_next]). The finest level's last kernel forms
+// G r from the pre-smoothing values; large finest levels keep a pre-smoothing
+// kernel, which writes w D^-1 (r + res) = G r and res, and restrict res.
+// From the bottom level down the whole cycle is one dense symmetric matrix,
+//   B_l = G_l + Q_l B_(l+1) Q_l^T  (the coarsest: its inverse),
+// at the first level of at most 2 coarse_max (and kMaxBottom) unknowns; where
+// that matrix times the restriction above it is small, the two are one.
 template <typename T>
-static void upload_coarse_tail(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
-    const int L = (int)h.lv.size();
-    if (L < 2 || !c->fold) return;
-    Level<T>& lc = h.lv[L - 1];
-    const int t = L - 2;
-    const Csr<double>& R = ah.R[t];
-    const int64_t nc = lc.n, nt = R.n_cols;
-    if (nc * nt > kMaxCoarseR) return;
-    auto inv = [&](int64_t i, int64_t k) { return ah.coarse_inv[(size_t)(k * nc + i)]; };  // column-major
-    // C = A_c^-1 R_t (dense, row-major nc x nt)
-    std::vector<double> C((size_t)(nc * nt), 0.0);
-    for (int32_t k = 0; k < R.n_rows; ++k)
-        for (int32_t e = R.ptr[k]; e < R.ptr[k + 1]; ++e)
-            for (int64_t i = 0; i < nc; ++i) C[(size_t)(i * nt + R.col[e])] += inv(i, k) * R.val[e];
-    if (t == 0) {  // finest level above the coarsest: fold the restriction only
-        std::vector<T> Ct(C.size());
-        for (size_t k = 0; k < C.size(); ++k) Ct[k] = (T)C[k];
-        lc.coarse_R = upload_vec(c, Ct);
-        lc.coarse_R_cols = (int32_t)nt;
-        return;
+static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
+    const int L = (int)ah.A.size();
+    int t = L - 1;
+    for (int l = L - 1; l >= 1; --l)
+        if (ah.A[l].n_rows <= std::min(kMaxBottom, 2 * c->amg.coarse_max)) t = l;
+    h.folded = true;
+    h.bottom = t;
+    h.direct = ah.A[0].n_rows <= kDirectRows;
+    std::vector<std::vector<double>> d(L);
+    std::vector<Csr<double>> Q(L);
+    for (int l = 0; l + 1 < L; ++l) {
+        d[l] = diagonal(ah.A[l]);
+        Q[l] = smoothed_prolongation(ah.P[l], ah.AP[l], d[l], ah.omega[l]);
     }
-    Level<T>& lt = h.lv[t];
-    const Csr<double>& A = ah.A[t];
-    const Csr<double>& P = ah.P[t];
-    const std::vector<double> d = diagonal(A);
-    const double w = ah.omega[t];
-    // C' = C - w C A D^-1: row i of C A is sum_k C(i,k) A(k,:)
-    std::vector<double> Cp = C;
-    for (int32_t k = 0; k < A.n_rows; ++k)
-        for (int32_t e = A.ptr[k]; e < A.ptr[k + 1]; ++e) {
-            const int32_t j = A.col[e];
-            const double f = w * A.val[e] / d[j];
-            for (int64_t i = 0; i < nc; ++i) Cp[(size_t)(i * nt + j)] -= C[(size_t)(i * nt + k)] * f;
-        }
-    // [G Q]: row i holds G's entries (columns j < nt) then Q's nonzeros
-    // (columns nt + k), Q = P - w D^-1 A P
-    Csr<double> GQ;
-    GQ.n_rows = (int32_t)nt;
-    GQ.n_cols = (int32_t)(nt + nc);
-    GQ.ptr.assign((size_t)nt + 1, 0);
-    std::vector<double> q((size_t)nc);
-    for (int32_t i = 0; i < (int32_t)nt; ++i) {
-        for (int32_t e = A.ptr[i]; e < A.ptr[i + 1]; ++e) {
-            const int32_t j = A.col[e];
-            const double g = (j == i ? 2.0 * w / d[i] : 0.0) - w * w * A.val[e] / (d[i] * d[j]);
-            GQ.col.push_back(j);
-            GQ.val.push_back(g);
-        }
-        std::fill(q.begin(), q.end(), 0.0);
-        for (int32_t e = P.ptr[i]; e < P.ptr[i + 1]; ++e) q[P.col[e]] += P.val[e];
-        for (int32_t e = A.ptr[i]; e < A.ptr[i + 1]; ++e) {
-            const int32_t k = A.col[e];
-            const double f = w * A.val[e] / d[i];
-            for (int32_t u = P.ptr[k]; u < P.ptr[k + 1]; ++u) q[P.col[u]] -= f * P.val[u];
-        }
-        for (int64_t k = 0; k < nc; ++k)
-            if (q[(size_t)k] != 0.0) {
-                GQ.col.push_back((int32_t)(nt + k));
-                GQ.val.push_back(q[(size_t)k]);
+    auto g_value = [&](int l, int32_t i, int32_t e) {  // entry e (row i) of G_l
+        const Csr<double>& A = ah.A[l];
+        const int32_t j = A.col[e];
+        const double w = ah.omega[l];
+        return (j == i ? 2.0 * w / d[l][i] : 0.0) - w * w * A.val[e] / (d[l][i] * d[l][j]);
+    };
+    // the bottom's dense operator (symmetric)
+    std::vector<double> B = ah.coarse_inv;
+    for (int l = L - 2; l >= t; --l) {
+        const int64_t n = ah.A[l].n_rows, m = ah.A[l + 1].n_rows;
+        std::vector<double> W((size_t)(n * m), 0.0), Bl((size_t)(n * n), 0.0);  // W = Q B
+        for (int64_t i = 0; i < n; ++i)
+            for (int32_t e = Q[l].ptr[i]; e < Q[l].ptr[i + 1]; ++e)
+                for (int64_t k = 0; k < m; ++k) W[(size_t)(i * m + k)] += Q[l].val[e] * B[(size_t)(Q[l].col[e] * m + k)];
+        for (int64_t i = 0; i < n; ++i) {
+            for (int64_t j = 0; j <= i; ++j) {
+                double v = 0.0;
+                for (int32_t e = Q[l].ptr[j]; e < Q[l].ptr[j + 1]; ++e) v += W[(size_t)(i * m + Q[l].col[e])] * Q[l].val[e];
+                Bl[(size_t)(i * n + j)] = Bl[(size_t)(j * n + i)] = v;
             }
-        GQ.ptr[(size_t)i + 1] = (int32_t)GQ.col.size();
+        }
+        for (int32_t i = 0; i < (int32_t)n; ++i)
+            for (int32_t e = ah.A[l].ptr[i]; e < ah.A[l].ptr[i + 1]; ++e) Bl[(size_t)i * n + ah.A[l].col[e]] += g_value(l, i, e);
+        B.swap(Bl);
     }
-    std::vector<T> Ct(Cp.size());
-    for (size_t k = 0; k < Cp.size(); ++k) Ct[k] = (T)Cp[k];
-    lc.coarse_R = upload_vec(c, Ct);
-    lc.coarse_R_cols = (int32_t)nt;
-    lt.GQ = tuned_spmat<T>(c, GQ, ("[G Q]" + std::to_string(t)).c_str(), false, true);
-    // b_t and x_c side by side: the restriction from above writes b_t, the
-    // dense product writes x_c, the sparse product reads both
-    T* bx = (T*)dev_alloc(c, sizeof(T) * (size_t)(nt + nc));
-    dev_free(c, lt.b);  // the separate vectors they replace
-    dev_free(c, lc.x);
-    lt.b = bx;
-    lc.x = bx + nt;
-    lt.tail = true;
+    const int64_t nt = ah.A[t].n_rows, na = ah.A[t - 1].n_rows;
+    const bool merged = nt * na <= kMaxCoarseR;  // B_t times the restriction above it as one dense matrix
+    Level<T>& bot = h.lv[t];
+    if (merged) {
+        const Csr<double>& up = (t > 1 || h.direct) ? Q[0 + (t - 1)] : ah.P[0];  // its transpose restricts
+        std::vector<T> C((size_t)(nt * na));
+        std::vector<double> row((size_t)na);
+        for (int64_t i = 0; i < nt; ++i) {
+            for (int64_t j = 0; j < na; ++j) {
+                double v = 0.0;
+                for (int32_t e = up.ptr[j]; e < up.ptr[j + 1]; ++e) v += B[(size_t)(i * nt + up.col[e])] * up.val[e];
+                row[(size_t)j] = v;
+            }
+            for (int64_t j = 0; j < na; ++j) C[(size_t)(i * na + j)] = (T)row[(size_t)j];
+        }
+        bot.coarse_R = upload_vec(c, C);
+        bot.coarse_R_cols = (int32_t)na;
+    } else {
+        bot.dense_inv = upload_vec(c, std::vector<T>(B.begin(), B.end()));
+    }
+    // vectors: b of every level below the finest, with the next level's result
+    // behind it where a stacked product reads both
+    for (int l = 1; l <= t; ++l) {
+        const bool stacked = l < t;
+        T* buf = (T*)dev_alloc(c, sizeof(T) * ((size_t)ah.A[l].n_rows + (stacked ? (size_t)ah.A[l + 1].n_rows : 0)));
+        h.lv[l].b = buf;
+        if (stacked) h.lv[l + 1].xs = buf + ah.A[l].n_rows;
+    }
+    h.lv[1].xs = (T*)dev_alloc(c, sizeof(T) * (size_t)ah.A[1].n_rows);
+    for (int l = 0; l + 1 < L; ++l) {
+        Level<T>& lv = h.lv[l];
+        const std::string id = std::to_string(l);
+        lv.A.nnz = ah.A[l].nnz();
+        lv.P.nnz = ah.P[l].nnz();
+        lv.R.nnz = ah.R[l].nnz();
+        if (l >= t) continue;
+        if (l == 0) {
+            Csr<double> As = ah.A[0];  // A w D^-1
+            for (size_t k = 0; k < As.val.size(); ++k) As.val[k] *= lv.omega / d[0][As.col[k]];
+            lv.A = tuned_spmat<T>(c, As, "A0", true);
+            lv.sval = lv.A.sell.val;
+            std::vector<T> dinv(lv.n);
+            for (int32_t i = 0; i < lv.n; ++i) dinv[i] = (T)(1.0 / d[0][i]);
+            lv.dinv = upload_vec(c, dinv);
+            if (!h.direct) {
+                lv.x = (T*)dev_alloc(c, sizeof(T) * lv.n);
+                lv.res = (T*)dev_alloc(c, sizeof(T) * lv.n);
+            }
+            // the direct form's last kernel walks A_0 and Q_0 with one row order
+            lv.Q = finest_Q<T>(c, Q[0], ah.A[0], h.direct, lv.A.sell.perm != nullptr);
+        } else {
+            Csr<double> GQ;
+            const int32_t n = ah.A[l].n_rows;
+            GQ.n_rows = n;
+            GQ.n_cols = n + ah.A[l + 1].n_rows;
+            GQ.ptr.assign((size_t)n + 1, 0);
+            GQ.col.reserve((size_t)(ah.A[l].nnz() + Q[l].nnz()));
+            GQ.val.reserve((size_t)(ah.A[l].nnz() + Q[l].nnz()));
+            for (int32_t i = 0; i < n; ++i) {
+                for (int32_t e = ah.A[l].ptr[i]; e < ah.A[l].ptr[i + 1]; ++e) {
+                    GQ.col.push_back(ah.A[l].col[e]);
+                    GQ.val.push_back(g_value(l, i, e));
+                }
+                for (int32_t e = Q[l].ptr[i]; e < Q[l].ptr[i + 1]; ++e) {
+                    GQ.col.push_back(n + Q[l].col[e]);
+                    GQ.val.push_back(Q[l].val[e]);
+                }
+                GQ.ptr[(size_t)i + 1] = (int32_t)GQ.col.size();
+            }
+            lv.GQ = tuned_spmat<T>(c, GQ, ("[G Q]" + id).c_str(), false, true);
+        }
+        if (l == t - 1 && merged) continue;
+        if (l > 0 || h.direct)
+            lv.R = tuned_spmat<T>(c, transpose(Q[l]), ("R" + id + "(I-AwD^-1)").c_str(), false, true);
+        else
+            lv.R = tuned_spmat<T>(c, ah.R[l], ("R" + id).c_str(), false, true);
+    }
+}
+
+template <typename T>
+static void upload_hierarchy(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
+    h = Hierarchy<T>{};
+    h.lv.resize(ah.A.size());
+    for (size_t l = 0; l < ah.A.size(); ++l) {
+        h.lv[l].n = ah.A[l].n_rows;
+        h.lv[l].A.nnz = ah.A[l].nnz();
+        h.lv[l].omega = ah.omega[l];
+    }
+    if (c->fold && ah.A.size() > 1) upload_folded<T>(c, ah, h);
+    else upload_plain<T>(c, ah, h);
 }
 
 // Morton key of a point quantised to 21 bits per axis inside the box [lo, hi].
@@ -1565,9 +1600,9 @@ void upload(eqs_ctx* c) {
     c->M.xcd = 1;  // the CG SpMV walks its row blocks in the XCD order (row_block in sell.h)
     c->tune_log += std::string("M: sell64") + (c->M.perm ? "s (rows sorted within 256-row windows)" : "") + ", " +
                    (c->M.d16 ? "16-bit column offsets\n" : "32-bit columns\n");
-    AmgHost ah = build_sa_amg(M, c->amg);
-    if (c->amg.precision == EQS_PREC_FP32) upload_hierarchy<float>(c, ah, c->h32, nullptr);
-    else upload_hierarchy<double>(c, ah, c->h64, nullptr);
+    AmgHost ah = build_sa_amg(M, c->amg, c->fold);
+    if (c->amg.precision == EQS_PREC_FP32) upload_hierarchy<float>(c, ah, c->h32);
+    else upload_hierarchy<double>(c, ah, c->h64);
 
     auto vec = [&](int64_t n) { return (double*)dev_alloc(c, sizeof(double) * (size_t)n); };
     c->d_r = vec(NF); c->d_z = vec(NF); c->d_p = vec(NF); c->d_q = vec(NF); c->d_mx = vec(NF);
@@ -1631,8 +1666,8 @@ void free_device(eqs_ctx* c) {
         if (e) { (void)hipEventDestroy(e); e = nullptr; }
     c->M = Sell<double>{};
     c->stage_iters.clear();
-    c->h64.lv.clear();
-    c->h32.lv.clear();
+    c->h64 = Hierarchy<double>{};
+    c->h32 = Hierarchy<float>{};
     c->d_tpack = nullptr; c->d_bnodes = nullptr; c->d_boff = nullptr; c->n_blocks = 0; c->max_block_nodes = 0; c->n_block_nodes = 0;
     c->d_kslots = nullptr; c->d_kend = nullptr; c->d_occ_off = nullptr; c->d_occ = nullptr; c->d_kx_part = nullptr;
     c->d_cx = c->d_cy = c->d_cz = nullptr; c->d_mats = nullptr; c->tet_tpt = 0;
