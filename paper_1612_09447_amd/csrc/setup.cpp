@@ -1182,9 +1182,12 @@ static void upload_plain(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
 // Up to this many finest rows the restriction is the folded Q_0^T on r itself:
 // 8.8 entries per fine row (first-order stencil) against 7 + 3.6 in the
 // pre-smoothing kernel and R_0, but one launch instead of two and one more
-// product inside the last kernel. The smaller cycles are bound by the launches
-// (4-6 us each), the larger by the entries' bytes.
-constexpr int32_t kDirectRows = 500000;
+// product inside the last kernel. Small cycles are bound by the launches and
+// their chains of dependent loads, large ones by the entries' bytes. RKC(8)
+// steps, direct against pre-smoothed: 4.22 / 4.55 ms at 31,713 rows (FP32),
+// 4.80 / 5.00 at 63,878 (FP64), 5.85 / 5.88 at 130,000 (FP32), 10.6 / 10.2
+// (12 stages) at 266,175 (FP64).
+constexpr int32_t kDirectRows = 100000;
 
 // Folded cycle, formed here in FP64. A V(1,1) visit of a level l that is not
 // the bottom is, with x = w D^-1 b, res = b - A x, x += P x_next,
