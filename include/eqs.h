@@ -467,7 +467,7 @@ int eqs_galerkin_start(eqs_ctx *ctx, int32_t k, const double *S_dev, const doubl
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * result as eqs_galerkin_start, with the same arguments and errors, but its
- * dot-product scratch is a static device array of the library (287,232 bytes
+ * dot-product scratch is a static device array of the library (1,081,344 bytes
  * per GPU, held until the process ends) instead of context memory allocated
  * on first use; the call allocates nothing. k is limited to 16 (the scratch
  * holds the dots of 16 columns); a larger k gives EQS_ERR_INVALID_ARG. All

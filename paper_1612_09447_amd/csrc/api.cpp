@@ -664,8 +664,7 @@ int eqs_galerkin_start_noalloc(eqs_ctx* c, int32_t k, const double* S_dev, const
              "x0 must not overlap S, R or r");
         bind_device(c);
         double* base = eqs::noalloc_scratch(c->device);
-        const int m = eqs::guess_galerkin_explicit(c, k, S_dev, R_dev, r_dev, x0_dev, base,
-                                                   base + eqs::kNoAllocPartDoubles);
+        const int m = eqs::guess_galerkin_explicit(c, k, S_dev, R_dev, r_dev, x0_dev, base);
         EQS_HIP(hipStreamSynchronize(c->stream));
         if (m_out) *m_out = m;
         return EQS_OK;

@@ -188,7 +188,6 @@ struct GuessState {
     double* d_guard = nullptr;        // [16 x 16 + 16 + 1] reduced matrix, RHS change, scale (network guard)
     double* h_guard = nullptr;        // pinned staging of d_guard
     int32_t* d_gstat = nullptr;       // [2] network corrections kept / dropped on the device
-    double* d_dots = nullptr;
     double* d_part = nullptr;
     float *d_bx = nullptr, *d_bt = nullptr;  // minibatch staging
     float* h_stage = nullptr;         // pinned
@@ -310,6 +309,8 @@ struct eqs_ctx {
     eqs::PcgScalars* d_hscal = nullptr;  // its device-side address
     eqs::PcgSummary* h_sum = nullptr;    // pinned host mirror of the summary
     eqs::PcgSummary* d_hsum = nullptr;
+    double* h_dots = nullptr;            // pinned host memory for summed dot products (start vectors)
+    double* d_hdots = nullptr;           // its device-side address
     hipEvent_t ev[2] = {nullptr, nullptr};
 
     // Device memory: every buffer of the context comes from dev_alloc, either
@@ -471,12 +472,13 @@ void guess_release(eqs_ctx* c);
 void guess_reset(eqs_ctx* c);
 int guess_stage(eqs_ctx* c);
 int guess_galerkin_explicit(eqs_ctx* c, int k, const double* S, const double* R, const double* r, double* x0,
-                            double* part = nullptr, double* dots_dev = nullptr);
+                            double* part = nullptr);
 // static device scratch of eqs_galerkin_start_noalloc: set up once per device
 // (with that device current), then its address on a device
 void noalloc_scratch_init(int device);
 double* noalloc_scratch(int device);
-constexpr int64_t kNoAllocPartDoubles = (2 * 16 + 3) * 1024;  // dot partials ahead of the 64 summed dots
+constexpr int64_t kNoAllocPartDoubles = (2 * 16 * 16 + 16) * 256;  // dot partials of one call
+constexpr int kHostDots = 2 * 16 * 16 + 16;                        // summed dots (pinned host memory)
 void guess_after_solve(eqs_ctx* c, int32_t iters);
 void guess_train(eqs_ctx* c);
 double guess_last_loss(eqs_ctx* c);

@@ -38,22 +38,45 @@ constexpr int kNDots = 2 * kMaxWin + 3;
 constexpr int kDotGrid = 1024;
 constexpr int kGuardLen = 16 * 16 + 16 + 1;
 constexpr int kMaxPairsPerStage = 256;  // minibatches of up to 64 pairs, one Adam step each
-constexpr int kNoAllocScratch = kNDots * kDotGrid + 64;  // doubles of the static scratch
-static_assert(kNoAllocPartDoubles == (int64_t)kNDots * kDotGrid, "static scratch layout");
+constexpr int kGramVals = 2 * kMaxWin * kMaxWin + kMaxWin;  // S^T S, S^T R, S^T r
+constexpr int kGramGrid = 256;                               // its workgroups
+constexpr int64_t kPartDoubles = std::max<int64_t>((int64_t)kNDots * kDotGrid, (int64_t)kGramVals * kGramGrid);
+static_assert(kNoAllocPartDoubles == kPartDoubles, "static scratch layout");
+static_assert(kHostDots >= kGramVals && kHostDots >= kNDots, "pinned dots");
 
-// ------------------------------------------------------------- kernels
-template <int NQ>
-__device__ __forceinline__ void block_sums_store(double (&v)[NQ], double* __restrict__ part, int64_t stride) {
-    __shared__ double sh[NQ][4];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+// ---- window passes -------------------------------------------------------
+// The window's columns are read by lanes: lane l of a wavefront serves column
+// l % 16 and, of a chunk of 16 rows, the rows 4 (l / 16) .. +3 (two 16-byte
+// loads; the four lanes of a column read one 128-byte line). A dot product
+// with every column is then one accumulator per lane, summed over four lanes
+// at the end, instead of one per column and thread summed over the block.
+struct Quad {
+    double x[4];
+};
+// rows i..i+3 of p (8-byte aligned), zeros past n
+__device__ __forceinline__ Quad load_quad(const double* __restrict__ p, int64_t i, int64_t n) {
+    Quad q;
+    if (i + 4 <= n) {
+        __builtin_memcpy(q.x, __builtin_assume_aligned(p + i, 8), sizeof q.x);
+    } else {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        double x = v[q];
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-        if (lane == 0) sh[q][wid] = x;
+        for (int j = 0; j < 4; ++j) q.x[j] = i + j < n ? p[i + j] : 0.0;
     }
-    __syncthreads();
-    for (int q = threadIdx.x; q < NQ; q += blockDim.x) part[q * stride + blockIdx.x] = ((sh[q][0] + sh[q][1]) + sh[q][2]) + sh[q][3];
+    return q;
+}
+__device__ __forceinline__ Quad select_quad(bool keep, const Quad& q) {
+    Quad r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.x[j] = keep ? q.x[j] : 0.0;
+    return r;
+}
+__device__ __forceinline__ void dot_quad(double& acc, const Quad& a, const Quad& b) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc += a.x[j] * b.x[j];
+}
+__device__ __forceinline__ double over_rows(double v) {  // the four lanes of a column
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
 }
 
 // S^T u, S^T v for the first nslot slots, and u.u, u.v, u.w;
@@ -63,26 +86,105 @@ __global__ __launch_bounds__(256) void k_window_dots(double* __restrict__ S, int
                                                       const double* __restrict__ u, const double* __restrict__ v,
                                                       const double* __restrict__ w, int64_t n,
                                                       double* __restrict__ part) {
-    double acc[kNDots];
+    __shared__ double sh[4][kNDots];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane & 15, g = lane >> 4;
+    const double* Sa = S + (int64_t)min(a, max(nslot - 1, 0)) * ld;
+    double su = 0.0, sv = 0.0, uu = 0.0, uv = 0.0, uw = 0.0;
+    for (int64_t c = (int64_t)blockIdx.x * 4 + wave; c * 16 < n; c += (int64_t)gridDim.x * 4) {
+        const int64_t i = c * 16 + 4 * g;
+        const Quad s = select_quad(a < nslot, load_quad(Sa, i, n));
+        const Quad qu = load_quad(u, i, n), qv = load_quad(v, i, n), qw = load_quad(w, i, n);
+        dot_quad(su, s, qu);
+        dot_quad(sv, s, qv);
+        dot_quad(uu, qu, qu);
+        dot_quad(uv, qu, qv);
+        dot_quad(uw, qu, qw);
+        if (a == ins)
 #pragma unroll
-    for (int q = 0; q < kNDots; ++q) acc[q] = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double ui = u[i], vi = v[i], wi = w[i];
-        double sk[kMaxWin];
-#pragma unroll
-        for (int k = 0; k < kMaxWin; ++k) sk[k] = S[(int64_t)min(k, max(nslot - 1, 0)) * ld + i];
-#pragma unroll
-        for (int k = 0; k < kMaxWin; ++k) {
-            const double d = k < nslot ? sk[k] : 0.0;
-            acc[2 * k] += d * ui;
-            acc[2 * k + 1] += d * vi;
-        }
-        acc[2 * kMaxWin] += ui * ui;
-        acc[2 * kMaxWin + 1] += ui * vi;
-        acc[2 * kMaxWin + 2] += ui * wi;
-        if (ins >= 0) S[(int64_t)ins * ld + i] = ui;
+            for (int j = 0; j < 4; ++j)
+                if (i + j < n) S[(int64_t)ins * ld + i + j] = qu.x[j];
     }
-    block_sums_store<kNDots>(acc, part, kDotGrid);
+    su = over_rows(su);
+    sv = over_rows(sv);
+    uu = over_rows(uu);
+    uv = over_rows(uv);
+    uw = over_rows(uw);
+    if (g == 0) {
+        sh[wave][2 * a] = su;
+        sh[wave][2 * a + 1] = sv;
+        if (a == 0) {
+            sh[wave][2 * kMaxWin] = uu;
+            sh[wave][2 * kMaxWin + 1] = uv;
+            sh[wave][2 * kMaxWin + 2] = uw;
+        }
+    }
+    __syncthreads();
+    const int q = threadIdx.x;
+    if (q < kNDots) part[q * (int64_t)kDotGrid + blockIdx.x] = ((sh[0][q] + sh[1][q]) + sh[2][q]) + sh[3][q];
+}
+static unsigned dots_grid(int64_t n) { return (unsigned)std::min<int64_t>(kDotGrid, (n + 63) / 64); }
+
+// G = S^T S, H = S^T R and S^T r of k <= 16 columns in one pass over S, R and r:
+// the two 16 x 16 products are FP64 matrix instructions (16 x 16 x 4: a lane's
+// value is row 4 g + j of column a as both operands' entry, so S serves as A
+// and B of G and as A of H), S^T r a multiply-add per value. Element (i, j) of
+// a product sits in lane 16 (i % 4) + j, register i / 4. Bound by the 2 k + 1
+// columns it reads: 2.1M rows, k = 16, 558 MB. (One pass of k_window_dots per
+// column, each followed by a host wait, took 17 x 56 us for the same sums.)
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kGramWaves = 16;
+__global__ __launch_bounds__(64 * kGramWaves) void k_window_gram(const double* __restrict__ S,
+                                                                 const double* __restrict__ R,
+                                                                 const double* __restrict__ r, int64_t ld, int k,
+                                                                 int64_t n, double* __restrict__ part) {
+    __shared__ double sh[kGramWaves / 2][kGramVals];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, a = lane & 15, g = lane >> 4;
+    const double* Sa = S + (int64_t)min(a, k - 1) * ld;
+    const double* Ra = R + (int64_t)min(a, k - 1) * ld;
+    const bool col = a < k;
+    f64x4 G = {0.0, 0.0, 0.0, 0.0}, H = {0.0, 0.0, 0.0, 0.0};
+    double sr = 0.0;
+    for (int64_t c = (int64_t)blockIdx.x * kGramWaves + wave; c * 16 < n; c += (int64_t)gridDim.x * kGramWaves) {
+        const int64_t i = c * 16 + 4 * g;
+        const Quad s = select_quad(col, load_quad(Sa, i, n)), t = select_quad(col, load_quad(Ra, i, n));
+        const Quad q = load_quad(r, i, n);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            G = __builtin_amdgcn_mfma_f64_16x16x4f64(s.x[j], s.x[j], G, 0, 0, 0);
+            H = __builtin_amdgcn_mfma_f64_16x16x4f64(s.x[j], t.x[j], H, 0, 0, 0);
+        }
+        dot_quad(sr, s, q);
+    }
+    sr = over_rows(sr);
+    // halves of the waves in turn, so that their values fit the LDS; fixed order
+    for (int half = kGramWaves / 2; half >= 1; half /= 2) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                sh[wave - half][64 * q + lane] = G[q];
+                sh[wave - half][256 + 64 * q + lane] = H[q];
+            }
+            if (g == 0) sh[wave - half][512 + a] = sr;
+        }
+        __syncthreads();
+        if (wave < half) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                G[q] += sh[wave][64 * q + lane];
+                H[q] += sh[wave][256 + 64 * q + lane];
+            }
+            if (g == 0) sr += sh[wave][512 + a];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            part[(64 * q + lane) * (int64_t)kGramGrid + blockIdx.x] = G[q];
+            part[(256 + 64 * q + lane) * (int64_t)kGramGrid + blockIdx.x] = H[q];
+        }
+        if (g == 0) part[(512 + a) * (int64_t)kGramGrid + blockIdx.x] = sr;
+    }
 }
 
 // out[q] = sum of part[q][0..nb) in a fixed order (one block per value).
@@ -275,9 +377,8 @@ static int64_t rounded(int64_t b) { return (b + 255) / 256 * 256; }
 int64_t guess_pending_bytes(const eqs_ctx* c) {
     const GuessState& g = c->guess;
     const int64_t NF = c->n_free;
-    const int64_t scratch = rounded(sizeof(double) * kNDots * kDotGrid) + rounded(sizeof(double) * 64);
-    const int64_t have = (g.d_part ? rounded(sizeof(double) * kNDots * kDotGrid) : 0) +
-                         (g.d_dots ? rounded(sizeof(double) * 64) : 0);
+    const int64_t scratch = rounded(sizeof(double) * kPartDoubles);
+    const int64_t have = g.d_part ? scratch : 0;
     if (g.p.kind >= EQS_GUESS_GALERKIN && !g.dev_ready) {
         const int64_t full = rounded(sizeof(double) * (int64_t)kMaxWin * NF) + rounded(sizeof(double) * NF) +
                              rounded(sizeof(double) * kMaxWin) + scratch + rounded(sizeof(double) * kGuardLen) +
@@ -289,11 +390,22 @@ int64_t guess_pending_bytes(const eqs_ctx* c) {
     return scratch - have;  // the dot scratch is allocated at upload, so normally 0
 }
 
-// The dot scratch of eqs_galerkin_start, allocated with the context's other buffers.
+// The dot scratch of the window passes, allocated with the context's other
+// buffers; the summed dots go to pinned host memory.
 void guess_alloc_scratch(eqs_ctx* c) {
     GuessState& g = c->guess;
-    if (!g.d_part) g.d_part = (double*)dev_alloc(c, sizeof(double) * kNDots * kDotGrid);
-    if (!g.d_dots) g.d_dots = (double*)dev_alloc(c, sizeof(double) * 64);
+    if (!g.d_part) g.d_part = (double*)dev_alloc(c, sizeof(double) * kPartDoubles);
+    if (!c->h_dots) {
+        EQS_HIP(hipHostMalloc((void**)&c->h_dots, sizeof(double) * kHostDots, hipHostMallocMapped));
+        EQS_HIP(hipHostGetDevicePointer((void**)&c->d_hdots, c->h_dots, 0));
+    }
+}
+
+// The sums of nq rows of block partials, in c->h_dots once this returns.
+static void sum_dots(eqs_ctx* c, const double* part, int64_t stride, int nq, int nb) {
+    hipLaunchKernelGGL(k_sum_rows, dim3((unsigned)nq), dim3(kBlock), 0, c->stream, part, stride, nb, c->d_hdots);
+    EQS_HIP(hipGetLastError());
+    EQS_HIP(hipStreamSynchronize(c->stream));
 }
 
 // Basis from the Gram matrix of the current window (slots in age order).
@@ -384,10 +496,10 @@ static bool galerkin_coef(const Basis& B, const std::vector<double>& K, const do
 
 // ------------------------------------------- scratch that needs no allocation
 // The dot-product partials of eqs_galerkin_start_noalloc live in this array,
-// one copy per GPU for the life of the process: kNDots x kDotGrid block
-// partials, then 64 summed dots (287,232 bytes). Host code reaches it only
-// through the address hipGetSymbolAddress returns for the current device.
-static __device__ __align__(256) double scratch[kNoAllocScratch];
+// one copy per GPU for the life of the process (1,081,344 bytes). Host code
+// reaches it only through the address hipGetSymbolAddress returns for the
+// current device.
+static __device__ __align__(256) double scratch[kPartDoubles];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -412,20 +524,18 @@ double* noalloc_scratch(int device) {
 }
 
 // Eq. (5) on a window given by the caller (k columns of S, oldest first, with
-// R = M S): G = S^T S and H = S^T R from k passes of the window-dots kernel,
-// S^T r from one more, then the basis, reduced matrix and coefficient solve of
-// a stage's GALERKIN start vector and x0 = S alpha. Returns the number of
-// directions kept (0: x0 = 0). The dot partials go to `part` (kNDots x
-// kDotGrid doubles) and `dots` (64 doubles), or, when part is NULL, to the
-// context's start-vector scratch (allocated on first use). Runs on c->stream.
+// R = M S): G = S^T S, H = S^T R and S^T r from one pass over the columns
+// (k_window_gram), then the basis, reduced matrix and coefficient solve of a
+// stage's GALERKIN start vector and x0 = S alpha. Returns the number of
+// directions kept (0: x0 = 0). The dot partials go to `part` (kPartDoubles
+// doubles) or, when part is NULL, to the context's start-vector scratch.
+// Runs on c->stream.
 int guess_galerkin_explicit(eqs_ctx* c, int k, const double* S, const double* R, const double* r, double* x0,
-                            double* part, double* dots_dev) {
-    GuessState& gs = c->guess;
+                            double* part) {
     if (!part) {
         // only the dot-product scratch is needed here (not the stage window)
         guess_alloc_scratch(c);
-        part = gs.d_part;
-        dots_dev = gs.d_dots;
+        part = c->guess.d_part;
     }
     hipStream_t s = c->stream;
     const int64_t NF = c->n_free;
@@ -436,28 +546,17 @@ int guess_galerkin_explicit(eqs_ctx* c, int k, const double* S, const double* R,
     g.G.assign(kMaxWin * kMaxWin, 0.0);
     g.H.assign(kMaxWin * kMaxWin, 0.0);
     std::vector<double> rs(kMaxWin, 0.0);
-    const unsigned grid = (unsigned)std::min<int64_t>(kDotGrid, (NF + kBlock - 1) / kBlock);
-    double dots[kNDots];
-    for (int a = 0; a <= k; ++a) {
-        // u = s_a, v = r_a (column a of G and H); the last pass u = v = r
-        const double* u = a < k ? S + (int64_t)a * NF : r;
-        const double* v = a < k ? R + (int64_t)a * NF : r;
-        hipLaunchKernelGGL(k_window_dots, dim3(grid), dim3(kBlock), 0, s, const_cast<double*>(S), NF, k, -1, u, v, v,
-                           NF, part);
-        hipLaunchKernelGGL(k_sum_rows, dim3(kNDots), dim3(kBlock), 0, s, part, (int64_t)kDotGrid, (int)grid,
-                           dots_dev);
-        EQS_HIP(hipMemcpyAsync(dots, dots_dev, sizeof dots, hipMemcpyDeviceToHost, s));
-        EQS_HIP(hipStreamSynchronize(s));
+    const unsigned grid = (unsigned)std::min<int64_t>(kGramGrid, (NF + 16 * kGramWaves - 1) / (16 * kGramWaves));
+    hipLaunchKernelGGL(k_window_gram, dim3(grid), dim3(64 * kGramWaves), 0, s, S, R, r, NF, k, NF, part);
+    sum_dots(c, part, kGramGrid, kGramVals, (int)grid);
+    for (int a = 0; a < k; ++a) {
         for (int b = 0; b < k; ++b) {
-            if (a < k) {
-                g.G[b * kMaxWin + a] = dots[2 * b];      // s_b . s_a
-                g.H[b * kMaxWin + a] = dots[2 * b + 1];  // s_b . M s_a
-            } else {
-                rs[b] = dots[2 * b];  // s_b . r
-            }
+            g.G[b * kMaxWin + a] = c->h_dots[b * kMaxWin + a];                        // s_b . s_a
+            g.H[b * kMaxWin + a] = c->h_dots[kMaxWin * kMaxWin + b * kMaxWin + a];  // s_b . M s_a
         }
+        rs[a] = c->h_dots[2 * kMaxWin * kMaxWin + a];  // s_a . r
     }
-    for (int a = 0; a < k; ++a)  // both are symmetric; each pair was summed twice
+    for (int a = 0; a < k; ++a)  // both are symmetric up to rounding
         for (int b = a + 1; b < k; ++b) {
             const double gv = 0.5 * (g.G[a * kMaxWin + b] + g.G[b * kMaxWin + a]);
             const double hv = 0.5 * (g.H[a * kMaxWin + b] + g.H[b * kMaxWin + a]);
@@ -503,14 +602,11 @@ int guess_stage(eqs_ctx* c) {
                                       g.last_iters > g.p.add_threshold);
     // fused pass over the window with u = F_{j-1}, v = r_j, w = r_{j-1}; it
     // also stores F_{j-1} in slot e
-    const unsigned grid = (unsigned)std::min<int64_t>(kDotGrid, (NF + kBlock - 1) / kBlock);
+    const unsigned grid = dots_grid(NF);
     hipLaunchKernelGGL(k_window_dots, dim3(grid), dim3(kBlock), 0, s, g.d_S, NF, n_old, insert ? e : -1, c->d_F,
                        c->d_rhs, g.d_rprev, NF, g.d_part);
-    hipLaunchKernelGGL(k_sum_rows, dim3(kNDots), dim3(kBlock), 0, s, g.d_part, (int64_t)kDotGrid, (int)grid,
-                       g.d_dots);
-    double dots[kNDots];
-    EQS_HIP(hipMemcpyAsync(dots, g.d_dots, sizeof dots, hipMemcpyDeviceToHost, s));
-    EQS_HIP(hipStreamSynchronize(s));
+    sum_dots(c, g.d_part, kDotGrid, kNDots, (int)grid);
+    const double* dots = c->h_dots;
     double Su[kMaxWin], Sv[kMaxWin];
     for (int k = 0; k < kMaxWin; ++k) {
         Su[k] = k < n_old ? dots[2 * k] : 0.0;

@@ -655,7 +655,7 @@ void visit_device_ptrs(eqs_ctx* c, const std::function<void(void**)>& f) {
     f((void**)&c->d_sum);
     f((void**)&c->d_force);
     GuessState& g = c->guess;
-    for (double** q : {&g.d_S, &g.d_rprev, &g.d_alpha, &g.d_guard, &g.d_dots, &g.d_part}) f((void**)q);
+    for (double** q : {&g.d_S, &g.d_rprev, &g.d_alpha, &g.d_guard, &g.d_part}) f((void**)q);
     f((void**)&g.d_gstat);
     f((void**)&g.d_bx);
     f((void**)&g.d_bt);
@@ -1663,6 +1663,7 @@ void free_device(eqs_ctx* c) {
     c->device_bytes = 0;
     ws_reset(c);  // a workspace stays attached, empty
     if (c->h_scal) { (void)hipHostFree(c->h_scal); c->h_scal = nullptr; c->d_hscal = nullptr; }
+    if (c->h_dots) { (void)hipHostFree(c->h_dots); c->h_dots = nullptr; c->d_hdots = nullptr; }
     if (c->h_sum) { (void)hipHostFree(c->h_sum); c->h_sum = nullptr; c->d_hsum = nullptr; }
     c->d_sum = nullptr; c->d_inst_row = nullptr; c->d_blk_inst = nullptr; c->d_force = nullptr;
     for (auto& e : c->ev)
@@ -1684,7 +1685,7 @@ void free_device(eqs_ctx* c) {
     c->built = false;
     c->have_Flast = false;
     c->guess.dev_ready = false;
-    c->guess.d_S = c->guess.d_rprev = c->guess.d_alpha = c->guess.d_dots = c->guess.d_part = nullptr;
+    c->guess.d_S = c->guess.d_rprev = c->guess.d_alpha = c->guess.d_part = nullptr;
     c->guess.d_guard = nullptr;
     c->guess.d_gstat = nullptr;
     c->guess.d_bx = c->guess.d_bt = nullptr;
