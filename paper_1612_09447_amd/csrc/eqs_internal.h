@@ -76,6 +76,19 @@ struct Sell {
     int32_t xcd = 0;            // 1: products walk row blocks in the XCD order (row_block in sell.h)
 };
 
+// A symmetric matrix by diagonals: entry (i, i + d_k) of the K upper diagonals
+// at val[(k + 1) n + i], the diagonal at val[i], zero where there is none; the
+// lower triangle is the upper one read at row i - d_k. The offsets d_k
+// (increasing) may differ between instances. K = 0: not stored this way.
+constexpr int kMaxDiagonals = 7;
+template <typename T>
+struct Dia {
+    int32_t K = 0, n = 0;
+    int32_t off[kMaxDiagonals] = {};  // of the first instance
+    T* val = nullptr;                 // [(K + 1) n]
+    int32_t* offs = nullptr;          // [n_inst][K], with several instances
+};
+
 // A hierarchy operator in one of two layouts, chosen per matrix by timing
 // (or, without the autotuner, from its mean row length): SELL (1, 2, 4 or 8
 // lanes per row, sell.lanes), or CSR with `lanes` lanes per row (a power of
@@ -133,6 +146,20 @@ struct PcgScalars {
     int32_t status;  // EQS_OK / EQS_ERR_NOT_CONVERGED / EQS_ERR_BREAKDOWN
     int32_t fresh;   // 1: next beta is 0 (first iteration or restart)
     int32_t flexible;
+    int32_t apply;   // finaliser form: 1 if the current iteration's update is to be applied
+    int32_t pad;
+};
+
+// What the CG SpMV's workgroups found out about an instance from the r.z
+// partials, for the update of the same iteration (see k_pcg_spmv).
+struct PcgStep {
+    double rho;      // r.z
+    double bb, tol2;
+    int32_t it, maxit;
+    int32_t done;    // as before the iteration
+    int32_t brk;     // 0; 1: r.z not positive or not finite; 2: r.z = 0
+    int32_t fresh;   // first iteration of a solve or restart
+    int32_t pad;
 };
 
 // Summary of all instances' CG states (written by the finalisers).
@@ -159,6 +186,8 @@ struct Level {
     // a V(1,1) visit of a level is b_next = Q^T b, then out = G b + Q x_next.
     SpMat<T> GQ;  // levels between the finest and the bottom: [G Q] on the stacked [b; x_next]
     SpMat<T> Q;   // finest level
+    Dia<T> D;     // finest level: A by diagonals (then A.sell holds nothing) ...
+    T* w = nullptr;  // ... and w D^-1, its column scaling in the pre-smoothing product
     // bottom level, when small enough: dense n x coarse_R_cols matrix from the
     // level above's input (its b; the finest level's residual or right-hand
     // side) straight to the bottom's solution, row-major
@@ -280,6 +309,7 @@ struct eqs_ctx {
 
     // device: M and the hierarchy
     eqs::Sell<double> M;
+    eqs::Dia<double> Mdia;  // M by diagonals for CG, where it has few (diagonals_of in setup.cpp)
     eqs::Hierarchy<double> h64;
     eqs::Hierarchy<float> h32;
 
@@ -291,7 +321,7 @@ struct eqs_ctx {
     double *d_rhs = nullptr, *d_rhs_alt = nullptr;  // the stage RHS, and the next stage's when it is formed early
     double *d_tmpN = nullptr, *d_tmpN2 = nullptr;  // n_nodes
     bool have_Flast = false;
-    double* d_partials = nullptr;  // 4 * max_blocks doubles
+    double* d_partials = nullptr;  // 6 arrays of 2 * max_blocks doubles
     int64_t max_blocks = 0;
     // independent instances (a batch): contiguous node, tet and free-row ranges
     int64_t n_inst = 1;
@@ -304,6 +334,7 @@ struct eqs_ctx {
     std::vector<double> inst_relres;  // largest final relative residual per instance over the same
 
     eqs::PcgScalars* d_scal = nullptr;   // [n_inst]
+    eqs::PcgStep* d_step = nullptr;      // [n_inst]
     eqs::PcgSummary* d_sum = nullptr;
     eqs::PcgScalars* h_scal = nullptr;   // pinned host mirror of d_scal, written by the finalisers
     eqs::PcgScalars* d_hscal = nullptr;  // its device-side address
@@ -325,6 +356,7 @@ struct eqs_ctx {
     std::map<int64_t, int64_t> ws_free;  // free ranges of the workspace: offset -> length
     bool index16 = true;   // 16-bit column offsets for SELL operators whose entries allow them
     bool autotune = true;  // time the candidate layouts of every AMG operator at build time
+    bool diagonals = true;  // matrices of few diagonals are stored by them
     bool fold = true;       // fold pre-smoothers into restrictions and the lowest two levels into two products
     int force_layout = -1;      // >= 1: SELL with that many lanes per row, 0: CSR, for every coarse operator
     bool force_sorted = false;  // with force_layout >= 1: sorted rows where allowed
@@ -441,7 +473,6 @@ void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int 
 // flight; the kernels act only if that iteration completed every instance
 void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, double* mx_out = nullptr,
                        bool only_if_done = false);
-void pcg_zero_rhs_rows(hipStream_t s, eqs_ctx* c, double* x);
 
 template <typename T>
 void vcycle(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* r, double* z, double* part_rz,
@@ -552,6 +583,7 @@ void prof_end(eqs_ctx* c, int cls, hipStream_t s);
 // next start/stop pair of a profiled single-kernel class (false: not profiled);
 // cls2 (or -1): a second class whose work the launch does too
 bool prof_pair(eqs_ctx* c, int cls, hipEvent_t* e0, hipEvent_t* e1, int cls2 = -1);
+void prof_again(eqs_ctx* c, int cls);
 void prof_release(eqs_ctx* c);
 
 // drivers (solver.cpp)

@@ -161,7 +161,7 @@ __device__ __forceinline__ void inst_blocks(const InstMap& m, int32_t i, int32_t
 template <int NP>
 __device__ __forceinline__ void wave_range_sums(const double* const (&parts)[NP], int32_t lo, int32_t hi,
                                                 double (&out)[NP]) {
-    constexpr int U = 16;
+    constexpr int U = NP <= 2 ? 16 : 8;  // loads in flight per lane and array (registers: 2 NP U)
     const int lane = threadIdx.x & 63;
     double acc[NP];
 #pragma unroll
@@ -242,6 +242,54 @@ __device__ __forceinline__ void for_each_instance_sum(const double* const (&part
         }
         body(i0 + k, sums);
     }
+}
+
+// ---- reductions by the consumer -----------------------------------------
+// Up to kProBlocks blocks per instance, the kernel that needs an instance's
+// dot products sums the producer's block partials itself, every workgroup the
+// same way (fixed order, so all get the same value): at most kProU loads per
+// thread and array, which travel together with the kernel's own first loads.
+// A finaliser launch in between costs 4-6 us (its launch, a chain of loads,
+// the sum, the stores of the scalars), more than a small SpMV; with more blocks
+// every workgroup would read more partials than rows.
+constexpr int kProU = 5;
+constexpr int kProBlocks = 256 * kProU + 1;
+template <int NP>
+struct ProParts {
+    double t[NP][kProU], h[NP];
+    int32_t lo, hi;
+};
+template <int NP>
+__device__ __forceinline__ void pro_load(const double* const (&parts)[NP], const InstMap& m, int32_t i, ProParts<NP>& P) {
+    int32_t b0, b1, head;
+    inst_blocks(m, i, b0, b1, head);
+    P.lo = b0 + 1 + (int32_t)threadIdx.x;
+    P.hi = b1;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        P.h[p] = threadIdx.x == 0 && b1 >= b0 ? parts[p][2 * (int64_t)b0 + head] : 0.0;
+#pragma unroll
+        for (int u = 0; u < kProU; ++u) {
+            const int32_t b = P.lo + 256 * u;
+            P.t[p][u] = b <= P.hi ? parts[p][2 * (int64_t)b] : 0.0;
+        }
+    }
+}
+// every thread gets the sums; sh: 4 NP doubles used by this call only
+template <int NP>
+__device__ __forceinline__ void pro_sum(const ProParts<NP>& P, double* sh, double (&out)[NP]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        double v = P.h[p];
+#pragma unroll
+        for (int u = 0; u < kProU; ++u) v += P.t[p][u];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0) sh[4 * p + wave] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NP; ++p) out[p] = ((sh[4 * p] + sh[4 * p + 1]) + sh[4 * p + 2]) + sh[4 * p + 3];
 }
 
 // ------------------------------------------------------------- simple ops
@@ -944,6 +992,75 @@ static unsigned sell_grid(const Sell<T>& A) {
     return (unsigned)(((int64_t)A.n_slices * kSlice + kBlock - 1) / kBlock);
 }
 
+// ---- row sums of the finest matrices, in either storage -------------------
+// Op::sum(g, row, m, inst, f) is sum_j a_ij f(j) for the row of global thread g,
+// `inst` the row's instance; one thread per row, workgroups of 256 rows.
+template <typename T>
+struct SellOp {
+    SellView<T> A;
+    __device__ __forceinline__ int64_t block() const { return row_block(A.xcd); }
+    __device__ __forceinline__ bool live(int64_t g) const { return g < (int64_t)A.n_slices * 64; }
+    __device__ __forceinline__ int32_t row(int64_t g) const { return sell_perm_row<1>(A.perm, g); }
+    __device__ __forceinline__ int32_t rows() const { return A.n_rows; }
+    template <typename F>
+    __device__ __forceinline__ T sum(int64_t g, int32_t row, const InstMap&, int32_t, F f) const {
+        return sell_accum<1>(A, g, row, f);
+    }
+};
+// By diagonals (Dia): no slice table and no column ids, so a row's 2 K + 1
+// values and operands are one round of independent, contiguous loads instead of
+// three dependent ones, and half of the values come from the cache (the lower
+// triangle is the upper one of an earlier row): 32 B of matrix a row in FP64
+// instead of 70, 16 instead of 42 in FP32. At 2.1M rows the CG SpMV takes %SPMV%
+// us instead of 46 and the pre-smoother %PRE% instead of 27. Terms are added in
+// column order; an absent entry (zero) adds nothing whatever its operand.
+template <typename T, int K>
+struct DiaOp {
+    const T* __restrict__ val;
+    const int32_t* __restrict__ offs;
+    int32_t n;
+    int32_t off[K];
+    __device__ __forceinline__ int64_t block() const { return row_block(1); }
+    __device__ __forceinline__ bool live(int64_t g) const { return g < n; }
+    __device__ __forceinline__ int32_t row(int64_t g) const { return (int32_t)g; }
+    __device__ __forceinline__ int32_t rows() const { return n; }
+    template <typename F>
+    __device__ __forceinline__ T sum(int64_t, int32_t row, const InstMap& m, int32_t inst, F f) const {
+        const int32_t r0 = m.rows1 >= 0 ? 0 : m.row_off[inst];
+        T v[2 * K + 1], x[2 * K + 1];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t d = offs ? offs[inst * K + k] : off[k];
+            const int32_t jl = row - d >= r0 ? row - d : row, ju = row + d < n ? row + d : row;
+            const T lo = val[(int64_t)(k + 1) * n + jl];
+            v[K - 1 - k] = row - d >= r0 ? lo : T(0);
+            x[K - 1 - k] = (T)f(jl);
+            v[K + 1 + k] = val[(int64_t)(k + 1) * n + row];
+            x[K + 1 + k] = (T)f(ju);
+        }
+        v[K] = val[row];
+        x[K] = (T)f(row);
+        T acc = T(0);
+#pragma unroll
+        for (int e = 0; e < 2 * K + 1; ++e) acc += v[e] == T(0) ? T(0) : v[e] * x[e];
+        return acc;
+    }
+};
+template <typename T, int K>
+static DiaOp<T, K> dia_op(const Dia<T>& D) {
+    DiaOp<T, K> o{D.val, D.offs, D.n, {}};
+    for (int k = 0; k < K; ++k) o.off[k] = D.off[k];
+    return o;
+}
+// Runs CALL with `op` the operator in its storage.
+#define EQS_WITH_OP(D, SELLVIEW, CALL)                                     \
+    do {                                                                   \
+        if ((D).K == 3) { const auto op = dia_op<OpT, 3>(D); CALL; }       \
+        else if ((D).K == kMaxDiagonals) { const auto op = dia_op<OpT, kMaxDiagonals>(D); CALL; } \
+        else { const SellOp<OpT> op{SELLVIEW}; CALL; }                     \
+    } while (0)
+static unsigned row_grid(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+
 // y = A x (acc 0) or y += A x (acc 1), L lanes per row, groups of U entries;
 // x may be wider than the operator (the finest right-hand side). The
 // epilogue's own load is issued before the row sum, so it waits together with
@@ -1060,15 +1177,31 @@ __global__ __launch_bounds__(256, (U >= 16 ? 4 : kSparseWaves)) void k_postsmoot
 // ---- finest level of the folded cycle (see upload_folded) ----------------
 // Pre-smoothing kernel of large finest levels: As = A w D^-1 gathers r only;
 //   res = r - As r,   u = w D^-1 (r + res) = G r.
-template <typename T, int U = 8>
-__global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(SellView<T> As, const T* __restrict__ dinv, T omega,
+// By diagonals the product is with A itself and w_j r_j, w = w D^-1.
+template <typename T>
+__device__ __forceinline__ T presmoothed(const SellOp<T>& op, int64_t g, int32_t row, const InstMap& m, int32_t inst,
+                                         const T*, const double* __restrict__ r) {
+    return op.sum(g, row, m, inst, [&](int32_t j) { return (T)r[j]; });
+}
+template <typename T, int K>
+__device__ __forceinline__ T presmoothed(const DiaOp<T, K>& op, int64_t g, int32_t row, const InstMap& m, int32_t inst,
+                                         const T* __restrict__ w, const double* __restrict__ r) {
+    return op.sum(g, row, m, inst, [&](int32_t j) { return w[j] * (T)r[j]; });
+}
+
+template <typename T, typename Op>
+__global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(Op op, InstMap m, const T* __restrict__ w,
+                                                                   const T* __restrict__ dinv, T omega,
                                                                    const double* __restrict__ r, T* __restrict__ u,
                                                                    T* __restrict__ res) {
-    const int64_t g = row_block(As.xcd) * blockDim.x + threadIdx.x;
-    if (g >= (int64_t)As.n_slices * 64) return;
-    const int32_t row = sell_perm_row<1>(As.perm, g);
-    const T acc = sell_row<1, U>(As, g, row, r);
-    if (row < As.n_rows) {
+    const int64_t B = op.block();
+    const int64_t g = B * blockDim.x + threadIdx.x;
+    if (!op.live(g)) return;
+    int32_t lo, bound;
+    block_instances(m, lo, bound, B);
+    const int32_t row = op.row(g);
+    const T acc = presmoothed(op, g, row, m, row >= bound ? lo + 1 : lo, w, r);
+    if (row < op.rows()) {
         const T ri = (T)r[row], rs = ri - acc;
         u[row] = omega * dinv[row] * (ri + rs);
         res[row] = rs;
@@ -1077,9 +1210,9 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(SellView<T> A
 
 // Last kernel of the cycle: z = G r + Q x_1 (CG's FP64 z) with the block
 // partials of r.z and r.z_old as in k_postsmooth. DIRECT: G r is formed here,
-// w D^-1 (2 r - As r), from As and Q in one row order; else it is read (u).
-template <typename T, bool DOT, bool DIRECT, int U = 8>
-__global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, SellView<T> As,
+// w D^-1 (2 r - A w D^-1 r), from A_0 and Q in one row order; else it is read (u).
+template <typename T, bool DOT, bool DIRECT, typename Op>
+__global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, Op op, const T* __restrict__ w,
                                                                  const T* __restrict__ dinv, T omega,
                                                                  const T* __restrict__ u, const double* __restrict__ r,
                                                                  const T* __restrict__ x1, double* __restrict__ z,
@@ -1089,6 +1222,9 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, 
     const int64_t B = row_block(Q.xcd);
     const int64_t g = B * blockDim.x + threadIdx.x;
     const int32_t row = sell_perm_row<1>(Q.perm, g);
+    int32_t lo, bound;
+    block_instances(m, lo, bound, B);
+    const bool second = row >= bound;
     double rz = 0.0, rzo = 0.0;
     if (g < (int64_t)Q.n_slices * 64) {
         const bool in = row < Q.n_rows;
@@ -1099,9 +1235,10 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, 
             if (DOT) zo = z[row];
             ui = DIRECT ? dinv[row] : u[row];
         }
-        const T qx = sell_row<1, U>(Q, g, row, x1);
+        const T qx = sell_row<1>(Q, g, row, x1);
         if constexpr (DIRECT) {
-            const T ar = sell_row<1, U>(As, g, row, r);
+            T ar = T(0);
+            if (op.live(g)) ar = presmoothed(op, g, row, m, second ? lo + 1 : lo, w, r);
             ui = omega * ui * (T(2) * (T)ri - ar);
         }
         if (in) {
@@ -1114,11 +1251,9 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, 
         }
     }
     if (DOT) {
-        int32_t lo, bound;
-        block_instances(m, lo, bound, B);
         double* const parts[2] = {part_rz, part_rzold};
         const double vals[2] = {rz, rzo};
-        store_pairs<2>(parts, vals, row >= bound, bound, sh, B);
+        store_pairs<2>(parts, vals, second, bound, sh, B);
     }
 }
 
@@ -1430,9 +1565,13 @@ static void vcycle_folded(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const doub
     const int t = h.bottom;
     Level<T>& l0 = h.lv[0];
     Level<T>& bot = h.lv[t];
+    const InstMap m = inst_map(c);
+    using OpT = T;
     if (!h.direct)
-        EQS_LAUNCH_TIMED(c, EQS_KCLASS_PRESMOOTH0, (k_presmooth_u<T>), dim3(sell_grid(l0.A.sell)), b, 0, s, sview(l0),
-                         (const T*)l0.dinv, (T)l0.omega, r, l0.x, l0.res);
+        EQS_WITH_OP(l0.D, sview(l0),
+                    EQS_LAUNCH_TIMED(c, EQS_KCLASS_PRESMOOTH0, (k_presmooth_u<T, std::decay_t<decltype(op)>>),
+                                     dim3(row_grid(l0.n)), b, 0, s, op, m, (const T*)l0.w, (const T*)l0.dinv,
+                                     (T)l0.omega, r, l0.x, l0.res));
     const bool whole = t == 1 && bot.coarse_R;  // the finest restriction is part of the bottom's product
     if (whole) {
         prof_begin(c, EQS_KCLASS_VCOARSE, s);
@@ -1459,15 +1598,16 @@ static void vcycle_folded(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const doub
         launch_mv<T, T>(s, c, l == 1 ? EQS_KCLASS_POSTSMOOTH1 : -1, -1, h.lv[l].GQ, (const T*)h.lv[l].b, h.lv[l].xs, 0,
                         MV_PLAIN);
     prof_end(c, EQS_KCLASS_VCOARSE, s);
-    const InstMap m = part_rz ? inst_map(c) : InstMap{nullptr, nullptr, 0, -1};
-#define EQS_POST_FOLD(DOT_, DIRECT_)                                                                                   \
-    EQS_LAUNCH_TIMED2(c, EQS_KCLASS_POSTSMOOTH0, EQS_KCLASS_PROLONG0, (k_post_fold<T, DOT_, DIRECT_>),                 \
-                      dim3(sell_grid(l0.Q.sell)), b, 0, s, view(l0.Q.sell), sview(l0), (const T*)l0.dinv, (T)l0.omega, \
-                      (const T*)l0.x, r, (const T*)h.lv[1].xs, z, m, part_rz, part_rzold)
+#define EQS_POST_FOLD(DOT_, DIRECT_)                                                                                    \
+    EQS_LAUNCH_TIMED2(c, EQS_KCLASS_POSTSMOOTH0, EQS_KCLASS_PROLONG0,                                                   \
+                      (k_post_fold<T, DOT_, DIRECT_, std::decay_t<decltype(op)>>), dim3(sell_grid(l0.Q.sell)), b, 0, s, \
+                      view(l0.Q.sell), op, (const T*)l0.w, (const T*)l0.dinv, (T)l0.omega, (const T*)l0.x, r,           \
+                      (const T*)h.lv[1].xs, z, m, part_rz, part_rzold)
     if (h.direct) {
-        if (part_rz) EQS_POST_FOLD(true, true);
-        else EQS_POST_FOLD(false, true);
+        if (part_rz) EQS_WITH_OP(l0.D, sview(l0), EQS_POST_FOLD(true, true));
+        else EQS_WITH_OP(l0.D, sview(l0), EQS_POST_FOLD(false, true));
     } else {
+        const SellOp<T> op{sview(l0)};  // not read
         if (part_rz) EQS_POST_FOLD(true, false);
         else EQS_POST_FOLD(false, false);
     }
@@ -1553,19 +1693,23 @@ template void vcycle<float>(hipStream_t, eqs_ctx*, Hierarchy<float>&, const doub
 
 // r = rhs - M x; pair partials of |r|^2 and |rhs|^2. With mx_out, M x is
 // also stored (the next solve that starts from this x then needs no product).
-__global__ __launch_bounds__(256, kSparseWaves) void k_pcg_residual(SellView<double> M, InstMap m, const double* __restrict__ rhs,
+template <typename Op>
+__global__ __launch_bounds__(256, kSparseWaves) void k_pcg_residual(Op op, InstMap m, const double* __restrict__ rhs,
                                                        const double* __restrict__ x, double* __restrict__ r,
                                                        double* __restrict__ part_rr, double* __restrict__ part_bb,
                                                        double* __restrict__ mx_out, const int32_t* __restrict__ when_done) {
     __shared__ double sh[kPairSh];
     if (when_done && !*when_done) return;  // queued ahead of the host's decision: only once every instance is done
-    const int64_t B = row_block(M.xcd);
+    const int64_t B = op.block();
     const int64_t g = B * blockDim.x + threadIdx.x;
-    const int32_t row = sell_perm_row<1>(M.perm, g);  // the row order, if any, stays inside the block's rows
+    const int32_t row = op.row(g);  // the row order, if any, stays inside the block's rows
+    int32_t lo, bound;
+    block_instances(m, lo, bound, B);
+    const bool second = row >= bound;
     double rr = 0.0, bb = 0.0;
-    if (g < (int64_t)M.n_slices * 64) {
-        const double mx = sell_row<1>(M, g, row, x);
-        if (row < M.n_rows) {
+    if (op.live(g)) {
+        const double mx = op.sum(g, row, m, second ? lo + 1 : lo, [&](int32_t j) { return x[j]; });
+        if (row < op.rows()) {
             const double bi = rhs[row];
             const double ri = bi - mx;
             r[row] = ri;
@@ -1574,11 +1718,9 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_pcg_residual(SellView<dou
             bb = bi * bi;
         }
     }
-    int32_t lo, bound;
-    block_instances(m, lo, bound, B);
     double* const parts[2] = {part_rr, part_bb};
     const double vals[2] = {rr, bb};
-    store_pairs<2>(parts, vals, row >= bound, bound, sh, B);
+    store_pairs<2>(parts, vals, second, bound, sh, B);
 }
 
 // r = rhs - mx with mx = M x stored by the residual check that ended the
@@ -1605,121 +1747,256 @@ __global__ __launch_bounds__(256) void k_pcg_residual_mx(InstMap m, const double
     store_pairs<2>(parts, vals, row >= bound, bound, sh, blockIdx.x);
 }
 
-// q = M z + beta q, p = z + beta p (so q = M p without a second pass); pair partials of p.q.
-// stop (may be NULL) ends the launch at entry. ONE: a single instance; nothing in it waits for the scalars
-// before the row's loads are issued: they are read with vector loads issued first, and used by selects, not
-// branches (a branch on a loaded flag is waited for where the compiler places it, ahead of the loads). It
-// writes p and q even after the solve has converged: a finished solve, and a restart (beta = 0), read neither.
-template <bool ONE>
-__global__ __launch_bounds__(256, kSparseWaves) void k_pcg_spmv(SellView<double> M, InstMap m, const double* __restrict__ z,
-                                                   double* __restrict__ p, double* __restrict__ q,
-                                                   double* __restrict__ part_pq, const PcgScalars* __restrict__ scal,
-                                                   const int32_t* __restrict__ stop) {
-    __shared__ double sh[kPairSh];
-    if (stop && *stop) return;
-    const int64_t B = row_block(M.xcd);
-    const int64_t g = B * blockDim.x + threadIdx.x;
-    const int32_t row = sell_perm_row<1>(M.perm, g);  // the row order, if any, stays inside the block's rows
-    double pq = 0.0;
-    if constexpr (ONE) {
-        const double beta = vec_load(&scal->beta);
-        const int32_t fresh = vec_load(&scal->fresh);
-        const int32_t bound = m.rows1;
-        if (g < (int64_t)M.n_slices * 64) {
-            const double mz = sell_row<1>(M, g, row, z);
-            if (row < M.n_rows) {
-                const double zi = z[row], po = p[row], qo = q[row];
-                const double pi = fresh ? zi : zi + beta * po;
-                const double qi = fresh ? mz : mz + beta * qo;
-                p[row] = pi;
-                q[row] = qi;
-                pq = pi * qi;
-            }
-        }
-        double* const parts[1] = {part_pq};
-        const double vals[1] = {pq};
-        store_pairs<1>(parts, vals, row >= bound, bound, sh, B);
-    } else {
-        int32_t lo, bound;
-        block_instances(m, lo, bound, B);
-        const bool second = row >= bound;
-        const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
-        if (g < (int64_t)M.n_slices * 64) {
-            const double mz = sell_row<1>(M, g, row, z);
-            if (row < M.n_rows && !S.done) {
-                double pi, qi;
-                if (S.fresh) {
-                    pi = z[row];
-                    qi = mz;
-                } else {
-                    pi = z[row] + S.beta * p[row];
-                    qi = mz + S.beta * q[row];
-                }
-                p[row] = pi;
-                q[row] = qi;
-                pq = pi * qi;
-            }
-        }
-        double* const parts[1] = {part_pq};
-        const double vals[1] = {pq};
-        store_pairs<1>(parts, vals, second, bound, sh, B);
-    }
+// CG decisions from the reduced dot products.
+enum { FIN_GO = 0, FIN_CONVERGED = 1, FIN_BREAKDOWN = 2, FIN_OUT_OF_ITERS = 3 };
+__device__ __forceinline__ int fin_positive(double d) { return (!(d > 0.0) || !isfinite(d)) ? FIN_BREAKDOWN : FIN_GO; }
+__device__ __forceinline__ int fin_conv_decision(double rr, double tol2, int32_t it, int32_t maxit) {
+    if (rr <= tol2) return FIN_CONVERGED;
+    if (!isfinite(rr)) return FIN_BREAKDOWN;
+    if (it >= maxit) return FIN_OUT_OF_ITERS;
+    return FIN_GO;
 }
-// x += alpha p, r -= alpha q; pair partials of r.r. stop and ONE as for k_pcg_spmv: with one instance the done
-// flag selects the stored values (x and r written back unchanged once the solve has converged), so the four
-// streams' loads do not wait for it. xcd: M's block order, so that each workgroup reads the p and q rows the SpMV
-// wrote on the same XCD.
-template <bool ONE>
-__global__ __launch_bounds__(256) void k_pcg_update(InstMap m, double* __restrict__ x, double* __restrict__ r,
-                                                     const double* __restrict__ p, const double* __restrict__ q,
-                                                     int64_t n, double* __restrict__ part_rr,
-                                                     const PcgScalars* __restrict__ scal,
-                                                     const int32_t* __restrict__ stop, int32_t xcd) {
-    __shared__ double sh[kPairSh];
-    if (stop && *stop) return;
-    const int64_t B = row_block(xcd);
-    const int64_t i = B * blockDim.x + threadIdx.x;
-    double rr = 0.0;
-    if constexpr (ONE) {
-        const double alpha = vec_load(&scal->alpha);
-        const int32_t done = vec_load(&scal->done);
-        const int32_t bound = m.rows1;
-        if (i < n) {
-            const double pi = p[i], qi = q[i], xi = x[i], ri0 = r[i];
-            __builtin_amdgcn_sched_barrier(0);  // the four loads are issued before anything waits
-            const double xn = xi + alpha * pi, rn = ri0 - alpha * qi;
-            x[i] = done ? xi : xn;
-            r[i] = done ? ri0 : rn;
-            rr = done ? 0.0 : rn * rn;
-        }
-        double* const parts[1] = {part_rr};
-        const double vals[1] = {rr};
-        store_pairs<1>(parts, vals, i >= bound, bound, sh, B);
-    } else {
-        int32_t lo, bound;
-        block_instances(m, lo, bound, B);
-        const bool second = i >= bound;
-        const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
-        if (i < n && !S.done) {
-            const double pi = p[i], qi = q[i], xi = x[i], ri0 = r[i];
-            __builtin_amdgcn_sched_barrier(0);  // the four loads are issued before anything waits
-            x[i] = xi + S.alpha * pi;
-            const double ri = ri0 - S.alpha * qi;
-            r[i] = ri;
-            rr = ri * ri;
-        }
-        double* const parts[1] = {part_rr};
-        const double vals[1] = {rr};
-        store_pairs<1>(parts, vals, second, bound, sh, B);
-    }
+__device__ __forceinline__ int fin_rz(double rz) { return rz == 0.0 ? 2 : fin_positive(rz) != FIN_GO ? 1 : 0; }
+__device__ __forceinline__ double fin_beta_of(int fresh, int flexible, double rho_old, double rz, double rzo) {
+    return fresh ? 0.0 : (flexible ? (rz - rzo) / rho_old : rz / rho_old);
 }
 
-// x = 0 on the rows of instances whose right-hand side is zero.
-__global__ void k_zero_rhs_rows(InstMap m, double* __restrict__ x, int64_t n, const PcgScalars* __restrict__ scal) {
+// One CG step's scalars from the SpMV's dots d = {p.q, r.q, q.q, r.r}: alpha,
+// and the residual after the update, |r - alpha q|^2 = r.r - 2 alpha r.q +
+// alpha^2 q.q, known before the update runs, so that no reduction follows it.
+// r.r is summed afresh every iteration; the difference is meaningful down to
+// the rounding of its terms, so it is kept above 1e-13 r.r (a solve that drops
+// further in one iteration is found converged by the next one's r.r).
+struct StepOut {
+    double alpha, rr, relres;
+    int32_t it, done, status, apply;
+};
+__device__ __forceinline__ StepOut fin_step(const PcgStep& S, const double (&d)[4]) {
+    StepOut o{0.0, d[3], S.bb > 0.0 ? sqrt(d[3] / S.bb) : 0.0, S.it, 1, EQS_OK, 0};
+    // r is zero, or (not at a start, where the start's check decided) already small enough
+    if (S.brk == 2 || (!S.fresh && d[3] <= S.tol2)) {
+        if (!(d[3] <= S.tol2)) o.status = EQS_ERR_BREAKDOWN;
+        return o;
+    }
+    if (S.brk || fin_positive(d[0]) != FIN_GO) {
+        o.status = EQS_ERR_BREAKDOWN;
+        return o;
+    }
+    o.alpha = S.rho / d[0];
+    const double floor_rr = 1e-13 * d[3];
+    const double rr = d[3] - 2.0 * o.alpha * d[1] + o.alpha * o.alpha * d[2];
+    o.rr = rr < floor_rr ? floor_rr : rr;  // NaN stays
+    o.relres = sqrt(o.rr / S.bb);
+    o.it = S.it + 1;
+    o.apply = 1;
+    const int c = fin_conv_decision(o.rr, S.tol2, o.it, S.maxit);
+    o.done = c != FIN_GO;
+    if (c == FIN_BREAKDOWN) o.status = EQS_ERR_BREAKDOWN;
+    if (c == FIN_OUT_OF_ITERS) o.status = EQS_ERR_NOT_CONVERGED;
+    return o;
+}
+// writes an instance's scalars after a step (fields that a step leaves alone are not touched)
+__device__ __forceinline__ void store_step(PcgScalars* __restrict__ s, double rho, const StepOut& o) {
+    s->rho = rho;
+    s->alpha = o.alpha;
+    s->rr = o.rr;
+    s->relres = o.relres;
+    s->it = o.it;
+    s->done = o.done;
+    s->status = o.status;
+    s->fresh = 0;
+}
+__device__ __forceinline__ void store_summary_one(PcgSummary* __restrict__ sum, PcgSummary* __restrict__ host_sum,
+                                                  int32_t done, int32_t status, double bb, int32_t it, double relres) {
+    PcgSummary v;
+    v.all_done = done ? 1 : 0;
+    v.n_active = done ? 0 : 1;
+    v.n_breakdown = status == EQS_ERR_BREAKDOWN;
+    v.n_notconv = status == EQS_ERR_NOT_CONVERGED;
+    v.n_zero_rhs = bb == 0.0;
+    v.max_it = max(it, 0);
+    const double mr = isnan(relres) ? INFINITY : relres;
+    v.max_relres = mr > 0.0 ? mr : 0.0;
+    *sum = v;
+    *host_sum = v;
+}
+
+// The four partial arrays of the SpMV's dots.
+struct DotParts {
+    double *pq, *rq, *qq, *rr;
+};
+__device__ __forceinline__ void store_dots(const DotParts& D, const double (&v)[4], bool second, int32_t bound,
+                                           double* sh, int64_t B) {
+    double* const a[2] = {D.pq, D.rq};
+    const double va[2] = {v[0], v[1]};
+    store_pairs<2>(a, va, second, bound, sh, B);
+    double* const b[2] = {D.qq, D.rr};
+    const double vb[2] = {v[2], v[3]};
+    store_pairs<2>(b, vb, second, bound, sh + kPairSh, B);
+}
+
+// q = M z + beta q, p = z + beta p (so q = M p without a second pass); pair
+// partials of p.q, r.q, q.q and r.r. stop (may be NULL) ends the launch at entry.
+// PRO: every workgroup sums the r.z partials of its rows' instances and forms
+// their beta itself; the workgroup of an instance's first row leaves what it
+// found in step[] for the update (scal is only read here: other workgroups
+// still need it). Else beta and fresh are read from scal, where the finaliser
+// left them; with one instance they are read with vector loads issued first and
+// used by selects (a branch on a loaded flag is waited for where the compiler
+// places it, ahead of the row's loads). Rows of an instance that is done keep
+// their p and q, except with one instance, where they are written and not read:
+// a finished solve, and a restart (beta = 0), read neither.
+template <bool ONE, bool PRO, typename Op>
+__global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_spmv(
+    Op op, InstMap m, const double* __restrict__ z, const double* __restrict__ r, double* __restrict__ p,
+    double* __restrict__ q, DotParts D, const PcgScalars* __restrict__ scal, PcgStep* __restrict__ step,
+    const double* __restrict__ part_rz, const double* __restrict__ part_rzold, const int32_t* __restrict__ stop) {
+    __shared__ double sh[2 * kPairSh + 16];
+    const int64_t B = op.block();
     int32_t lo, bound;
-    block_instances(m, lo, bound, blockIdx.x);
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && scal[min(i >= bound ? lo + 1 : lo, m.n_inst - 1)].bb == 0.0) x[i] = 0.0;
+    block_instances(m, lo, bound, B);
+    if (stop && *stop) {  // past convergence: nothing to do here, and nothing for the update
+        if (PRO && threadIdx.x == 0) {
+            if (ONE ? B == 0 : (m.row_off[lo] >> 8) == B) step[lo].done = 1;
+            if (!ONE && lo + 1 < m.n_inst && (bound >> 8) == B) step[lo + 1].done = 1;
+        }
+        return;
+    }
+    const int64_t g = B * blockDim.x + threadIdx.x;
+    const int32_t row = op.row(g);  // the row order, if any, stays inside the block's rows
+    const bool second = row >= bound;
+    const double* const rzp[2] = {part_rz, part_rzold};
+    ProParts<2> P;
+    if constexpr (PRO) pro_load<2>(rzp, m, lo, P);
+    double beta1 = 0.0;
+    int32_t fresh1 = 0;
+    if constexpr (ONE && !PRO) {
+        beta1 = vec_load(&scal->beta);
+        fresh1 = vec_load(&scal->fresh);
+    }
+    double mz = 0.0, zi = 0.0, po = 0.0, qo = 0.0, ri = 0.0;
+    const bool in = op.live(g) && row < op.rows();
+    if (op.live(g)) mz = op.sum(g, row, m, second ? lo + 1 : lo, [&](int32_t j) { return z[j]; });
+    if (in) {
+        zi = z[row];
+        po = p[row];
+        qo = q[row];
+        ri = r[row];
+    }
+    double beta = beta1;
+    int32_t fresh = fresh1, done = 0;
+    if constexpr (PRO) {
+        const bool split = !ONE && (int64_t)bound < (B + 1) * (int64_t)blockDim.x;
+        const int32_t i1 = min(lo + 1, m.n_inst - 1);
+        for (int k = 0; k < (split ? 2 : 1); ++k) {
+            const int32_t i = k ? i1 : lo;
+            double sums[2];
+            if (k) pro_load<2>(rzp, m, i, P);
+            pro_sum<2>(P, sh + 2 * kPairSh + 8 * k, sums);
+            const PcgScalars& S = scal[i];
+            const int32_t dn = S.done, fr = S.fresh;
+            const double be = fin_beta_of(fr, S.flexible, S.rho, sums[0], sums[1]);
+            const int32_t first = ONE ? 0 : m.row_off[i];
+            if (threadIdx.x == 0 && (first >> 8) == B)
+                step[i] = PcgStep{sums[0], S.bb, S.tol2, S.it, S.maxit, dn, dn ? 0 : fin_rz(sums[0]), fr, 0};
+            if (second == (k == 1)) {
+                beta = be;
+                fresh = fr;
+                done = dn;
+            }
+        }
+    } else if constexpr (!ONE) {
+        const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
+        beta = S.beta;
+        fresh = S.fresh;
+        done = S.done;
+    }
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (in && (ONE || !done)) {
+        const double pi = fresh ? zi : zi + beta * po;
+        const double qi = fresh ? mz : mz + beta * qo;
+        p[row] = pi;
+        q[row] = qi;
+        v[0] = pi * qi;
+        v[1] = ri * qi;
+        v[2] = qi * qi;
+        v[3] = ri * ri;
+    }
+    store_dots(D, v, second, bound, sh, B);
+}
+
+// x += alpha p, r -= alpha q where the iteration's step is to be applied; x = 0
+// where the right-hand side is zero. PRO: every workgroup forms its rows'
+// instances' step from the SpMV's dots and step[]; the workgroup of an
+// instance's first row writes the instance's scalars (and with one instance the
+// summary the host polls). Else the finaliser left alpha and apply in scal. xcd:
+// M's block order, so that each workgroup reads the p and q rows the SpMV wrote
+// on the same XCD.
+template <bool ONE, bool PRO>
+__global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_update(
+    InstMap m, double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
+    const double* __restrict__ q, int64_t n, DotParts D, PcgScalars* __restrict__ scal,
+    const PcgStep* __restrict__ step, PcgSummary* __restrict__ sum, PcgSummary* __restrict__ host_sum, int32_t xcd) {
+    __shared__ double sh[32];
+    const int64_t B = row_block(xcd);
+    const int64_t i = B * blockDim.x + threadIdx.x;
+    int32_t lo, bound;
+    block_instances(m, lo, bound, B);
+    const bool second = i >= bound;
+    const double* const dp[4] = {D.pq, D.rq, D.qq, D.rr};
+    ProParts<4> P;
+    if constexpr (PRO) pro_load<4>(dp, m, lo, P);
+    double alpha = 0.0, bb = 0.0;
+    int32_t apply = 0;
+    if constexpr (ONE && !PRO) {
+        alpha = vec_load(&scal->alpha);
+        bb = vec_load(&scal->bb);
+        apply = vec_load(&scal->apply);
+    }
+    double pi = 0.0, qi = 0.0, xi = 0.0, ri = 0.0;
+    if (i < n) {
+        pi = p[i];
+        qi = q[i];
+        xi = x[i];
+        ri = r[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all loads are issued before anything waits
+    if constexpr (PRO) {
+        const bool split = !ONE && (int64_t)bound < (B + 1) * (int64_t)blockDim.x;
+        const int32_t i1 = min(lo + 1, m.n_inst - 1);
+        for (int k = 0; k < (split ? 2 : 1); ++k) {
+            const int32_t j = k ? i1 : lo;
+            double d[4];
+            if (k) pro_load<4>(dp, m, j, P);
+            pro_sum<4>(P, sh + 16 * k, d);
+            const PcgStep S = step[j];
+            StepOut o{};
+            if (!S.done) o = fin_step(S, d);
+            const int32_t first = ONE ? 0 : m.row_off[j];
+            if (!S.done && threadIdx.x == 0 && (first >> 8) == B) {
+                store_step(scal + j, S.rho, o);
+                if (ONE) store_summary_one(sum, host_sum, o.done, o.status, S.bb, o.it, o.relres);
+            }
+            if (second == (k == 1)) {
+                alpha = o.alpha;
+                apply = o.apply;
+                bb = S.bb;
+            }
+        }
+    } else if constexpr (!ONE) {
+        const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
+        alpha = S.alpha;
+        apply = S.apply;
+        bb = S.bb;
+    }
+    if (i < n) {
+        if (apply) {
+            x[i] = xi + alpha * pi;
+            r[i] = ri - alpha * qi;
+        } else if (bb == 0.0) {
+            x[i] = 0.0;
+        }
+    }
 }
 
 // Summary over the instances, mirrored with all scalars to the host; every
@@ -1779,23 +2056,6 @@ __device__ void summarise(const PcgScalars* __restrict__ s, int32_t n, PcgSummar
 // struct, read, modified and written back, would keep the untouched fields in
 // LDS, and the loads into it would be waited for before the partials' loads
 // are issued).
-struct FinIn {
-    double rho, bb, tol2;
-    int32_t it, maxit, done, fresh, flexible;
-};
-__device__ __forceinline__ FinIn fin_fields(const PcgScalars* __restrict__ s, int32_t i) {
-    const PcgScalars* p = s + i;
-    return FinIn{p->rho, p->bb, p->tol2, p->it, p->maxit, p->done, p->fresh, p->flexible};
-}
-// the fields of instance kFinWaves * blockIdx.x + threadIdx.x, the one this thread's body call serves
-// (for_each_instance_sum)
-__device__ __forceinline__ FinIn prefetch_fields(const PcgScalars* __restrict__ s, const InstMap& m) {
-    FinIn x{};
-    const int32_t i = (int32_t)blockIdx.x * kFinWaves + (int32_t)threadIdx.x;
-    if ((int32_t)threadIdx.x < kFinWaves && i < m.n_inst) x = fin_fields(s, i);
-    return x;
-}
-
 // One instance: every wavefront sums an equal share of the blocks' first
 // partials (the second is 0 when there is one instance); thread 0 gets the
 // totals. The order of the additions is fixed.
@@ -1820,23 +2080,6 @@ __device__ __forceinline__ void single_instance_sums(const double* const (&parts
             for (int w = 0; w < kFinWaves; ++w) t += sh[p][w];
         out[p] = t;
     }
-}
-
-// CG decisions from the reduced dot products; 0 = carry on.
-enum { FIN_GO = 0, FIN_CONVERGED = 1, FIN_BREAKDOWN = 2, FIN_OUT_OF_ITERS = 3 };
-__device__ __forceinline__ int fin_positive(double d) { return (!(d > 0.0) || !isfinite(d)) ? FIN_BREAKDOWN : FIN_GO; }
-__device__ __forceinline__ int fin_conv_decision(double rr, double tol2, int32_t it, int32_t maxit) {
-    if (rr <= tol2) return FIN_CONVERGED;
-    if (!isfinite(rr)) return FIN_BREAKDOWN;
-    if (it >= maxit) return FIN_OUT_OF_ITERS;
-    return FIN_GO;
-}
-__device__ __forceinline__ void set_breakdown(PcgScalars* __restrict__ p) {
-    p->done = 1;
-    p->status = EQS_ERR_BREAKDOWN;
-}
-__device__ __forceinline__ double fin_beta_of(const FinIn& x, double rz, double rzo) {
-    return x.fresh ? 0.0 : (x.flexible ? (rz - rzo) / x.rho : rz / x.rho);
 }
 
 // mode 0: start of a solve (it = 0); mode 1: restart from the true residual
@@ -1911,19 +2154,11 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
         h.status = status;
         h.fresh = fresh;
         h.flexible = flex;
+        h.apply = 0;
+        h.pad = 0;
         *s = h;
         *host = h;
-        PcgSummary v1;
-        v1.all_done = done ? 1 : 0;
-        v1.n_active = done ? 0 : 1;
-        v1.n_breakdown = status == EQS_ERR_BREAKDOWN;
-        v1.n_notconv = status == EQS_ERR_NOT_CONVERGED;
-        v1.n_zero_rhs = bb == 0.0;
-        v1.max_it = max(it, 0);
-        const double mr = isnan(relres) ? INFINITY : relres;
-        v1.max_relres = mr > 0.0 ? mr : 0.0;
-        *sum = v1;
-        *host_sum = v1;
+        store_summary_one(sum, host_sum, done, status, bb, it, relres);
     } else {
         if (when_done && !sum->all_done) return;  // pairs with k_pcg_residual's when_done
         const int32_t forced = (mode == 1 && force) ? *force : 0;
@@ -1977,165 +2212,74 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
     }
 }
 
-// beta from r.z (Polak-Ribiere with r.z_old when flexible). ONE: a single
-// instance (InstMap::rows1 >= 0); the two forms are separate kernels so each
-// gets its own register allocation.
+// beta from r.z (Polak-Ribiere with r.z_old when flexible), and the step's
+// record for k_fin_step. ONE: a single instance (InstMap::rows1 >= 0); the two
+// forms are separate kernels so each gets its own register allocation.
 template <bool ONE>
-__global__ __launch_bounds__(kFin) void k_fin_beta(PcgScalars* __restrict__ s, InstMap m,
-                                                    const double* __restrict__ prz, const double* __restrict__ przold,
-                                                    const int32_t* __restrict__ stop) {
-    const int32_t stopped = ONE ? vec_load(stop) : *stop;
+__global__ __launch_bounds__(kFin) void k_fin_beta(PcgScalars* __restrict__ s, PcgStep* __restrict__ step, InstMap m,
+                                                    const double* __restrict__ prz, const double* __restrict__ przold) {
     const double* parts[2] = {prz, przold};
     if constexpr (ONE) {
         // only the fields used: a vector load whose result is never read still holds its register
-        FinIn x{};
-        x.rho = vec_load(&s->rho);
-        x.done = vec_load(&s->done);
-        x.fresh = vec_load(&s->fresh);
-        x.flexible = vec_load(&s->flexible);
+        const double rho = vec_load(&s->rho), bb = vec_load(&s->bb), tol2 = vec_load(&s->tol2);
+        const int32_t it = vec_load(&s->it), maxit = vec_load(&s->maxit), done = vec_load(&s->done);
+        const int32_t fresh = vec_load(&s->fresh), flexible = vec_load(&s->flexible);
         double v[2];
         single_instance_sums<2>(parts, m.rows1, v);
-        if (threadIdx.x == 0 && !stopped && !x.done) {
-            if (fin_positive(v[0]) != FIN_GO) {
-                set_breakdown(s);
-            } else {
-                s->beta = fin_beta_of(x, v[0], v[1]);
-                s->rho = v[0];
-            }
+        if (threadIdx.x == 0) {
+            s->beta = fin_beta_of(fresh, flexible, rho, v[0], v[1]);
+            *step = PcgStep{v[0], bb, tol2, it, maxit, done, done ? 0 : fin_rz(v[0]), fresh, 0};
         }
     } else {
-        const FinIn pre = prefetch_fields(s, m);
         for_each_instance_sum<2>(parts, m, [&](int32_t i, const double* v) {
-            if (stopped) return;
-            const FinIn& x = pre;
-            if (x.done) return;
             PcgScalars* p = s + i;
-            if (fin_positive(v[0]) != FIN_GO) {
-                set_breakdown(p);
-            } else {
-                p->beta = fin_beta_of(x, v[0], v[1]);
-                p->rho = v[0];
-            }
+            p->beta = fin_beta_of(p->fresh, p->flexible, p->rho, v[0], v[1]);
+            step[i] = PcgStep{v[0], p->bb, p->tol2, p->it, p->maxit, p->done, p->done ? 0 : fin_rz(v[0]), p->fresh, 0};
         });
     }
 }
 
+// The step (fin_step) of every instance from the SpMV's dots, and the summary.
 template <bool ONE>
-__global__ __launch_bounds__(kFin) void k_fin_alpha(PcgScalars* __restrict__ s, InstMap m,
-                                                     const double* __restrict__ ppq, const int32_t* __restrict__ stop) {
-    const int32_t stopped = ONE ? vec_load(stop) : *stop;
-    const double* parts[1] = {ppq};
-    if constexpr (ONE) {
-        const double rho = vec_load(&s->rho);
-        const int32_t done = vec_load(&s->done);
-        double v[1];
-        single_instance_sums<1>(parts, m.rows1, v);
-        if (threadIdx.x == 0 && !stopped && !done) {
-            if (fin_positive(v[0]) != FIN_GO) {
-                set_breakdown(s);
-            } else {
-                s->alpha = rho / v[0];
-                s->fresh = 0;
-            }
-        }
-    } else {
-        const FinIn pre = prefetch_fields(s, m);
-        for_each_instance_sum<1>(parts, m, [&](int32_t i, const double* v) {
-            if (stopped) return;
-            const FinIn& x = pre;
-            if (x.done) return;
-            PcgScalars* p = s + i;
-            if (fin_positive(v[0]) != FIN_GO) {
-                set_breakdown(p);
-            } else {
-                p->alpha = x.rho / v[0];
-                p->fresh = 0;
-            }
-        });
-    }
-}
-
-template <bool ONE>
-__global__ __launch_bounds__(kFin) void k_fin_conv(PcgScalars* __restrict__ s, InstMap m,
-                                                    const double* __restrict__ prr, PcgSummary* __restrict__ sum,
+__global__ __launch_bounds__(kFin) void k_fin_step(PcgScalars* __restrict__ s, const PcgStep* __restrict__ step,
+                                                    InstMap m, DotParts D, PcgSummary* __restrict__ sum,
                                                     PcgSummary* __restrict__ host_sum, PcgScalars* __restrict__ host) {
-    const int32_t stopped = ONE ? vec_load(&sum->all_done) : sum->all_done;
-    const double* parts[1] = {prr};
+    const double* parts[4] = {D.pq, D.rq, D.qq, D.rr};
     if constexpr (ONE) {
-        // the instance's scalars and the summary as summarise() leaves them for one instance; the struct is
-        // handled field by field (a whole-struct copy would be kept in LDS)
-        const PcgScalars* p = s;
-        const double bb = vec_load(&p->bb), rho = vec_load(&p->rho), rho_old = vec_load(&p->rho_old);
-        const double beta = vec_load(&p->beta), alpha = vec_load(&p->alpha), tol2 = vec_load(&p->tol2);
-        const double rr0 = vec_load(&p->rr), relres0 = vec_load(&p->relres);
-        const int32_t it0 = vec_load(&p->it), maxit = vec_load(&p->maxit), done0 = vec_load(&p->done);
-        const int32_t status0 = vec_load(&p->status), fresh = vec_load(&p->fresh), flexible = vec_load(&p->flexible);
-        double v[1];
-        single_instance_sums<1>(parts, m.rows1, v);
-        if (threadIdx.x == 0 && !stopped) {
-            double rr = rr0, relres = relres0;
-            int32_t it = it0, done = done0, status = status0;
-            if (!done0) {
-                rr = v[0];
-                relres = sqrt(rr / bb);
-                it = it0 + 1;
-                const int d = fin_conv_decision(rr, tol2, it, maxit);
-                if (d != FIN_GO) done = 1;
-                if (d == FIN_BREAKDOWN) status = EQS_ERR_BREAKDOWN;
-                if (d == FIN_OUT_OF_ITERS) status = EQS_ERR_NOT_CONVERGED;
-                s->rr = rr;
-                s->relres = relres;
-                s->it = it;
-                s->done = done;
-                s->status = status;
+        const PcgStep* t = step;
+        PcgStep S;
+        S.rho = vec_load(&t->rho);
+        S.bb = vec_load(&t->bb);
+        S.tol2 = vec_load(&t->tol2);
+        S.it = vec_load(&t->it);
+        S.maxit = vec_load(&t->maxit);
+        S.done = vec_load(&t->done);
+        S.brk = vec_load(&t->brk);
+        S.fresh = vec_load(&t->fresh);
+        double v[4];
+        single_instance_sums<4>(parts, m.rows1, v);
+        if (threadIdx.x == 0) {
+            if (S.done) {
+                s->apply = 0;
+            } else {
+                const StepOut o = fin_step(S, v);
+                store_step(s, S.rho, o);
+                s->apply = o.apply;
+                store_summary_one(sum, host_sum, o.done, o.status, S.bb, o.it, o.relres);
             }
-            PcgScalars h;
-            h.bb = bb;
-            h.rr = rr;
-            h.rho = rho;
-            h.rho_old = rho_old;
-            h.beta = beta;
-            h.alpha = alpha;
-            h.tol2 = tol2;
-            h.relres = relres;
-            h.it = it;
-            h.maxit = maxit;
-            h.done = done;
-            h.status = status;
-            h.fresh = fresh;
-            h.flexible = flexible;
-            *host = h;
-            PcgSummary v1;
-            v1.all_done = done ? 1 : 0;
-            v1.n_active = done ? 0 : 1;
-            v1.n_breakdown = status == EQS_ERR_BREAKDOWN;
-            v1.n_notconv = status == EQS_ERR_NOT_CONVERGED;
-            v1.n_zero_rhs = bb == 0.0;
-            v1.max_it = max(it, 0);
-            const double mr = isnan(relres) ? INFINITY : relres;
-            v1.max_relres = mr > 0.0 ? mr : 0.0;
-            *sum = v1;
-            *host_sum = v1;
         }
     } else {
-        const FinIn pre = prefetch_fields(s, m);
-        for_each_instance_sum<1>(parts, m, [&](int32_t i, const double* v) {
-            if (stopped) return;
-            const FinIn& x = pre;
-            if (x.done) return;
-            const double rr = v[0];
-            const int32_t it = x.it + 1;
-            PcgScalars* p = s + i;
-            p->rr = rr;
-            p->relres = sqrt(rr / x.bb);
-            p->it = it;
-            const int d = fin_conv_decision(rr, x.tol2, it, x.maxit);
-            if (d == FIN_CONVERGED) p->done = 1;
-            else if (d == FIN_BREAKDOWN) set_breakdown(p);
-            else if (d == FIN_OUT_OF_ITERS) {
-                p->done = 1;
-                p->status = EQS_ERR_NOT_CONVERGED;
+        const int32_t stopped = sum->all_done;
+        for_each_instance_sum<4>(parts, m, [&](int32_t i, const double* v) {
+            const PcgStep S = step[i];
+            if (S.done) {
+                s[i].apply = 0;
+                return;
             }
+            const double d[4] = {v[0], v[1], v[2], v[3]};
+            const StepOut o = fin_step(S, d);
+            store_step(s + i, S.rho, o);
+            s[i].apply = o.apply;
         });
         if (stopped || gridDim.x > 1) return;  // the summary already says all done, or k_fin_summary follows
         __syncthreads();
@@ -2147,7 +2291,7 @@ __global__ __launch_bounds__(kFin) void k_fin_conv(PcgScalars* __restrict__ s, I
 // workgroups (more than kFinWaves instances), which cannot summarise itself:
 // what summarise() does at the end of a one-workgroup finaliser. gate 0:
 // always; 1: only while the summary does not yet say all done (after
-// k_fin_conv, which then acted); 2: only once it does (after a k_fin_start
+// k_fin_step or the update, which then acted); 2: only once it does (after a k_fin_start
 // queued with when_done). force (may be NULL): cleared here, after every
 // workgroup of the k_fin_start before has read it.
 __global__ __launch_bounds__(kFin) void k_fin_summary(const PcgScalars* __restrict__ s, int32_t n_inst,
@@ -2171,13 +2315,16 @@ static unsigned fin_grid(const eqs_ctx* c) { return (unsigned)((c->n_inst + kFin
 
 void pcg_init(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, int32_t maxit, double rtol,
               int flexible, const double* mx) {
-    const int64_t nb = sell_grid(c->M);
+    using OpT = double;
+    const unsigned nb = row_grid(c->n_free);
     if (mx)
         hipLaunchKernelGGL(k_pcg_residual_mx, dim3(grid_for(c->n_free)), dim3(kBlock), 0, s, inst_map(c), rhs, mx,
                            c->d_r, c->n_free, part(c, 0), part(c, 1));
     else
-        hipLaunchKernelGGL(k_pcg_residual, dim3(nb), dim3(kBlock), 0, s, view(c->M), inst_map(c), rhs, x, c->d_r,
-                           part(c, 0), part(c, 1), (double*)nullptr, (const int32_t*)nullptr);
+        EQS_WITH_OP(c->Mdia, view(c->M),
+                    hipLaunchKernelGGL(k_pcg_residual<std::decay_t<decltype(op)>>, dim3(nb), dim3(kBlock), 0, s, op,
+                                       inst_map(c), rhs, x, c->d_r, part(c, 0), part(c, 1), (double*)nullptr,
+                                       (const int32_t*)nullptr));
     hipLaunchKernelGGL(inst_map(c).rows1 >= 0 ? k_fin_start<true> : k_fin_start<false>, dim3(fin_grid(c)),
                        dim3(kFin), 0, s, c->d_scal, inst_map(c), part(c, 0), part(c, 1), rtol, maxit, flexible, 0,
                        c->d_sum, c->d_hsum, c->d_hscal, 0, (int32_t*)nullptr);
@@ -2189,10 +2336,12 @@ void pcg_init(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, int
 
 void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, double* mx_out,
                        bool only_if_done) {
-    const int64_t nb = sell_grid(c->M);
+    using OpT = double;
+    const unsigned nb = row_grid(c->n_free);
     const int32_t* done = only_if_done ? &c->d_sum->all_done : nullptr;
-    hipLaunchKernelGGL(k_pcg_residual, dim3(nb), dim3(kBlock), 0, s, view(c->M), inst_map(c), rhs, x, c->d_r,
-                       part(c, 0), part(c, 1), mx_out, done);
+    EQS_WITH_OP(c->Mdia, view(c->M),
+                hipLaunchKernelGGL(k_pcg_residual<std::decay_t<decltype(op)>>, dim3(nb), dim3(kBlock), 0, s, op,
+                                   inst_map(c), rhs, x, c->d_r, part(c, 0), part(c, 1), mx_out, done));
     int32_t* force = c->test_reject_first ? c->d_force : (int32_t*)nullptr;
     hipLaunchKernelGGL(inst_map(c).rows1 >= 0 ? k_fin_start<true> : k_fin_start<false>, dim3(fin_grid(c)),
                        dim3(kFin), 0, s, c->d_scal, inst_map(c), part(c, 0), part(c, 1), 0.0, 0, 0, 1, c->d_sum,
@@ -2202,21 +2351,15 @@ void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const doubl
                            c->d_hscal, only_if_done ? 2 : 0, force);
 }
 
-void pcg_zero_rhs_rows(hipStream_t s, eqs_ctx* c, double* x) {
-    hipLaunchKernelGGL(k_zero_rhs_rows, dim3(grid_for(c->n_free)), dim3(kBlock), 0, s, inst_map(c), x, c->n_free,
-                       c->d_scal);
-}
-
 void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int precision) {
     (void)rhs;
-    const int64_t nbM = sell_grid(c->M);
-    const int64_t nbV = grid_for(c->n_free);
-    const int32_t* stop = &c->d_sum->all_done;
-    // With one iteration per graph the CG SpMV and update do not test the flag either (the V-cycle never does;
-    // see vcycle): an iteration past convergence is rarely launched (the host waits once the residuals
-    // extrapolate to rtol), and it writes only partials and p and q, guarded for x and r by the instance's done
-    // flag. With several iterations per graph they test it, so that surplus iterations skip their SpMV and update.
-    const int32_t* vstop = c->graph_iters > 1 ? stop : nullptr;
+    using OpT = double;
+    const unsigned nbV = row_grid(c->n_free);
+    // With one iteration per graph the SpMV does not test the stop flag either (the V-cycle never does; see
+    // vcycle): an iteration past convergence is rarely launched (the host waits once the residuals extrapolate to
+    // rtol), and it writes only partials and p and q (x and r are guarded by the instance's state). With several
+    // iterations per graph it tests it, so that surplus iterations skip the product.
+    const int32_t* vstop = c->graph_iters > 1 ? &c->d_sum->all_done : nullptr;
     // z = B r, with pair partials of r.z (part 0) and r.z_old (part 1)
     prof_begin(c, EQS_KCLASS_VCYCLE, s);
     if (precision == EQS_PREC_FP32) vcycle<float>(s, c, c->h32, c->d_r, c->d_z, part(c, 0), part(c, 1));
@@ -2224,19 +2367,36 @@ void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int 
     prof_end(c, EQS_KCLASS_VCYCLE, s);
     const InstMap im = inst_map(c);
     const bool one = im.rows1 >= 0;
+    const DotParts D{part(c, 2), part(c, 3), part(c, 4), part(c, 5)};
+    // the consumers reduce (kProBlocks); the finalisers' own time is only seen with launches of their own
+    const bool pro = nbV <= kProBlocks && !(c->prof_mask & (1u << EQS_KCLASS_FINALISE));
     const dim3 fg(fin_grid(c));
-    EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_beta<true> : k_fin_beta<false>, fg, dim3(kFin), 0, s,
-                     c->d_scal, im, part(c, 0), part(c, 1), stop);
-    EQS_LAUNCH_TIMED(c, EQS_KCLASS_SPMV_M, one ? k_pcg_spmv<true> : k_pcg_spmv<false>, dim3(nbM), dim3(kBlock), 0,
-                     s, view(c->M), im, c->d_z, c->d_p, c->d_q, part(c, 2), c->d_scal, vstop);
-    EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_alpha<true> : k_fin_alpha<false>, fg, dim3(kFin), 0, s,
-                     c->d_scal, im, part(c, 2), stop);
-    EQS_LAUNCH_TIMED(c, EQS_KCLASS_CG_UPDATE, one ? k_pcg_update<true> : k_pcg_update<false>, dim3(nbV),
-                     dim3(kBlock), 0, s, im, x, c->d_r, c->d_p, c->d_q, c->n_free, part(c, 3), c->d_scal, vstop,
-                     c->M.xcd);
-    EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_conv<true> : k_fin_conv<false>, fg, dim3(kFin), 0, s,
-                     c->d_scal, im, part(c, 3), c->d_sum, c->d_hsum, c->d_hscal);
-    if (fg.x > 1)  // the summary of all instances (part of the finalise class's work, not timed on its own)
+    if (!pro)
+        EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_beta<true> : k_fin_beta<false>, fg, dim3(kFin), 0, s,
+                         c->d_scal, c->d_step, im, part(c, 0), part(c, 1));
+#define EQS_SPMV(ONE_, PRO_) k_pcg_spmv<ONE_, PRO_, std::decay_t<decltype(op)>>
+    EQS_WITH_OP(c->Mdia, view(c->M),
+                EQS_LAUNCH_TIMED(c, EQS_KCLASS_SPMV_M,
+                                 (pro ? (one ? EQS_SPMV(true, true) : EQS_SPMV(false, true))
+                                      : (one ? EQS_SPMV(true, false) : EQS_SPMV(false, false))),
+                                 dim3(nbV), dim3(kBlock), 0, s, op, im, c->d_z, c->d_r, c->d_p, c->d_q, D, c->d_scal,
+                                 c->d_step, part(c, 0), part(c, 1), vstop));
+#undef EQS_SPMV
+    if (!pro) {
+        // two of the three finalisations of an iteration (alpha, convergence): the second counts with no time of its own
+        EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_step<true> : k_fin_step<false>, fg, dim3(kFin), 0, s,
+                         c->d_scal, c->d_step, im, D, c->d_sum, c->d_hsum, c->d_hscal);
+        prof_again(c, EQS_KCLASS_FINALISE);
+        if (fg.x > 1)  // the summary of all instances (part of the finalise class's work, not timed on its own)
+            hipLaunchKernelGGL(k_fin_summary, dim3(1), dim3(kFin), 0, s, c->d_scal, (int32_t)c->n_inst, c->d_sum,
+                               c->d_hsum, c->d_hscal, 1, (int32_t*)nullptr);
+    }
+    EQS_LAUNCH_TIMED(c, EQS_KCLASS_CG_UPDATE,
+                     pro ? (one ? k_pcg_update<true, true> : k_pcg_update<false, true>)
+                         : (one ? k_pcg_update<true, false> : k_pcg_update<false, false>),
+                     dim3(nbV), dim3(kBlock), 0, s, im, x, c->d_r, c->d_p, c->d_q, c->n_free, D, c->d_scal, c->d_step,
+                     c->d_sum, c->d_hsum, c->M.xcd);
+    if (pro && !one)
         hipLaunchKernelGGL(k_fin_summary, dim3(1), dim3(kFin), 0, s, c->d_scal, (int32_t)c->n_inst, c->d_sum,
                            c->d_hsum, c->d_hscal, 1, (int32_t*)nullptr);
 }

@@ -44,6 +44,15 @@ bool prof_pair(eqs_ctx* c, int cls, hipEvent_t* e0, hipEvent_t* e1, int cls2) {
     return true;
 }
 
+// The class's last launch did the work of two of its launches: the second is
+// counted with no time of its own.
+void prof_again(eqs_ctx* c, int cls) {
+    if (!(c->prof_mask & (1u << cls)) || c->prof_used[cls] == 0) return;
+    const hipEvent_t e = c->prof_ev[cls][(size_t)c->prof_used[cls] - 1].second;
+    slot(c, cls) = {e, e};
+    c->prof_used[cls]++;
+}
+
 void prof_end(eqs_ctx* c, int cls, hipStream_t s) {
     if (!(c->prof_mask & (1u << cls))) return;
     EQS_HIP(hipEventRecord(c->prof_ev[cls][(size_t)c->prof_used[cls]].second, s));

@@ -12,6 +12,7 @@
 
 #include <functional>
 #include <iterator>
+#include <type_traits>
 
 #include "eqs_internal.h"
 #include "p2.h"
@@ -616,6 +617,11 @@ static void visit_spmat(SpMat<T>& A, const std::function<void(void**)>& f) {
     f((void**)&A.val);
 }
 template <typename T>
+static void visit_dia(Dia<T>& D, const std::function<void(void**)>& f) {
+    f((void**)&D.val);
+    f((void**)&D.offs);
+}
+template <typename T>
 static void visit_hierarchy(Hierarchy<T>& h, const std::function<void(void**)>& f) {
     for (Level<T>& lv : h.lv) {
         visit_spmat(lv.A, f);
@@ -623,6 +629,8 @@ static void visit_hierarchy(Hierarchy<T>& h, const std::function<void(void**)>& 
         visit_spmat(lv.R, f);
         visit_spmat(lv.GQ, f);
         visit_spmat(lv.Q, f);
+        visit_dia(lv.D, f);
+        f((void**)&lv.w);
         for (T** q : {&lv.dinv, &lv.sval, &lv.b, &lv.x, &lv.xs, &lv.res, &lv.dense_inv, &lv.coarse_R}) f((void**)q);
     }
 }
@@ -644,6 +652,7 @@ void visit_device_ptrs(eqs_ctx* c, const std::function<void(void**)>& f) {
     f((void**)&c->d_drives);
     f((void**)&c->d_int_to_user);
     visit_sell(c->M, f);
+    visit_dia(c->Mdia, f);
     visit_hierarchy(c->h64, f);
     visit_hierarchy(c->h32, f);
     for (double** q : {&c->d_r, &c->d_z, &c->d_p, &c->d_q, &c->d_mx, &c->d_Y0, &c->d_Ya, &c->d_Yb, &c->d_Yc, &c->d_F0,
@@ -652,6 +661,7 @@ void visit_device_ptrs(eqs_ctx* c, const std::function<void(void**)>& f) {
     f((void**)&c->d_inst_row);
     f((void**)&c->d_blk_inst);
     f((void**)&c->d_scal);
+    f((void**)&c->d_step);
     f((void**)&c->d_sum);
     f((void**)&c->d_force);
     GuessState& g = c->guess;
@@ -885,6 +895,85 @@ static bool row_order_pays(const Csr<double>& A) {
         for (int32_t s0 = 0; s0 < (int32_t)w.size(); s0 += kSlice) sorted += (int64_t)kSlice * w[(size_t)s0];
     }
     return sorted * 10 <= plain * 9;
+}
+
+// The upper diagonals (offsets, per instance) of a symmetric matrix that has at
+// most kMaxDiagonals of them per instance; 3 or 7 are stored (the 7-point and
+// 15-point stencils of structured numberings), with at most half as many zeros
+// as entries in them. Empty: not such a matrix. Meshes numbered along their axes
+// give few diagonals whatever their geometry; others do not.
+static std::vector<std::vector<int32_t>> diagonals_of(const eqs_ctx* c, const Csr<double>& A, int& K) {
+    std::vector<std::vector<int32_t>> off((size_t)c->n_inst);
+    K = 0;
+    int64_t upper = 0;
+    for (int64_t i = 0; i < c->n_inst; ++i) {
+        std::vector<int32_t>& o = off[(size_t)i];
+        for (int32_t r = c->inst_row_off[i]; r < c->inst_row_off[i + 1]; ++r) {
+            bool diag = false;
+            for (int32_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k) {
+                const int32_t d = A.col[k] - r;
+                if (d == 0) diag = true;
+                if (d <= 0) continue;
+                ++upper;
+                auto it = std::lower_bound(o.begin(), o.end(), d);
+                if (it == o.end() || *it != d) {
+                    if (o.size() == (size_t)kMaxDiagonals) return {};
+                    o.insert(it, d);
+                }
+            }
+            if (!diag) return {};
+        }
+        K = std::max(K, (int)o.size());
+    }
+    K = K <= 3 ? 3 : kMaxDiagonals;
+    if (2 * ((int64_t)K * A.n_rows - upper) > upper) return {};
+    for (auto& o : off)  // unused diagonals hold zeros only; offset 0 reads the row itself
+        o.resize((size_t)K, 0);
+    return off;
+}
+
+// By diagonals, or K = 0 where that does not apply (diagonals_of) or the stored
+// triangles are not equal bit for bit.
+template <typename T>
+static Dia<T> to_dia(eqs_ctx* c, const Csr<double>& A) {
+    Dia<T> D;
+    if (!c->diagonals || A.n_rows != A.n_cols || A.n_rows == 0) return D;
+    int K = 0;
+    const auto off = diagonals_of(c, A, K);
+    if (off.empty()) return D;
+    const int64_t n = A.n_rows;
+    std::vector<double> val((size_t)((K + 1) * n), 0.0);
+    for (int64_t i = 0; i < c->n_inst; ++i) {
+        const std::vector<int32_t>& o = off[(size_t)i];
+        auto which = [&](int32_t d) {
+            int k = 0;
+            while (o[(size_t)k] != d) ++k;
+            return k;
+        };
+        for (int32_t r = c->inst_row_off[i]; r < c->inst_row_off[i + 1]; ++r)
+            for (int32_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k) {
+                const int32_t d = A.col[k] - r;
+                if (d >= 0) val[(size_t)((d == 0 ? 0 : which(d) + 1) * n + r)] = A.val[k];
+            }
+        for (int32_t r = c->inst_row_off[i]; r < c->inst_row_off[i + 1]; ++r)
+            for (int32_t k = A.ptr[r]; k < A.ptr[r + 1]; ++k) {
+                const int32_t d = r - A.col[k];
+                if (d <= 0) continue;
+                int q = 0;  // a lower offset without an upper entry: not symmetric
+                while (q < K && o[(size_t)q] != d) ++q;
+                if (q == K || val[(size_t)((q + 1) * n + A.col[k])] != A.val[k]) return D;
+            }
+    }
+    D.K = K;
+    D.n = (int32_t)n;
+    for (int k = 0; k < K; ++k) D.off[k] = off[0][(size_t)k];
+    if (c->n_inst > 1) {
+        std::vector<int32_t> all;
+        for (const auto& o : off) all.insert(all.end(), o.begin(), o.end());
+        D.offs = upload_vec(c, all);
+    }
+    D.val = upload_vec(c, std::vector<T>(val.begin(), val.end()));
+    return D;
 }
 
 template <typename T>
@@ -1280,10 +1369,19 @@ static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
         lv.R.nnz = ah.R[l].nnz();
         if (l >= t) continue;
         if (l == 0) {
-            Csr<double> As = ah.A[0];  // A w D^-1
-            for (size_t k = 0; k < As.val.size(); ++k) As.val[k] *= lv.omega / d[0][As.col[k]];
-            lv.A = tuned_spmat<T>(c, As, "A0", true);
-            lv.sval = lv.A.sell.val;
+            if constexpr (std::is_same_v<T, double>) lv.D = c->Mdia;  // A_0 is M
+            else lv.D = to_dia<T>(c, ah.A[0]);
+            if (lv.D.K) {
+                std::vector<T> w(lv.n);
+                for (int32_t i = 0; i < lv.n; ++i) w[i] = (T)(lv.omega / d[0][i]);
+                lv.w = upload_vec(c, w);
+                c->tune_log += "A0: " + std::to_string(lv.D.K) + " upper diagonals (finest level)\n";
+            } else {
+                Csr<double> As = ah.A[0];  // A w D^-1
+                for (size_t k = 0; k < As.val.size(); ++k) As.val[k] *= lv.omega / d[0][As.col[k]];
+                lv.A = tuned_spmat<T>(c, As, "A0", true);
+                lv.sval = lv.A.sell.val;
+            }
             std::vector<T> dinv(lv.n);
             for (int32_t i = 0; i < lv.n; ++i) dinv[i] = (T)(1.0 / d[0][i]);
             lv.dinv = upload_vec(c, dinv);
@@ -1601,8 +1699,10 @@ void upload(eqs_ctx* c) {
     c->nnz_M = M.nnz();
     c->M = to_sell<double>(c, M, 1, row_order_pays(M));
     c->M.xcd = 1;  // the CG SpMV walks its row blocks in the XCD order (row_block in sell.h)
+    c->Mdia = to_dia<double>(c, M);
     c->tune_log += std::string("M: sell64") + (c->M.perm ? "s (rows sorted within 256-row windows)" : "") + ", " +
-                   (c->M.d16 ? "16-bit column offsets\n" : "32-bit columns\n");
+                   (c->M.d16 ? "16-bit column offsets" : "32-bit columns") +
+                   (c->Mdia.K ? "; in CG " + std::to_string(c->Mdia.K) + " upper diagonals\n" : "\n");
     AmgHost ah = build_sa_amg(M, c->amg, c->fold);
     if (c->amg.precision == EQS_PREC_FP32) upload_hierarchy<float>(c, ah, c->h32);
     else upload_hierarchy<double>(c, ah, c->h64);
@@ -1613,8 +1713,9 @@ void upload(eqs_ctx* c) {
     c->d_Y0 = vec(NF); c->d_Ya = vec(NF); c->d_Yb = vec(NF); c->d_Yc = vec(NF); c->d_F0 = vec(NF); c->d_F = vec(NF);
     c->d_rhs = vec(NF); c->d_rhs_alt = vec(NF); c->d_tmpN = vec(N); c->d_tmpN2 = vec(N);
     c->max_blocks = (std::max<int64_t>(N, T) + kBlock - 1) / kBlock + 1;
-    c->d_partials = vec(8 * c->max_blocks);
+    c->d_partials = vec(12 * c->max_blocks);
     c->d_scal = (PcgScalars*)dev_alloc(c, sizeof(PcgScalars) * (size_t)c->n_inst);
+    c->d_step = (PcgStep*)dev_alloc(c, sizeof(PcgStep) * (size_t)c->n_inst);
     c->d_sum = (PcgSummary*)dev_alloc(c, sizeof(PcgSummary));
     EQS_HIP(hipMemset(c->d_sum, 0, sizeof(PcgSummary)));
     c->d_force = (int32_t*)dev_alloc(c, sizeof(int32_t));
@@ -1669,6 +1770,7 @@ void free_device(eqs_ctx* c) {
     for (auto& e : c->ev)
         if (e) { (void)hipEventDestroy(e); e = nullptr; }
     c->M = Sell<double>{};
+    c->Mdia = Dia<double>{};
     c->stage_iters.clear();
     c->h64 = Hierarchy<double>{};
     c->h32 = Hierarchy<float>{};
@@ -1682,6 +1784,7 @@ void free_device(eqs_ctx* c) {
     c->d_rhs = c->d_rhs_alt = c->d_tmpN = c->d_tmpN2 = nullptr;
     c->d_partials = nullptr;
     c->d_scal = nullptr;
+    c->d_step = nullptr;
     c->built = false;
     c->have_Flast = false;
     c->guess.dev_ready = false;

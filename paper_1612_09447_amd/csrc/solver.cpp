@@ -96,7 +96,6 @@ int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit
     hipStream_t s = c->stream;
     const int prec = c->amg.precision;
     pcg_init(s, c, rhs, y, maxit, rtol, c->amg.flexible, mx_in);
-    pcg_zero_rhs_rows(s, c, y);  // instances with rhs = 0 get y = 0 (others untouched)
     check_launch();
     // Iterations are enqueued without waiting for the start's result: an
     // instance that is already done leaves its rows alone, and once all are
