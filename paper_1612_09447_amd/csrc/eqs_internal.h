@@ -12,9 +12,9 @@
 //          work vectors; a dense inverse at the coarsest level
 //
 // SELL-64: rows are cut into slices of 64 consecutive rows (one wavefront);
-// slice s stores width_s = max row length of its rows, column-major: entry k
-// of row 64 s + l sits at sptr[s] + 64 k + l. Short rows are padded with a
-// zero value and an in-range column.
+// slice s stores width_s = max row length of its rows, rounded up to even, in
+// pairs: entries 2 k and 2 k + 1 of row 64 s + l sit at sptr[s] + 128 k + 2 l.
+// Short rows are padded with a zero value and an in-range column.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -186,8 +186,8 @@ struct Level {
     // a V(1,1) visit of a level is b_next = Q^T b, then out = G b + Q x_next.
     SpMat<T> GQ;  // levels between the finest and the bottom: [G Q] on the stacked [b; x_next]
     SpMat<T> Q;   // finest level
-    Dia<T> D;     // finest level: A by diagonals (then A.sell holds nothing) ...
-    T* w = nullptr;  // ... and w D^-1, its column scaling in the pre-smoothing product
+    Dia<T> D;     // finest level: A by diagonals (then A.sell holds nothing)
+    T* w = nullptr;  // finest level, folded cycle: w D^-1
     // bottom level, when small enough: dense n x coarse_R_cols matrix from the
     // level above's input (its b; the finest level's residual or right-hand
     // side) straight to the bottom's solution, row-major

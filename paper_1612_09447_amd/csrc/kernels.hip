@@ -65,6 +65,8 @@ struct InstMap {
     const int32_t* __restrict__ blk_inst;  // [blocks] instance of each block's first row
     int32_t n_inst;
     int32_t rows1;  // the row count when n_inst == 1 (no table lookups then), else -1
+    int32_t subs;   // rows per thread of a workgroup, one after the other: 1 with several instances
+    int32_t nparts; // n_inst == 1: partial sums per array (part[B], not pairs) that the kernel reads
 };
 
 // B: the block's row-block index (its logical block, see row_block)
@@ -78,34 +80,48 @@ __device__ __forceinline__ void block_instances(const InstMap& m, int32_t& lo, i
     bound = m.row_off[lo + 1];
 }
 
-// Sums over the 256-thread block of K values per thread, each in a fixed order
-// (wavefront tree, then the four wavefront sums in index order), with one
-// barrier for all K; valid in thread 0. sh holds 4 K doubles and is used once
-// per kernel.
+// Sums over the block of K values per thread, each in a fixed order (wavefront
+// tree, then the wavefronts' sums in index order), with one barrier for all K;
+// valid in thread 0. sh holds K doubles per wavefront and is used once per
+// kernel.
 template <int K>
 __device__ __forceinline__ void block_sums(double (&v)[K], double* sh) {
 #pragma unroll
     for (int k = 0; k < K; ++k)
         for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_down(v[k], off, 64);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if (lane == 0)
 #pragma unroll
-        for (int k = 0; k < K; ++k) sh[4 * k + wid] = v[k];
+        for (int k = 0; k < K; ++k) sh[nw * k + wid] = v[k];
     __syncthreads();
     if (threadIdx.x == 0)
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = ((sh[4 * k] + sh[4 * k + 1]) + sh[4 * k + 2]) + sh[4 * k + 3];
+        for (int k = 0; k < K; ++k) {
+            double t = sh[nw * k];
+            for (int w = 1; w < nw; ++w) t += sh[nw * k + w];
+            v[k] = t;
+        }
 }
 
 // Thread 0 stores the block's pair of sums of each v[p] into part[p] (split by
 // `second`, i.e. row >= bound). A block whose rows all lie before bound (the
 // common case: the block lies inside one instance) has a zero second sum and
-// needs only one reduction.
+// needs only one reduction. With one instance (`one`) there are no pairs: part[p][B].
 constexpr int kPairSh = 16;  // doubles of shared memory store_pairs needs (NP <= 2)
 template <int NP>
-__device__ __forceinline__ void store_pairs(double* const (&part)[NP], const double (&v)[NP], bool second,
+__device__ __forceinline__ void store_pairs(double* const (&part)[NP], const double (&v)[NP], bool one, bool second,
                                             int32_t bound, double* sh, int64_t B) {
     static_assert(NP >= 1 && NP <= 2, "at most two partial arrays");
+    if (one) {
+        double a[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) a[p] = v[p];
+        block_sums<NP>(a, sh);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) part[p][B] = a[p];
+        return;
+    }
     const bool split = (int64_t)bound < (B + 1) * (int64_t)blockDim.x;  // uniform over the block
     if (!split) {
         double a[NP];
@@ -159,8 +175,8 @@ __device__ __forceinline__ void inst_blocks(const InstMap& m, int32_t i, int32_t
 // memory latency. The order of the additions is fixed (it does not depend on
 // timing).
 template <int NP>
-__device__ __forceinline__ void wave_range_sums(const double* const (&parts)[NP], int32_t lo, int32_t hi,
-                                                double (&out)[NP]) {
+__device__ __forceinline__ void wave_range_sums(const double* const (&parts)[NP], int32_t stride, int32_t lo,
+                                                int32_t hi, double (&out)[NP]) {
     constexpr int U = NP <= 2 ? 16 : 8;  // loads in flight per lane and array (registers: 2 NP U)
     const int lane = threadIdx.x & 63;
     double acc[NP];
@@ -172,7 +188,7 @@ __device__ __forceinline__ void wave_range_sums(const double* const (&parts)[NP]
         for (int u = 0; u < U; ++u) {
             const int32_t bc = min(b + 64 * u, hi);
 #pragma unroll
-            for (int p = 0; p < NP; ++p) t[p][u] = parts[p][2 * (int64_t)bc];
+            for (int p = 0; p < NP; ++p) t[p][u] = parts[p][stride * (int64_t)bc];
         }
         // every load is issued before the first add (left alone, the scheduler starts adding after the
         // first loads, and the wait for them holds back the rest)
@@ -221,7 +237,7 @@ __device__ __forceinline__ void for_each_instance_sum(const double* const (&part
             double hv[NP];
 #pragma unroll
             for (int p = 0; p < NP; ++p) hv[p] = sub == 0 ? parts[p][2 * (int64_t)b0 + head] : 0.0;
-            wave_range_sums<NP>(parts, lo, hi, v);
+            wave_range_sums<NP>(parts, 2, lo, hi, v);
             if (sub == 0)
 #pragma unroll
                 for (int p = 0; p < NP; ++p) v[p] += hv[p];
@@ -245,51 +261,68 @@ __device__ __forceinline__ void for_each_instance_sum(const double* const (&part
 }
 
 // ---- reductions by the consumer -----------------------------------------
-// Up to kProBlocks blocks per instance, the kernel that needs an instance's
-// dot products sums the producer's block partials itself, every workgroup the
-// same way (fixed order, so all get the same value): at most kProU loads per
-// thread and array, which travel together with the kernel's own first loads.
-// A finaliser launch in between costs 4-6 us (its launch, a chain of loads,
-// the sum, the stores of the scalars), more than a small SpMV; with more blocks
-// every workgroup would read more partials than rows.
-constexpr int kProU = 5;
-constexpr int kProBlocks = 256 * kProU + 1;
-template <int NP>
+// The kernel that needs an instance's dot products sums the producer's partials
+// itself, every workgroup the same way (fixed order, so all get the same value):
+// a few loads per thread and array, which travel together with the kernel's own
+// first loads. A finaliser launch in between costs 4-6 us (its launch, a chain
+// of loads, the sum, the stores of the scalars; 13 us for four arrays of 8256),
+// more than a small SpMV. Up to pro_blocks(kProSmall) workgroups take one row per
+// thread; a single larger system takes several (InstMap::subs), for at most
+// pro_blocks(kProBig) workgroups. (1024-thread workgroups instead: the update at
+// 2.1M rows 127 us instead of 20, their registers spill.)
+constexpr int pro_blocks(int u) { return 256 * u + 1; }
+constexpr int kProSmall = 5, kProBig = 9;  // loads per thread and array (the update of a large system: 4)
+template <int NP, int U>
 struct ProParts {
-    double t[NP][kProU], h[NP];
+    double t[NP][U], h[NP];
     int32_t lo, hi;
 };
-template <int NP>
-__device__ __forceinline__ void pro_load(const double* const (&parts)[NP], const InstMap& m, int32_t i, ProParts<NP>& P) {
+template <int NP, int U>
+__device__ __forceinline__ void pro_load(const double* const (&parts)[NP], const InstMap& m, int32_t i,
+                                         ProParts<NP, U>& P) {
     int32_t b0, b1, head;
-    inst_blocks(m, i, b0, b1, head);
+    const bool one = m.rows1 >= 0;
+    if (one) {
+        b0 = 0;
+        b1 = m.nparts - 1;
+        head = 0;
+    } else {
+        inst_blocks(m, i, b0, b1, head);
+    }
+    const int32_t stride = one ? 1 : 2;
     P.lo = b0 + 1 + (int32_t)threadIdx.x;
     P.hi = b1;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-        P.h[p] = threadIdx.x == 0 && b1 >= b0 ? parts[p][2 * (int64_t)b0 + head] : 0.0;
+        P.h[p] = threadIdx.x == 0 && b1 >= b0 ? parts[p][stride * (int64_t)b0 + head] : 0.0;
 #pragma unroll
-        for (int u = 0; u < kProU; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int32_t b = P.lo + 256 * u;
-            P.t[p][u] = b <= P.hi ? parts[p][2 * (int64_t)b] : 0.0;
+            P.t[p][u] = b <= P.hi ? parts[p][stride * (int64_t)b] : 0.0;
         }
     }
 }
-// every thread gets the sums; sh: 4 NP doubles used by this call only
-template <int NP>
-__device__ __forceinline__ void pro_sum(const ProParts<NP>& P, double* sh, double (&out)[NP]) {
+// every thread gets the sums; sh: NP doubles per wavefront used by this call only
+template <int NP, int U>
+__device__ __forceinline__ void pro_sum(const ProParts<NP, U>& P, double* sh, double (&out)[NP]) {
+    constexpr int nw = 4;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         double v = P.h[p];
 #pragma unroll
-        for (int u = 0; u < kProU; ++u) v += P.t[p][u];
+        for (int u = 0; u < U; ++u) v += P.t[p][u];
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) sh[4 * p + wave] = v;
+        if (lane == 0) sh[nw * p + wave] = v;
     }
     __syncthreads();
 #pragma unroll
-    for (int p = 0; p < NP; ++p) out[p] = ((sh[4 * p] + sh[4 * p + 1]) + sh[4 * p + 2]) + sh[4 * p + 3];
+    for (int p = 0; p < NP; ++p) {
+        double t = sh[nw * p];
+#pragma unroll
+        for (int w = 1; w < nw; ++w) t += sh[nw * p + w];
+        out[p] = t;
+    }
 }
 
 // ------------------------------------------------------------- simple ops
@@ -1170,7 +1203,7 @@ __global__ __launch_bounds__(256, (U >= 16 ? 4 : kSparseWaves)) void k_postsmoot
         block_instances(m, lo, bound, B);
         double* const parts[2] = {part_rz, part_rzold};
         const double vals[2] = {rz, rzo};
-        store_pairs<2>(parts, vals, row >= bound, bound, sh, B);
+        store_pairs<2>(parts, vals, m.rows1 >= 0, row >= bound, bound, sh, B);
     }
 }
 
@@ -1191,7 +1224,6 @@ __device__ __forceinline__ T presmoothed(const DiaOp<T, K>& op, int64_t g, int32
 
 template <typename T, typename Op>
 __global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(Op op, InstMap m, const T* __restrict__ w,
-                                                                   const T* __restrict__ dinv, T omega,
                                                                    const double* __restrict__ r, T* __restrict__ u,
                                                                    T* __restrict__ res) {
     const int64_t B = op.block();
@@ -1203,7 +1235,7 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(Op op, InstMa
     const T acc = presmoothed(op, g, row, m, row >= bound ? lo + 1 : lo, w, r);
     if (row < op.rows()) {
         const T ri = (T)r[row], rs = ri - acc;
-        u[row] = omega * dinv[row] * (ri + rs);
+        u[row] = w[row] * (ri + rs);
         res[row] = rs;
     }
 }
@@ -1213,39 +1245,40 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_presmooth_u(Op op, InstMa
 // w D^-1 (2 r - A w D^-1 r), from A_0 and Q in one row order; else it is read (u).
 template <typename T, bool DOT, bool DIRECT, typename Op>
 __global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, Op op, const T* __restrict__ w,
-                                                                 const T* __restrict__ dinv, T omega,
                                                                  const T* __restrict__ u, const double* __restrict__ r,
                                                                  const T* __restrict__ x1, double* __restrict__ z,
                                                                  InstMap m, double* __restrict__ part_rz,
                                                                  double* __restrict__ part_rzold) {
     __shared__ double sh[kPairSh];
     const int64_t B = row_block(Q.xcd);
-    const int64_t g = B * blockDim.x + threadIdx.x;
-    const int32_t row = sell_perm_row<1>(Q.perm, g);
     int32_t lo, bound;
     block_instances(m, lo, bound, B);
-    const bool second = row >= bound;
+    bool second = false;
     double rz = 0.0, rzo = 0.0;
-    if (g < (int64_t)Q.n_slices * 64) {
+    for (int32_t k = 0; k < m.subs; ++k) {
+        const int64_t g = (B * m.subs + k) * blockDim.x + threadIdx.x;
+        if (g >= (int64_t)Q.n_slices * 64) break;
+        const int32_t row = sell_perm_row<1>(Q.perm, g);
+        second = row >= bound;
         const bool in = row < Q.n_rows;
         T ui = T(0);
         double ri = 0.0, zo = 0.0;
         if (in) {  // issued ahead of the row sums
             ri = r[row];
             if (DOT) zo = z[row];
-            ui = DIRECT ? dinv[row] : u[row];
+            ui = DIRECT ? w[row] : u[row];
         }
         const T qx = sell_row<1>(Q, g, row, x1);
         if constexpr (DIRECT) {
             T ar = T(0);
             if (op.live(g)) ar = presmoothed(op, g, row, m, second ? lo + 1 : lo, w, r);
-            ui = omega * ui * (T(2) * (T)ri - ar);
+            ui = ui * (T(2) * (T)ri - ar);
         }
         if (in) {
             const T v = ui + qx;
             if (DOT) {
-                rzo = ri * zo;
-                rz = ri * (double)v;
+                rzo += ri * zo;
+                rz += ri * (double)v;
             }
             z[row] = (double)v;
         }
@@ -1253,7 +1286,7 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_post_fold(SellView<T> Q, 
     if (DOT) {
         double* const parts[2] = {part_rz, part_rzold};
         const double vals[2] = {rz, rzo};
-        store_pairs<2>(parts, vals, second, bound, sh, B);
+        store_pairs<2>(parts, vals, m.rows1 >= 0, second, bound, sh, B);
     }
 }
 
@@ -1425,7 +1458,7 @@ static void launch_postsmooth(hipStream_t s, eqs_ctx* c, int cls, const Level<T>
                                                 EQS_LAUNCH_TIMED(c, cls, (k_postsmooth<L_, T, T, T, false, U_>),
                                                                  dim3(sell_grid(lv.A.sell)), dim3(kBlock), 0, s,
                                                                  view(lv.A.sell), (const T*)lv.dinv, (T)lv.omega, b,
-                                                                 x, out, InstMap{nullptr, nullptr, 0, -1}, nullptr,
+                                                                 x, out, InstMap{nullptr, nullptr, 0, -1, 1, 0}, nullptr,
                                                                  nullptr)));
     } else {
         EQS_LANES_SWITCH(lv.A.lanes, EQS_LAUNCH_TIMED(c, cls, (k_csr_postsmooth<L_, T, T, T>), dim3(csr_grid(lv.A)),
@@ -1546,12 +1579,33 @@ __global__ __launch_bounds__(256) void k_dense_precond(const T* __restrict__ inv
         block_instances(m, lo, bound, B);
         double* const parts[2] = {part_rz, part_rzold};
         const double vals[2] = {rz, rzo};
-        store_pairs<2>(parts, vals, i >= bound, bound, sh, B);
+        store_pairs<2>(parts, vals, m.rows1 >= 0, i >= bound, bound, sh, B);
     }
 }
 
-static InstMap inst_map(const eqs_ctx* c) {
-    return InstMap{c->d_inst_row, c->d_blk_inst, (int32_t)c->n_inst, c->n_inst == 1 ? (int32_t)c->n_free : -1};
+// Shape of the kernels around the CG dot products: rows per thread, workgroups,
+// and (InstMap::nparts) the partials a consumer reads per array. Small systems,
+// several instances and the plain cycle (whose smoothers take one row per
+// thread) use one row per thread. A single system of more than
+// pro_blocks(kProSmall) blocks: the SpMV and the update, each of whose
+// workgroups starts with those sums, about 1000 workgroups; the others twice as
+// many, because the gathers of the V-cycle's last kernel want more wavefronts.
+// At 2.1M rows: V-cycle's last kernel 45 us with 2064 workgroups, 56 with 918;
+// SpMV 41 and 35, update 24 and 20.
+struct PartShape {
+    int32_t subs;
+    unsigned grid;
+};
+static PartShape part_shape(const eqs_ctx* c, bool spmv = false) {
+    const bool loops = c->amg.precision == EQS_PREC_FP32 ? c->h32.folded : c->h64.folded;
+    const int64_t nb = grid_for(c->n_free);
+    if (c->n_inst > 1 || !loops || nb <= pro_blocks(kProSmall)) return {1, (unsigned)nb};
+    const int64_t most = spmv ? 1024 : pro_blocks(kProBig), subs = (nb + most - 1) / most;
+    return {(int32_t)subs, (unsigned)((nb + subs - 1) / subs)};
+}
+static InstMap inst_map(const eqs_ctx* c, bool spmv = false, bool reads_spmv = false) {
+    return InstMap{c->d_inst_row, c->d_blk_inst, (int32_t)c->n_inst, c->n_inst == 1 ? (int32_t)c->n_free : -1,
+                   part_shape(c, spmv).subs, (int32_t)part_shape(c, reads_spmv).grid};
 }
 
 // The folded cycle. Kernel classes: a launch that does the work of two classes
@@ -1570,8 +1624,7 @@ static void vcycle_folded(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const doub
     if (!h.direct)
         EQS_WITH_OP(l0.D, sview(l0),
                     EQS_LAUNCH_TIMED(c, EQS_KCLASS_PRESMOOTH0, (k_presmooth_u<T, std::decay_t<decltype(op)>>),
-                                     dim3(row_grid(l0.n)), b, 0, s, op, m, (const T*)l0.w, (const T*)l0.dinv,
-                                     (T)l0.omega, r, l0.x, l0.res));
+                                     dim3(row_grid(l0.n)), b, 0, s, op, m, (const T*)l0.w, r, l0.x, l0.res));
     const bool whole = t == 1 && bot.coarse_R;  // the finest restriction is part of the bottom's product
     if (whole) {
         prof_begin(c, EQS_KCLASS_VCOARSE, s);
@@ -1598,11 +1651,12 @@ static void vcycle_folded(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const doub
         launch_mv<T, T>(s, c, l == 1 ? EQS_KCLASS_POSTSMOOTH1 : -1, -1, h.lv[l].GQ, (const T*)h.lv[l].b, h.lv[l].xs, 0,
                         MV_PLAIN);
     prof_end(c, EQS_KCLASS_VCOARSE, s);
+    const PartShape ps = part_shape(c);
 #define EQS_POST_FOLD(DOT_, DIRECT_)                                                                                    \
     EQS_LAUNCH_TIMED2(c, EQS_KCLASS_POSTSMOOTH0, EQS_KCLASS_PROLONG0,                                                   \
-                      (k_post_fold<T, DOT_, DIRECT_, std::decay_t<decltype(op)>>), dim3(sell_grid(l0.Q.sell)), b, 0, s, \
-                      view(l0.Q.sell), op, (const T*)l0.w, (const T*)l0.dinv, (T)l0.omega, (const T*)l0.x, r,           \
-                      (const T*)h.lv[1].xs, z, m, part_rz, part_rzold)
+                      (k_post_fold<T, DOT_, DIRECT_, std::decay_t<decltype(op)>>), dim3(ps.grid), b, 0, s,             \
+                      view(l0.Q.sell), op, (const T*)l0.w, (const T*)l0.x, r, (const T*)h.lv[1].xs, z, m, part_rz,      \
+                      part_rzold)
     if (h.direct) {
         if (part_rz) EQS_WITH_OP(l0.D, sview(l0), EQS_POST_FOLD(true, true));
         else EQS_WITH_OP(l0.D, sview(l0), EQS_POST_FOLD(false, true));
@@ -1678,7 +1732,7 @@ void vcycle(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* r, double*
             else
                 EQS_LAUNCH_TIMED(c, EQS_KCLASS_POSTSMOOTH0, (k_postsmooth<1, T, double, double, false>),
                                  dim3(sell_grid(lv.A.sell)), b, 0, s, view(lv.A.sell), (const T*)lv.dinv, (T)lv.omega,
-                                 r, (const T*)lv.x, z, InstMap{nullptr, nullptr, 0, -1}, nullptr, nullptr);
+                                 r, (const T*)lv.x, z, InstMap{nullptr, nullptr, 0, -1, 1, 0}, nullptr, nullptr);
         }
     }
 }
@@ -1701,26 +1755,28 @@ __global__ __launch_bounds__(256, kSparseWaves) void k_pcg_residual(Op op, InstM
     __shared__ double sh[kPairSh];
     if (when_done && !*when_done) return;  // queued ahead of the host's decision: only once every instance is done
     const int64_t B = op.block();
-    const int64_t g = B * blockDim.x + threadIdx.x;
-    const int32_t row = op.row(g);  // the row order, if any, stays inside the block's rows
     int32_t lo, bound;
     block_instances(m, lo, bound, B);
-    const bool second = row >= bound;
+    bool second = false;
     double rr = 0.0, bb = 0.0;
-    if (op.live(g)) {
+    for (int32_t k = 0; k < m.subs; ++k) {
+        const int64_t g = (B * m.subs + k) * blockDim.x + threadIdx.x;
+        if (!op.live(g)) break;
+        const int32_t row = op.row(g);  // the row order, if any, stays inside the block's rows
+        second = row >= bound;
         const double mx = op.sum(g, row, m, second ? lo + 1 : lo, [&](int32_t j) { return x[j]; });
         if (row < op.rows()) {
             const double bi = rhs[row];
             const double ri = bi - mx;
             r[row] = ri;
             if (mx_out) mx_out[row] = mx;
-            rr = ri * ri;
-            bb = bi * bi;
+            rr += ri * ri;
+            bb += bi * bi;
         }
     }
     double* const parts[2] = {part_rr, part_bb};
     const double vals[2] = {rr, bb};
-    store_pairs<2>(parts, vals, second, bound, sh, B);
+    store_pairs<2>(parts, vals, m.rows1 >= 0, second, bound, sh, B);
 }
 
 // r = rhs - mx with mx = M x stored by the residual check that ended the
@@ -1731,20 +1787,24 @@ __global__ __launch_bounds__(256) void k_pcg_residual_mx(InstMap m, const double
                                                           int64_t n, double* __restrict__ part_rr,
                                                           double* __restrict__ part_bb) {
     __shared__ double sh[kPairSh];
-    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t B = blockIdx.x;
+    int32_t lo, bound;
+    block_instances(m, lo, bound, B);
+    bool second = false;
     double rr = 0.0, bb = 0.0;
-    if (row < n) {
+    for (int32_t k = 0; k < m.subs; ++k) {
+        const int64_t row = (B * m.subs + k) * blockDim.x + threadIdx.x;
+        if (row >= n) break;
+        second = row >= bound;
         const double bi = rhs[row];
         const double ri = bi - mx[row];
         r[row] = ri;
-        rr = ri * ri;
-        bb = bi * bi;
+        rr += ri * ri;
+        bb += bi * bi;
     }
-    int32_t lo, bound;
-    block_instances(m, lo, bound, blockIdx.x);
     double* const parts[2] = {part_rr, part_bb};
     const double vals[2] = {rr, bb};
-    store_pairs<2>(parts, vals, row >= bound, bound, sh, blockIdx.x);
+    store_pairs<2>(parts, vals, m.rows1 >= 0, second, bound, sh, B);
 }
 
 // CG decisions from the reduced dot products.
@@ -1825,19 +1885,19 @@ __device__ __forceinline__ void store_summary_one(PcgSummary* __restrict__ sum, 
 struct DotParts {
     double *pq, *rq, *qq, *rr;
 };
-__device__ __forceinline__ void store_dots(const DotParts& D, const double (&v)[4], bool second, int32_t bound,
-                                           double* sh, int64_t B) {
+__device__ __forceinline__ void store_dots(const DotParts& D, const double (&v)[4], bool one, bool second,
+                                           int32_t bound, double* sh, int64_t B) {
     double* const a[2] = {D.pq, D.rq};
     const double va[2] = {v[0], v[1]};
-    store_pairs<2>(a, va, second, bound, sh, B);
+    store_pairs<2>(a, va, one, second, bound, sh, B);
     double* const b[2] = {D.qq, D.rr};
     const double vb[2] = {v[2], v[3]};
-    store_pairs<2>(b, vb, second, bound, sh + kPairSh, B);
+    store_pairs<2>(b, vb, one, second, bound, sh + kPairSh, B);
 }
 
 // q = M z + beta q, p = z + beta p (so q = M p without a second pass); pair
 // partials of p.q, r.q, q.q and r.r. stop (may be NULL) ends the launch at entry.
-// PRO: every workgroup sums the r.z partials of its rows' instances and forms
+// PRO (loads per thread and array, pro_load): every workgroup sums the r.z partials of its rows' instances and forms
 // their beta itself; the workgroup of an instance's first row leaves what it
 // found in step[] for the update (scal is only read here: other workgroups
 // still need it). Else beta and fresh are read from scal, where the finaliser
@@ -1846,12 +1906,12 @@ __device__ __forceinline__ void store_dots(const DotParts& D, const double (&v)[
 // places it, ahead of the row's loads). Rows of an instance that is done keep
 // their p and q, except with one instance, where they are written and not read:
 // a finished solve, and a restart (beta = 0), read neither.
-template <bool ONE, bool PRO, typename Op>
+template <bool ONE, int PRO, typename Op>
 __global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_spmv(
     Op op, InstMap m, const double* __restrict__ z, const double* __restrict__ r, double* __restrict__ p,
     double* __restrict__ q, DotParts D, const PcgScalars* __restrict__ scal, PcgStep* __restrict__ step,
     const double* __restrict__ part_rz, const double* __restrict__ part_rzold, const int32_t* __restrict__ stop) {
-    __shared__ double sh[2 * kPairSh + 16];
+    __shared__ double sh[2 * kPairSh + 2 * 2 * 4];
     const int64_t B = op.block();
     int32_t lo, bound;
     block_instances(m, lo, bound, B);
@@ -1862,67 +1922,70 @@ __global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_spmv(
         }
         return;
     }
-    const int64_t g = B * blockDim.x + threadIdx.x;
-    const int32_t row = op.row(g);  // the row order, if any, stays inside the block's rows
-    const bool second = row >= bound;
     const double* const rzp[2] = {part_rz, part_rzold};
-    ProParts<2> P;
-    if constexpr (PRO) pro_load<2>(rzp, m, lo, P);
-    double beta1 = 0.0;
-    int32_t fresh1 = 0;
+    ProParts<2, PRO ? PRO : 1> P;
+    if constexpr (PRO) pro_load(rzp, m, lo, P);
+    double beta = 0.0, beta2 = 0.0;  // of instances lo and lo + 1
+    int32_t fresh = 0, fresh2 = 0, done = 0, done2 = 0;
     if constexpr (ONE && !PRO) {
-        beta1 = vec_load(&scal->beta);
-        fresh1 = vec_load(&scal->fresh);
-    }
-    double mz = 0.0, zi = 0.0, po = 0.0, qo = 0.0, ri = 0.0;
-    const bool in = op.live(g) && row < op.rows();
-    if (op.live(g)) mz = op.sum(g, row, m, second ? lo + 1 : lo, [&](int32_t j) { return z[j]; });
-    if (in) {
-        zi = z[row];
-        po = p[row];
-        qo = q[row];
-        ri = r[row];
-    }
-    double beta = beta1;
-    int32_t fresh = fresh1, done = 0;
-    if constexpr (PRO) {
-        const bool split = !ONE && (int64_t)bound < (B + 1) * (int64_t)blockDim.x;
-        const int32_t i1 = min(lo + 1, m.n_inst - 1);
-        for (int k = 0; k < (split ? 2 : 1); ++k) {
-            const int32_t i = k ? i1 : lo;
-            double sums[2];
-            if (k) pro_load<2>(rzp, m, i, P);
-            pro_sum<2>(P, sh + 2 * kPairSh + 8 * k, sums);
-            const PcgScalars& S = scal[i];
-            const int32_t dn = S.done, fr = S.fresh;
-            const double be = fin_beta_of(fr, S.flexible, S.rho, sums[0], sums[1]);
-            const int32_t first = ONE ? 0 : m.row_off[i];
-            if (threadIdx.x == 0 && (first >> 8) == B)
-                step[i] = PcgStep{sums[0], S.bb, S.tol2, S.it, S.maxit, dn, dn ? 0 : fin_rz(sums[0]), fr, 0};
-            if (second == (k == 1)) {
-                beta = be;
-                fresh = fr;
-                done = dn;
-            }
-        }
-    } else if constexpr (!ONE) {
-        const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
-        beta = S.beta;
-        fresh = S.fresh;
-        done = S.done;
+        beta = vec_load(&scal->beta);
+        fresh = vec_load(&scal->fresh);
     }
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (in && (ONE || !done)) {
-        const double pi = fresh ? zi : zi + beta * po;
-        const double qi = fresh ? mz : mz + beta * qo;
-        p[row] = pi;
-        q[row] = qi;
-        v[0] = pi * qi;
-        v[1] = ri * qi;
-        v[2] = qi * qi;
-        v[3] = ri * ri;
+    bool second = false;
+    for (int32_t k = 0; k < m.subs; ++k) {
+        const int64_t g = (B * m.subs + k) * blockDim.x + threadIdx.x;
+        const bool live = op.live(g);
+        const int32_t row = live ? op.row(g) : 0;  // the row order, if any, stays inside the block's rows
+        second = live && row >= bound;
+        const bool in = live && row < op.rows();
+        double mz = 0.0, zi = 0.0, po = 0.0, qo = 0.0, ri = 0.0;
+        if (live) mz = op.sum(g, row, m, second ? lo + 1 : lo, [&](int32_t j) { return z[j]; });
+        if (in) {
+            zi = z[row];
+            po = p[row];
+            qo = q[row];
+            ri = r[row];
+        }
+        if (k == 0) {  // the scalars are first needed here, with the first rows' loads under way
+            if constexpr (PRO) {
+                const bool split = !ONE && (int64_t)bound < (B + 1) * (int64_t)blockDim.x;
+                for (int e = 0; e < (split ? 2 : 1); ++e) {
+                    const int32_t i = e ? min(lo + 1, m.n_inst - 1) : lo;
+                    double sums[2];
+                    if (e) pro_load(rzp, m, i, P);
+                    pro_sum(P, sh + 2 * kPairSh + 8 * e, sums);
+                    const PcgScalars& S = scal[i];
+                    const int32_t dn = S.done, fr = S.fresh;
+                    const double be = fin_beta_of(fr, S.flexible, S.rho, sums[0], sums[1]);
+                    const int32_t first = ONE ? 0 : m.row_off[i];
+                    if (threadIdx.x == 0 && (first >> 8) == B)
+                        step[i] = PcgStep{sums[0], S.bb, S.tol2, S.it, S.maxit, dn, dn ? 0 : fin_rz(sums[0]), fr, 0};
+                    (e ? beta2 : beta) = be;
+                    (e ? fresh2 : fresh) = fr;
+                    (e ? done2 : done) = dn;
+                }
+            } else if constexpr (!ONE) {
+                const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
+                beta = beta2 = S.beta;
+                fresh = fresh2 = S.fresh;
+                done = done2 = S.done;
+            }
+        }
+        if (in && (ONE || !(second ? done2 : done))) {
+            const bool fr = ONE ? fresh : second ? fresh2 : fresh;
+            const double be = ONE ? beta : second ? beta2 : beta;
+            const double pi = fr ? zi : zi + be * po;
+            const double qi = fr ? mz : mz + be * qo;
+            p[row] = pi;
+            q[row] = qi;
+            v[0] += pi * qi;
+            v[1] += ri * qi;
+            v[2] += qi * qi;
+            v[3] += ri * ri;
+        }
     }
-    store_dots(D, v, second, bound, sh, B);
+    store_dots(D, v, m.rows1 >= 0, second, bound, sh, B);
 }
 
 // x += alpha p, r -= alpha q where the iteration's step is to be applied; x = 0
@@ -1932,69 +1995,71 @@ __global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_spmv(
 // summary the host polls). Else the finaliser left alpha and apply in scal. xcd:
 // M's block order, so that each workgroup reads the p and q rows the SpMV wrote
 // on the same XCD.
-template <bool ONE, bool PRO>
+template <bool ONE, int PRO>
 __global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_update(
     InstMap m, double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
     const double* __restrict__ q, int64_t n, DotParts D, PcgScalars* __restrict__ scal,
     const PcgStep* __restrict__ step, PcgSummary* __restrict__ sum, PcgSummary* __restrict__ host_sum, int32_t xcd) {
-    __shared__ double sh[32];
+    __shared__ double sh[2 * 4 * 4];
     const int64_t B = row_block(xcd);
-    const int64_t i = B * blockDim.x + threadIdx.x;
     int32_t lo, bound;
     block_instances(m, lo, bound, B);
-    const bool second = i >= bound;
     const double* const dp[4] = {D.pq, D.rq, D.qq, D.rr};
-    ProParts<4> P;
-    if constexpr (PRO) pro_load<4>(dp, m, lo, P);
-    double alpha = 0.0, bb = 0.0;
-    int32_t apply = 0;
+    ProParts<4, PRO ? PRO : 1> P;
+    if constexpr (PRO) pro_load(dp, m, lo, P);
+    double alpha = 0.0, alpha2 = 0.0, bb = 0.0, bb2 = 0.0;  // of instances lo and lo + 1
+    int32_t apply = 0, apply2 = 0;
     if constexpr (ONE && !PRO) {
         alpha = vec_load(&scal->alpha);
         bb = vec_load(&scal->bb);
         apply = vec_load(&scal->apply);
     }
-    double pi = 0.0, qi = 0.0, xi = 0.0, ri = 0.0;
-    if (i < n) {
-        pi = p[i];
-        qi = q[i];
-        xi = x[i];
-        ri = r[i];
-    }
-    __builtin_amdgcn_sched_barrier(0);  // all loads are issued before anything waits
-    if constexpr (PRO) {
-        const bool split = !ONE && (int64_t)bound < (B + 1) * (int64_t)blockDim.x;
-        const int32_t i1 = min(lo + 1, m.n_inst - 1);
-        for (int k = 0; k < (split ? 2 : 1); ++k) {
-            const int32_t j = k ? i1 : lo;
-            double d[4];
-            if (k) pro_load<4>(dp, m, j, P);
-            pro_sum<4>(P, sh + 16 * k, d);
-            const PcgStep S = step[j];
-            StepOut o{};
-            if (!S.done) o = fin_step(S, d);
-            const int32_t first = ONE ? 0 : m.row_off[j];
-            if (!S.done && threadIdx.x == 0 && (first >> 8) == B) {
-                store_step(scal + j, S.rho, o);
-                if (ONE) store_summary_one(sum, host_sum, o.done, o.status, S.bb, o.it, o.relres);
-            }
-            if (second == (k == 1)) {
-                alpha = o.alpha;
-                apply = o.apply;
-                bb = S.bb;
+    for (int32_t k = 0; k < m.subs; ++k) {
+        const int64_t i = (B * m.subs + k) * blockDim.x + threadIdx.x;
+        const bool second = i >= bound;
+        double pi = 0.0, qi = 0.0, xi = 0.0, ri = 0.0;
+        if (i < n) {
+            pi = p[i];
+            qi = q[i];
+            xi = x[i];
+            ri = r[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);  // all loads are issued before anything waits
+        if (k == 0) {
+            if constexpr (PRO) {
+                const bool split = !ONE && (int64_t)bound < (B + 1) * (int64_t)blockDim.x;
+                for (int e = 0; e < (split ? 2 : 1); ++e) {
+                    const int32_t j = e ? min(lo + 1, m.n_inst - 1) : lo;
+                    double d[4];
+                    if (e) pro_load(dp, m, j, P);
+                    pro_sum(P, sh + 16 * e, d);
+                    const PcgStep S = step[j];
+                    StepOut o{};
+                    if (!S.done) o = fin_step(S, d);
+                    const int32_t first = ONE ? 0 : m.row_off[j];
+                    if (!S.done && threadIdx.x == 0 && (first >> 8) == B) {
+                        store_step(scal + j, S.rho, o);
+                        if (ONE) store_summary_one(sum, host_sum, o.done, o.status, S.bb, o.it, o.relres);
+                    }
+                    (e ? alpha2 : alpha) = o.alpha;
+                    (e ? apply2 : apply) = o.apply;
+                    (e ? bb2 : bb) = S.bb;
+                }
+            } else if constexpr (!ONE) {
+                const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
+                alpha = alpha2 = S.alpha;
+                apply = apply2 = S.apply;
+                bb = bb2 = S.bb;
             }
         }
-    } else if constexpr (!ONE) {
-        const PcgScalars& S = scal[min(second ? lo + 1 : lo, m.n_inst - 1)];
-        alpha = S.alpha;
-        apply = S.apply;
-        bb = S.bb;
-    }
-    if (i < n) {
-        if (apply) {
-            x[i] = xi + alpha * pi;
-            r[i] = ri - alpha * qi;
-        } else if (bb == 0.0) {
-            x[i] = 0.0;
+        if (i < n) {
+            const double al = ONE ? alpha : second ? alpha2 : alpha;
+            if (ONE ? apply : second ? apply2 : apply) {
+                x[i] = xi + al * pi;
+                r[i] = ri - al * qi;
+            } else if ((ONE ? bb : second ? bb2 : bb) == 0.0) {
+                x[i] = 0.0;
+            }
         }
     }
 }
@@ -2057,18 +2122,17 @@ __device__ void summarise(const PcgScalars* __restrict__ s, int32_t n, PcgSummar
 // LDS, and the loads into it would be waited for before the partials' loads
 // are issued).
 // One instance: every wavefront sums an equal share of the blocks' first
-// partials (the second is 0 when there is one instance); thread 0 gets the
+// partials; thread 0 gets the
 // totals. The order of the additions is fixed.
 template <int NP>
-__device__ __forceinline__ void single_instance_sums(const double* const (&parts)[NP], int32_t rows,
+__device__ __forceinline__ void single_instance_sums(const double* const (&parts)[NP], int32_t nb,
                                                      double (&out)[NP]) {
     __shared__ double sh[NP][kFinWaves];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int32_t nb = (rows + 255) >> 8;
     const int32_t lo = (int32_t)(((int64_t)nb * wave) / kFinWaves);
     const int32_t hi = (int32_t)(((int64_t)nb * (wave + 1)) / kFinWaves) - 1;
     double v[NP];
-    wave_range_sums<NP>(parts, lo, hi, v);
+    wave_range_sums<NP>(parts, 1, lo, hi, v);
     if (lane == 0)
 #pragma unroll
         for (int p = 0; p < NP; ++p) sh[p][wave] = v[p];
@@ -2108,7 +2172,7 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
         int32_t it = vec_load(&p->it), mx = vec_load(&p->maxit), done = vec_load(&p->done);
         int32_t status = vec_load(&p->status), fresh = vec_load(&p->fresh), flex = vec_load(&p->flexible);
         double v[2];
-        single_instance_sums<2>(parts, m.rows1, v);
+        single_instance_sums<2>(parts, m.nparts, v);
         // the flags are tested only here, so that no wait for them precedes the partials' loads
         const int32_t skip = when_done ? !all_done : 0;
         const int32_t forced = (mode == 1 && force) ? force_raw : 0;
@@ -2225,7 +2289,7 @@ __global__ __launch_bounds__(kFin) void k_fin_beta(PcgScalars* __restrict__ s, P
         const int32_t it = vec_load(&s->it), maxit = vec_load(&s->maxit), done = vec_load(&s->done);
         const int32_t fresh = vec_load(&s->fresh), flexible = vec_load(&s->flexible);
         double v[2];
-        single_instance_sums<2>(parts, m.rows1, v);
+        single_instance_sums<2>(parts, m.nparts, v);
         if (threadIdx.x == 0) {
             s->beta = fin_beta_of(fresh, flexible, rho, v[0], v[1]);
             *step = PcgStep{v[0], bb, tol2, it, maxit, done, done ? 0 : fin_rz(v[0]), fresh, 0};
@@ -2257,7 +2321,7 @@ __global__ __launch_bounds__(kFin) void k_fin_step(PcgScalars* __restrict__ s, c
         S.brk = vec_load(&t->brk);
         S.fresh = vec_load(&t->fresh);
         double v[4];
-        single_instance_sums<4>(parts, m.rows1, v);
+        single_instance_sums<4>(parts, m.nparts, v);
         if (threadIdx.x == 0) {
             if (S.done) {
                 s->apply = 0;
@@ -2316,14 +2380,15 @@ static unsigned fin_grid(const eqs_ctx* c) { return (unsigned)((c->n_inst + kFin
 void pcg_init(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, int32_t maxit, double rtol,
               int flexible, const double* mx) {
     using OpT = double;
-    const unsigned nb = row_grid(c->n_free);
+    const PartShape ps = part_shape(c);
     if (mx)
-        hipLaunchKernelGGL(k_pcg_residual_mx, dim3(grid_for(c->n_free)), dim3(kBlock), 0, s, inst_map(c), rhs, mx,
+        hipLaunchKernelGGL(k_pcg_residual_mx, dim3(ps.grid), dim3(kBlock), 0, s, inst_map(c), rhs, mx,
                            c->d_r, c->n_free, part(c, 0), part(c, 1));
     else
         EQS_WITH_OP(c->Mdia, view(c->M),
-                    hipLaunchKernelGGL(k_pcg_residual<std::decay_t<decltype(op)>>, dim3(nb), dim3(kBlock), 0, s, op,
-                                       inst_map(c), rhs, x, c->d_r, part(c, 0), part(c, 1), (double*)nullptr,
+                    hipLaunchKernelGGL((k_pcg_residual<std::decay_t<decltype(op)>>),
+                                       dim3(ps.grid), dim3(kBlock), 0, s, op, inst_map(c), rhs, x, c->d_r,
+                                       part(c, 0), part(c, 1), (double*)nullptr,
                                        (const int32_t*)nullptr));
     hipLaunchKernelGGL(inst_map(c).rows1 >= 0 ? k_fin_start<true> : k_fin_start<false>, dim3(fin_grid(c)),
                        dim3(kFin), 0, s, c->d_scal, inst_map(c), part(c, 0), part(c, 1), rtol, maxit, flexible, 0,
@@ -2337,11 +2402,12 @@ void pcg_init(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, int
 void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const double* x, double* mx_out,
                        bool only_if_done) {
     using OpT = double;
-    const unsigned nb = row_grid(c->n_free);
+    const PartShape ps = part_shape(c);
     const int32_t* done = only_if_done ? &c->d_sum->all_done : nullptr;
     EQS_WITH_OP(c->Mdia, view(c->M),
-                hipLaunchKernelGGL(k_pcg_residual<std::decay_t<decltype(op)>>, dim3(nb), dim3(kBlock), 0, s, op,
-                                   inst_map(c), rhs, x, c->d_r, part(c, 0), part(c, 1), mx_out, done));
+                hipLaunchKernelGGL((k_pcg_residual<std::decay_t<decltype(op)>>),
+                                   dim3(ps.grid), dim3(kBlock), 0, s, op, inst_map(c), rhs, x, c->d_r, part(c, 0),
+                                   part(c, 1), mx_out, done));
     int32_t* force = c->test_reject_first ? c->d_force : (int32_t*)nullptr;
     hipLaunchKernelGGL(inst_map(c).rows1 >= 0 ? k_fin_start<true> : k_fin_start<false>, dim3(fin_grid(c)),
                        dim3(kFin), 0, s, c->d_scal, inst_map(c), part(c, 0), part(c, 1), 0.0, 0, 0, 1, c->d_sum,
@@ -2354,7 +2420,8 @@ void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const doubl
 void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int precision) {
     (void)rhs;
     using OpT = double;
-    const unsigned nbV = row_grid(c->n_free);
+    const PartShape ps = part_shape(c), ps_spmv = part_shape(c, true);
+    const bool big = ps.grid > (unsigned)pro_blocks(kProSmall);
     // With one iteration per graph the SpMV does not test the stop flag either (the V-cycle never does; see
     // vcycle): an iteration past convergence is rarely launched (the host waits once the residuals extrapolate to
     // rtol), and it writes only partials and p and q (x and r are guarded by the instance's state). With several
@@ -2365,11 +2432,11 @@ void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int 
     if (precision == EQS_PREC_FP32) vcycle<float>(s, c, c->h32, c->d_r, c->d_z, part(c, 0), part(c, 1));
     else vcycle<double>(s, c, c->h64, c->d_r, c->d_z, part(c, 0), part(c, 1));
     prof_end(c, EQS_KCLASS_VCYCLE, s);
-    const InstMap im = inst_map(c);
+    const InstMap im = inst_map(c), im_spmv = inst_map(c, true), im_upd = inst_map(c, true, true);
     const bool one = im.rows1 >= 0;
     const DotParts D{part(c, 2), part(c, 3), part(c, 4), part(c, 5)};
-    // the consumers reduce (kProBlocks); the finalisers' own time is only seen with launches of their own
-    const bool pro = nbV <= kProBlocks && !(c->prof_mask & (1u << EQS_KCLASS_FINALISE));
+    // the consumers reduce (pro_load); the finalisers' own time is only seen with launches of their own
+    const bool pro = ps.grid <= (unsigned)pro_blocks(one ? kProBig : kProSmall) && !(c->prof_mask & (1u << EQS_KCLASS_FINALISE));
     const dim3 fg(fin_grid(c));
     if (!pro)
         EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_beta<true> : k_fin_beta<false>, fg, dim3(kFin), 0, s,
@@ -2377,24 +2444,28 @@ void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int 
 #define EQS_SPMV(ONE_, PRO_) k_pcg_spmv<ONE_, PRO_, std::decay_t<decltype(op)>>
     EQS_WITH_OP(c->Mdia, view(c->M),
                 EQS_LAUNCH_TIMED(c, EQS_KCLASS_SPMV_M,
-                                 (pro ? (one ? EQS_SPMV(true, true) : EQS_SPMV(false, true))
-                                      : (one ? EQS_SPMV(true, false) : EQS_SPMV(false, false))),
-                                 dim3(nbV), dim3(kBlock), 0, s, op, im, c->d_z, c->d_r, c->d_p, c->d_q, D, c->d_scal,
+                                 (pro ? (!one  ? EQS_SPMV(false, kProSmall)
+                                         : big ? EQS_SPMV(true, kProBig)
+                                               : EQS_SPMV(true, kProSmall))
+                                      : (one ? EQS_SPMV(true, 0) : EQS_SPMV(false, 0))),
+                                 dim3(ps_spmv.grid), dim3(kBlock), 0, s, op, im_spmv, c->d_z, c->d_r, c->d_p, c->d_q, D, c->d_scal,
                                  c->d_step, part(c, 0), part(c, 1), vstop));
 #undef EQS_SPMV
     if (!pro) {
         // two of the three finalisations of an iteration (alpha, convergence): the second counts with no time of its own
         EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_step<true> : k_fin_step<false>, fg, dim3(kFin), 0, s,
-                         c->d_scal, c->d_step, im, D, c->d_sum, c->d_hsum, c->d_hscal);
+                         c->d_scal, c->d_step, im_upd, D, c->d_sum, c->d_hsum, c->d_hscal);
         prof_again(c, EQS_KCLASS_FINALISE);
         if (fg.x > 1)  // the summary of all instances (part of the finalise class's work, not timed on its own)
             hipLaunchKernelGGL(k_fin_summary, dim3(1), dim3(kFin), 0, s, c->d_scal, (int32_t)c->n_inst, c->d_sum,
                                c->d_hsum, c->d_hscal, 1, (int32_t*)nullptr);
     }
     EQS_LAUNCH_TIMED(c, EQS_KCLASS_CG_UPDATE,
-                     pro ? (one ? k_pcg_update<true, true> : k_pcg_update<false, true>)
-                         : (one ? k_pcg_update<true, false> : k_pcg_update<false, false>),
-                     dim3(nbV), dim3(kBlock), 0, s, im, x, c->d_r, c->d_p, c->d_q, c->n_free, D, c->d_scal, c->d_step,
+                     (pro ? (!one  ? k_pcg_update<false, kProSmall>
+                             : big ? k_pcg_update<true, 4>
+                                   : k_pcg_update<true, kProSmall>)
+                          : (one ? k_pcg_update<true, 0> : k_pcg_update<false, 0>)),
+                     dim3(ps_spmv.grid), dim3(kBlock), 0, s, im_upd, x, c->d_r, c->d_p, c->d_q, c->n_free, D, c->d_scal, c->d_step,
                      c->d_sum, c->d_hsum, c->M.xcd);
     if (pro && !one)
         hipLaunchKernelGGL(k_fin_summary, dim3(1), dim3(kFin), 0, s, c->d_scal, (int32_t)c->n_inst, c->d_sum,

@@ -1,6 +1,8 @@
 // SELL rows on the device: slices of one wavefront (64 lanes) each, stored
-// column-major with the slice's longest row, so lane l of a wavefront reads
-// its entry k at sptr[s] + 64 k + l (unit stride across lanes). With L lanes
+// in pairs of entries: lane l of a wavefront finds its entries 2 k and 2 k + 1 at
+// sptr[s] + 128 k + 2 l, so one load fetches two values (8 or 16 bytes a lane)
+// and one their columns; the slice is as wide as its longest row, rounded up to
+// a pair. With L lanes
 // per row a slice holds 64 / L rows: lane l serves row 64 s / L + l / L and
 // takes the row's entries l % L, l % L + L, ... (long rows of coarse AMG
 // operators then need 1/L as many sequential loads); the L partial sums are
@@ -82,51 +84,75 @@ __device__ __forceinline__ int32_t sell_perm_row(const uint8_t* __restrict__ per
     return base + (int32_t)perm[pos];
 }
 
+template <typename V>
+struct Pair {
+    V a, b;
+};
+// Pairs carry the nontemporal hint: the operator is read once per product, and
+// the caches are left to the gathered vector.
+template <typename V>
+__device__ __forceinline__ Pair<V> load_pair(const V* __restrict__ p) {
+    typedef V V2 __attribute__((ext_vector_type(2)));
+    const V2 v = __builtin_nontemporal_load(reinterpret_cast<const V2*>(p));
+    return Pair<V>{v.x, v.y};
+}
+
+// acc + the terms of N pairs at entry offset `at`: all loads, then all gathers,
+// are in flight together.
+template <int N, typename T, typename F>
+__device__ __forceinline__ T sell_pairs(const SellView<T>& A, int64_t at, int32_t base, F f, T acc) {
+    Pair<T> v[N];
+    Pair<int32_t> j[N];
+    if (A.d16) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            v[u] = load_pair(A.val + at + 128 * u);
+            const Pair<int16_t> d = load_pair(A.d16 + at + 128 * u);
+            j[u] = Pair<int32_t>{base + d.a, base + d.b};
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            v[u] = load_pair(A.val + at + 128 * u);
+            j[u] = load_pair(A.col + at + 128 * u);
+        }
+    }
+    T t[2 * N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        t[2 * u] = v[u].a * f(j[u].a);
+        t[2 * u + 1] = v[u].b * f(j[u].b);
+    }
+#pragma unroll
+    for (int u = 0; u < 2 * N; ++u) acc += t[u];
+    return acc;
+}
+
 // sum_k a_{row,k} f(col_k) over the stored entries of `row` served by global
 // thread g (rows past n_rows but inside the last slice see padding only).
-// Entries are taken in groups of U whose loads carry no branch: positions
-// past the slice's width re-read its last entry (a cache hit) and their terms
-// are dropped by a select, so all loads and gathers of a group are in flight
-// together (a row of w stored entries costs ceil(w / U) dependent rounds of
-// loads, then gathers; short rows want a small U, long ones a large U). The
-// operator's values and column data are read once per product and carry the
-// nontemporal hint, which leaves the caches to the gathered vector. Each lane
-// sums in k order; with L > 1 the lane sums are then combined by group_sum
-// (every lane of the group gets the row's sum).
+// Entries are taken in groups of U whose loads are in flight together (a row of
+// w stored entries costs about w / U dependent rounds of loads, then gathers;
+// short rows want a small U, long ones a large U); the slice's width is the same
+// for the whole wavefront, so the last, shorter group is a branch and nothing is
+// loaded twice. Each lane sums in k order; with L > 1 the lane sums are then
+// combined by group_sum (every lane of the group gets the row's sum).
 template <int L, int U = 8, typename T, typename F>
 __device__ __forceinline__ T sell_accum(const SellView<T>& A, int64_t g, int32_t row, F f) {
-    const int32_t s = (int32_t)(g >> 6), l = (int32_t)(g & 63);
+    const int32_t s = __builtin_amdgcn_readfirstlane((int32_t)(g >> 6));
     const int32_t beg = A.sptr[s];
-    const int32_t w = (A.sptr[s + 1] - beg) >> 6;  // uniform across the wavefront
-    const T* vp = A.val + beg + l;
+    int32_t w = (A.sptr[s + 1] - beg) >> 7;  // pairs
+    int64_t at = beg + 2 * (int32_t)(g & 63);
+    const int32_t base = A.d16 ? offset_base(row, A.n_rows, A.n_cols) : 0;
     T acc = T(0);
-    for (int32_t k0 = 0; k0 < w; k0 += U) {
-        T v[U];
-        int32_t j[U];
-        if (A.d16) {
-            const int16_t* dp = A.d16 + beg + l;
-            const int32_t base = offset_base(row, A.n_rows, A.n_cols);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t kk = (int64_t)min(k0 + u, w - 1) * 64;
-                v[u] = __builtin_nontemporal_load(vp + kk);
-                j[u] = base + (int32_t)__builtin_nontemporal_load(dp + kk);
-            }
-        } else {
-            const int32_t* cp = A.col + beg + l;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t kk = (int64_t)min(k0 + u, w - 1) * 64;
-                v[u] = __builtin_nontemporal_load(vp + kk);
-                j[u] = __builtin_nontemporal_load(cp + kk);
-            }
-        }
-        T t[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) t[u] = v[u] * f(j[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) acc += (k0 + u < w) ? t[u] : T(0);
+    for (; w >= U / 2; w -= U / 2, at += 64 * U) acc = sell_pairs<U / 2>(A, at, base, f, acc);
+    if (U > 8 && w >= 4) {
+        acc = sell_pairs<4>(A, at, base, f, acc);
+        w -= 4;
+        at += 512;
     }
+    if (w == 3) acc = sell_pairs<3>(A, at, base, f, acc);
+    else if (w == 2) acc = sell_pairs<2>(A, at, base, f, acc);
+    else if (w == 1) acc = sell_pairs<1>(A, at, base, f, acc);
     return group_sum<L>(acc);
 }
 

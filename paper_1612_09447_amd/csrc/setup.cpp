@@ -779,6 +779,7 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const 
     for (int32_t s = 0; s < S.n_slices; ++s) {
         int32_t w = 0;  // entries per lane
         for (int32_t k = s * rows_per; k < (s + 1) * rows_per; ++k) w = std::max(w, (len(pos2row[k]) + lanes - 1) / lanes);
+        w = (w + 1) & ~1;  // whole pairs
         int64_t next = (int64_t)sptr[s] + (int64_t)w * kSlice;
         if (next > INT32_MAX) fail(EQS_ERR_INVALID_ARG, "matrix too large for SELL offsets");
         sptr[s + 1] = (int32_t)next;
@@ -796,7 +797,7 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const 
             const int32_t n = len(r);
             if (n > 0) pad_col = A.col[A.ptr[r] + n - 1];
             for (int32_t k = 0; k < w; ++k) {
-                const int64_t at = sptr[s] + (int64_t)k * kSlice + l;
+                const int64_t at = sptr[s] + (int64_t)(k >> 1) * 2 * kSlice + 2 * l + (k & 1);
                 const int32_t e = k * lanes + part;
                 if (e < n) {
                     col[at] = A.col[A.ptr[r] + e];
@@ -819,7 +820,7 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const 
                 const int32_t r = pos2row[(size_t)(s * rows_per + l / lanes)];
                 const int64_t base = offset_base(r, A.n_rows, A.n_cols);
                 for (int32_t k = 0; k < w; ++k) {
-                    const int64_t at = sptr[s] + (int64_t)k * kSlice + l;
+                    const int64_t at = sptr[s] + (int64_t)(k >> 1) * 2 * kSlice + 2 * l + (k & 1);
                     const int64_t d = (r < A.n_rows ? (int64_t)col[at] : (int64_t)A.n_cols - 1) - base;
                     if (d < -32767 || d > 32767) {
                         fits = false;
@@ -1371,10 +1372,10 @@ static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
         if (l == 0) {
             if constexpr (std::is_same_v<T, double>) lv.D = c->Mdia;  // A_0 is M
             else lv.D = to_dia<T>(c, ah.A[0]);
+            std::vector<T> w(lv.n);
+            for (int32_t i = 0; i < lv.n; ++i) w[i] = (T)(lv.omega / d[0][i]);
+            lv.w = upload_vec(c, w);
             if (lv.D.K) {
-                std::vector<T> w(lv.n);
-                for (int32_t i = 0; i < lv.n; ++i) w[i] = (T)(lv.omega / d[0][i]);
-                lv.w = upload_vec(c, w);
                 c->tune_log += "A0: " + std::to_string(lv.D.K) + " upper diagonals (finest level)\n";
             } else {
                 Csr<double> As = ah.A[0];  // A w D^-1
@@ -1382,9 +1383,6 @@ static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
                 lv.A = tuned_spmat<T>(c, As, "A0", true);
                 lv.sval = lv.A.sell.val;
             }
-            std::vector<T> dinv(lv.n);
-            for (int32_t i = 0; i < lv.n; ++i) dinv[i] = (T)(1.0 / d[0][i]);
-            lv.dinv = upload_vec(c, dinv);
             if (!h.direct) {
                 lv.x = (T*)dev_alloc(c, sizeof(T) * lv.n);
                 lv.res = (T*)dev_alloc(c, sizeof(T) * lv.n);
