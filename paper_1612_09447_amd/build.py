@@ -26,7 +26,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ROCM_LIB = "/opt/rocm/lib"  # roctx ranges (rocprofiler-sdk-roctx)
 ARCH = "gfx950"
 
-SOURCES = ["api.cpp", "setup.cpp", "solver.cpp", "profile.cpp", "kernels.hip", "mlp.hip", "guess.hip", "batch.cpp"]
+SOURCES = ["api.cpp", "setup.cpp", "solver.cpp", "profile.cpp", "kernels.hip", "small.hip", "mlp.hip", "guess.hip", "batch.cpp"]
 
 COMMON = [
     "-O3",

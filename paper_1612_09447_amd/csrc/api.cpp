@@ -98,6 +98,8 @@ int eqs_create(eqs_ctx** out, int device, void* hip_stream) {
         c->index16 = !(i16 && i16[0] == '0');
         const char* tv = std::getenv("EQS_TUNE_LOG");  // "all": list every layout candidate's time
         c->tune_verbose = tv && std::string(tv) == "all";
+        const char* sm = std::getenv("EQS_SMALL");  // "0": small systems solve by launches like large ones
+        c->small = !(sm && sm[0] == '0');
         const char* dg = std::getenv("EQS_DIAGONALS");  // "0": no matrix is stored by diagonals
         c->diagonals = !(dg && dg[0] == '0');
         const char* fo = std::getenv("EQS_FOLD");  // "0": the plain V-cycle (no folded operators)

@@ -200,6 +200,7 @@ struct Hierarchy {
     std::vector<Level<T>> lv;
     bool folded = false;  // the folded cycle; levels past `bottom` have no device data then
     int bottom = 0;       // the level solved by its dense operator
+    bool small = false;   // folded: solves run in one launch (small.hip)
     bool direct = false;  // folded: the finest restriction acts on r itself (no pre-smoothing kernel)
 };
 
@@ -356,6 +357,7 @@ struct eqs_ctx {
     std::map<int64_t, int64_t> ws_free;  // free ranges of the workspace: offset -> length
     bool index16 = true;   // 16-bit column offsets for SELL operators whose entries allow them
     bool autotune = true;  // time the candidate layouts of every AMG operator at build time
+    bool small = true;      // small systems solve in one launch
     bool diagonals = true;  // matrices of few diagonals are stored by them
     bool fold = true;       // fold pre-smoothers into restrictions and the lowest two levels into two products
     int force_layout = -1;      // >= 1: SELL with that many lanes per row, 0: CSR, for every coarse operator
@@ -477,6 +479,16 @@ void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const doubl
 template <typename T>
 void vcycle(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* r, double* z, double* part_rz,
             double* part_rzold);
+
+// whole solves of small single systems in one launch (small.hip): whether a
+// folded hierarchy with its bottom at level 1 qualifies (rows and nonzeros of
+// M, unknowns of level 1, nonzeros of Q_0), and the solve, whose outcome is in
+// the pinned scalars and summary once the stream is idle. Its iterations are
+// bounded by kSmallMaxit per launch (longer budgets take the launches).
+constexpr int64_t kSmallBytes = 1 << 20;
+constexpr int32_t kSmallMaxit = 20000;
+bool small_solve_fits(const eqs_ctx* c, int64_t n, int64_t nnz, int64_t n1, int64_t nnz_q);
+void small_solve(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int32_t maxit, double rtol, double* mx_out);
 
 // start-vector network (mlp.hip)
 }  // namespace eqs

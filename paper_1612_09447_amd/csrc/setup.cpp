@@ -1188,6 +1188,19 @@ static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, 
     return best;
 }
 
+// A in CSR with L lanes per row.
+template <typename T>
+static SpMat<T> csr_spmat(eqs_ctx* c, const Csr<double>& A, int L) {
+    SpMat<T> S;
+    S.n_rows = A.n_rows; S.n_cols = A.n_cols; S.nnz = A.nnz();
+    S.fmt = FMT_CSR;
+    S.lanes = L;
+    S.rowptr = upload_vec(c, A.ptr);
+    upload_csr_cols(c, S, A);
+    S.val = upload_vec(c, std::vector<T>(A.val.begin(), A.val.end()));
+    return S;
+}
+
 // Values a_ij omega / a_jj of A omega D^{-1} in the storage order of the
 // uploaded layout S of A (same structure, so the same positions).
 template <typename T>
@@ -1334,7 +1347,8 @@ static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
         B.swap(Bl);
     }
     const int64_t nt = ah.A[t].n_rows, na = ah.A[t - 1].n_rows;
-    const bool merged = nt * na <= kMaxCoarseR;  // B_t times the restriction above it as one dense matrix
+    h.small = h.direct && t == 1 && c->n_inst == 1 && small_solve_fits(c, na, ah.A[0].nnz(), nt, Q[0].nnz());
+    const bool merged = !h.small && nt * na <= kMaxCoarseR;  // B_t times the restriction above it as one dense matrix
     Level<T>& bot = h.lv[t];
     if (merged) {
         const Csr<double>& up = (t > 1 || h.direct) ? Q[0 + (t - 1)] : ah.P[0];  // its transpose restricts
@@ -1411,7 +1425,10 @@ static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
             lv.GQ = tuned_spmat<T>(c, GQ, ("[G Q]" + id).c_str(), false, true);
         }
         if (l == t - 1 && merged) continue;
-        if (l > 0 || h.direct)
+        if (h.small) {
+            lv.R = csr_spmat<T>(c, transpose(Q[l]), 16);
+            c->tune_log += "R0(I-AwD^-1): csr16 (small system: solves in one launch)\n";
+        } else if (l > 0 || h.direct)
             lv.R = tuned_spmat<T>(c, transpose(Q[l]), ("R" + id + "(I-AwD^-1)").c_str(), false, true);
         else
             lv.R = tuned_spmat<T>(c, ah.R[l], ("R" + id).c_str(), false, true);

@@ -40,6 +40,15 @@ static void check_launch() {
     if (e != hipSuccess) fail(EQS_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
 }
 
+// kernel classes inside a CG iteration
+constexpr uint32_t kIterClasses =
+    (1u << EQS_KCLASS_SPMV_M) | (1u << EQS_KCLASS_PRESMOOTH0) | (1u << EQS_KCLASS_POSTSMOOTH0) |
+    (1u << EQS_KCLASS_VCYCLE) | (1u << EQS_KCLASS_CG_UPDATE) | (1u << EQS_KCLASS_RESTRICT0) |
+    (1u << EQS_KCLASS_PROLONG0) | (1u << EQS_KCLASS_VCOARSE) | (1u << EQS_KCLASS_POSTSMOOTH1) |
+    (1u << EQS_KCLASS_FINALISE);
+
+static int finish_solve(eqs_ctx* c, eqs_solve_stats* st);
+
 // The kernels of one CG iteration take every scalar from device memory, so a
 // single captured graph replays any iteration of any solve into the same x.
 // One graph holds c->graph_iters iterations (a launch runs that many; those
@@ -47,14 +56,8 @@ static void check_launch() {
 // and while kernels of the iteration are being timed individually (then the
 // iterations are launched one by one).
 static void run_iteration(eqs_ctx* c, double* x, int prec) {
-    const uint32_t iter_classes = (1u << EQS_KCLASS_SPMV_M) | (1u << EQS_KCLASS_PRESMOOTH0) |
-                                  (1u << EQS_KCLASS_POSTSMOOTH0) | (1u << EQS_KCLASS_VCYCLE) |
-                                  (1u << EQS_KCLASS_CG_UPDATE) | (1u << EQS_KCLASS_RESTRICT0) |
-                                  (1u << EQS_KCLASS_PROLONG0) | (1u << EQS_KCLASS_VCOARSE) |
-                                  (1u << EQS_KCLASS_POSTSMOOTH1) |
-                                  (1u << EQS_KCLASS_FINALISE);
     const int G = c->graph_iters;
-    if (!c->use_graphs || c->stream == nullptr || (c->prof_mask & iter_classes)) {
+    if (!c->use_graphs || c->stream == nullptr || (c->prof_mask & kIterClasses)) {
         for (int k = 0; k < G; ++k) pcg_iteration(c->stream, c, nullptr, x, prec);
         return;
     }
@@ -95,12 +98,26 @@ int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit
     const Range range("eqs: CG solve of M");
     hipStream_t s = c->stream;
     const int prec = c->amg.precision;
+    const bool small = (prec == EQS_PREC_FP32 ? c->h32.small : c->h64.small) && maxit <= kSmallMaxit &&
+                       !(c->prof_mask & kIterClasses);
+    if (small) {
+        small_solve(s, c, rhs, y, maxit, rtol, mx_out);
+        check_launch();
+        if (before_sync) {
+            EQS_HIP(hipEventRecord(c->ev[0], s));
+            (*before_sync)();
+            check_launch();
+            EQS_HIP(hipEventSynchronize(c->ev[0]));
+        } else {
+            EQS_HIP(hipStreamSynchronize(s));
+        }
+        return finish_solve(c, st);
+    }
     pcg_init(s, c, rhs, y, maxit, rtol, c->amg.flexible, mx_in);
     check_launch();
     // Iterations are enqueued without waiting for the start's result: an
     // instance that is already done leaves its rows alone, and once all are
     // done an iteration changes nothing (see pcg_iteration).
-    PcgSummary v{};
     int restarts = 0;
     int32_t it_before = 0;
     for (;;) {
@@ -173,9 +190,14 @@ int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit
             check_launch();
             EQS_HIP(hipStreamSynchronize(s));
         }
-        v = read_summary(c);
-        if (v.all_done || ++restarts > 4) break;
+        if (read_summary(c).all_done || ++restarts > 4) break;
     }
+    return finish_solve(c, st);
+}
+
+// Results of a finished solve from the pinned summary and scalars.
+static int finish_solve(eqs_ctx* c, eqs_solve_stats* st) {
+    const PcgSummary v = read_summary(c);
     int status = EQS_OK;
     if (v.n_notconv > 0 || !v.all_done) status = EQS_ERR_NOT_CONVERGED;
     if (v.n_breakdown > 0) status = EQS_ERR_BREAKDOWN;
