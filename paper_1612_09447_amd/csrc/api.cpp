@@ -98,6 +98,8 @@ int eqs_create(eqs_ctx** out, int device, void* hip_stream) {
         c->index16 = !(i16 && i16[0] == '0');
         const char* tv = std::getenv("EQS_TUNE_LOG");  // "all": list every layout candidate's time
         c->tune_verbose = tv && std::string(tv) == "all";
+        const char* fn = std::getenv("EQS_FANS");  // "0": the element pass takes single tets
+        c->fan_pass = !(fn && fn[0] == '0');
         const char* sm = std::getenv("EQS_SMALL");  // "0": small systems solve by launches like large ones
         c->small = !(sm && sm[0] == '0');
         const char* dg = std::getenv("EQS_DIAGONALS");  // "0": no matrix is stored by diagonals
@@ -738,8 +740,9 @@ int eqs_describe(const eqs_ctx* c, char* buf, int64_t cap, int64_t* needed) {
                       c->amg.precision == EQS_PREC_FP32 ? "fp32" : "fp64", (int)c->built);
         d += line;
         std::snprintf(line, sizeof line,
-                      "element blocks %lld of %d tets, block nodes %lld (max %d), graphs %d, autotune %d%s\n",
-                      (long long)c->n_blocks, eqs::kTetBlock * c->tet_tpt, (long long)c->n_block_nodes,
+                      "element blocks %lld of %s%d tets, block nodes %lld (max %d), graphs %d, autotune %d%s\n",
+                      (long long)c->n_blocks, c->fans ? "up to " : "",
+                      eqs::kTetBlock * (c->fans ? eqs::kFanTets : c->tet_tpt), (long long)c->n_block_nodes,
                       c->max_block_nodes, (int)c->use_graphs, (int)c->autotune,
                       c->kx_generic ? ", per-block LDS stride" : c->deterministic ? ", deterministic sums" : "");
         d += line;

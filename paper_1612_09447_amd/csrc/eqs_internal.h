@@ -33,6 +33,7 @@ namespace eqs {
 constexpr int kSlice = 64;   // SELL slice height = wavefront size
 constexpr int kTetBlock = 256;  // threads per element-pass workgroup
 constexpr int kMaxTetsPerThread = 8;  // element blocks hold kTetBlock * tpt tets, tpt in {1, 2, 4, 8}
+constexpr int kFanTets = 6;  // tets of a fan at most (k_kx_fan)
 constexpr int kMaxBlockNodes = 1360;  // distinct nodes per element block: 48 B of LDS each (<= 64 KiB)
 constexpr int64_t kMaxCoarseR = 4 << 20;  // entries of the fused restriction + bottom solve matrix
 constexpr int32_t kMaxBottom = 1024;      // unknowns of a dense bottom level above the coarsest
@@ -289,6 +290,7 @@ struct eqs_ctx {
     int64_t n_blocks = 0;
     int32_t max_block_nodes = 0;
     int32_t tet_tpt = 0;        // tets per thread of the element pass
+    bool fans = false;          // d_tpack holds fans (two words each, kTetBlock per block) instead of tets
     // deterministic element pass (eqs_set_deterministic; see k_kx_det): per
     // block the slots of every node in slot order, the end of every block
     // node's list, every node's block-node positions in block order, and the
@@ -357,6 +359,7 @@ struct eqs_ctx {
     std::map<int64_t, int64_t> ws_free;  // free ranges of the workspace: offset -> length
     bool index16 = true;   // 16-bit column offsets for SELL operators whose entries allow them
     bool autotune = true;  // time the candidate layouts of every AMG operator at build time
+    bool fan_pass = true;   // the element pass may walk fans of tets
     bool small = true;      // small systems solve in one launch
     bool diagonals = true;  // matrices of few diagonals are stored by them
     bool fold = true;       // fold pre-smoothers into restrictions and the lowest two levels into two products

@@ -423,29 +423,61 @@ __device__ __forceinline__ int32_t kx_stride(int32_t nn) {
     return STRIDE > 0 ? STRIDE : nn;
 }
 
+// Nodes of a block held by a thread: rounds of kTetBlock. Blocks of a fixed
+// stride are covered by them; past them (STRIDE = 0) nodes are taken one by one.
+template <int STRIDE>
+constexpr int kKxRounds = STRIDE > 0 ? (STRIDE - 1 + kTetBlock - 1) / kTetBlock : 2;
+
 template <bool RHS, int STRIDE>
-__device__ __forceinline__ bool kx_stage(const KxArgs& A, double* lds, int32_t off, int32_t nn) {
-    const int32_t S = kx_stride<STRIDE>(nn);
-    for (int k = threadIdx.x; k < nn; k += kTetBlock) {
-        const int32_t id = A.bnodes[off + k];
-        double u, rate = 0.0;
-        if (id < A.n_free) {
-            u = A.yfree[id];
-        } else {
-            const DriveDev d = A.drives[A.ddrive[id - A.n_free]];
-            const double ph = d.w * A.t + d.phase;
-            u = d.amp * sin(ph);
-            rate = d.w * d.amp * cos(ph);
-        }
-        double* q = lds + k;
-        q[0] = A.X[id];
-        q[S] = A.Y[id];
-        q[2 * S] = A.Z[id];
-        q[3 * S] = u;
-        q[4 * S] = rate;
-        q[5 * S] = 0.0;
+__device__ __forceinline__ void kx_put(const KxArgs& A, double* lds, int32_t S, int k, int32_t id, double x, double y,
+                                       double z, double u) {
+    double rate = 0.0;
+    if (id >= A.n_free) {
+        const DriveDev d = A.drives[A.ddrive[id - A.n_free]];
+        const double ph = d.w * A.t + d.phase;
+        u = d.amp * sin(ph);
+        rate = d.w * d.amp * cos(ph);
     }
-    return RHS && nn > 0 && A.bnodes[off + nn - 1] >= A.n_free;
+    double* q = lds + k;
+    q[0] = x;
+    q[S] = y;
+    q[2 * S] = z;
+    q[3 * S] = u;
+    q[4 * S] = rate;
+    q[5 * S] = 0.0;
+}
+
+// Stages the block's nodes; ids: the thread's (see kx_scatter). The loads of all
+// rounds are issued together: a block's time is mostly the latency of ids, then
+// node data, then the scatter, each once instead of once per round.
+template <bool RHS, int STRIDE>
+__device__ __forceinline__ bool kx_stage(const KxArgs& A, double* lds, int32_t off, int32_t nn,
+                                         int32_t (&ids)[kKxRounds<STRIDE>]) {
+    constexpr int NR = kKxRounds<STRIDE>;
+    const int32_t S = kx_stride<STRIDE>(nn);
+    const int32_t last = A.bnodes[off + nn - 1];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) ids[q] = A.bnodes[off + min((int32_t)threadIdx.x + q * kTetBlock, nn - 1)];
+    double x[NR], y[NR], z[NR], u[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const int32_t id = ids[q];
+        x[q] = A.X[id];
+        y[q] = A.Y[id];
+        z[q] = A.Z[id];
+        u[q] = *(id < A.n_free ? A.yfree + id : A.X + id);  // Dirichlet nodes: any address that is there
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const int k = (int)threadIdx.x + q * kTetBlock;
+        if (k < nn) kx_put<RHS, STRIDE>(A, lds, S, k, ids[q], x[q], y[q], z[q], u[q]);
+    }
+    if (STRIDE == 0)
+        for (int k = (int)threadIdx.x + NR * kTetBlock; k < nn; k += kTetBlock) {
+            const int32_t id = A.bnodes[off + k];
+            kx_put<RHS, STRIDE>(A, lds, S, k, id, A.X[id], A.Y[id], A.Z[id], id < A.n_free ? A.yfree[id] : 0.0);
+        }
+    return RHS && last >= A.n_free;
 }
 
 // The thread's TPT consecutive tets of block b: records with 16-byte loads
@@ -465,84 +497,88 @@ __device__ __forceinline__ void kx_records(const KxArgs& A, int64_t b, uint64_t 
     }
 }
 
-// Element matrices of the thread's tets times the staged potentials, added
-// into the LDS accumulator (see the kernel comment for the algebra). With
-// contrib (the deterministic pass) the four values of the thread's tet i go
-// to contrib[4 (threadIdx.x TPT + i) + a] instead, each written once.
-template <bool RHS, int TPT, int STRIDE>
-__device__ __forceinline__ void kx_tets(const KxArgs& A, double* lds, int32_t nn, bool has_dir,
-                                        const uint64_t (&rec)[TPT], double* contrib = nullptr) {
+// Element matrix of one tet (block-local vertices l) times the staged potentials
+// (see the kernel comment for the algebra).
+template <bool RHS, int STRIDE>
+__device__ __forceinline__ void kx_one(const KxArgs& A, const double* lds, int32_t nn, bool has_dir,
+                                       const MatDev* __restrict__ mp, const int (&l)[4], double (&y)[4]) {
     const int32_t S = kx_stride<STRIDE>(nn);
     const double* PX = lds;
     const double* PY = PX + S;
     const double* PZ = PY + S;
     const double* PU = PZ + S;
     const double* R = PU + S;
-    double* Acc = lds + 5 * S;
+    const MatDev m = *mp;
+    const double4 p0 = make_double4(PX[l[0]], PY[l[0]], PZ[l[0]], PU[l[0]]);
+    const double4 p1 = make_double4(PX[l[1]], PY[l[1]], PZ[l[1]], PU[l[1]]);
+    const double4 p2 = make_double4(PX[l[2]], PY[l[2]], PZ[l[2]], PU[l[2]]);
+    const double4 p3 = make_double4(PX[l[3]], PY[l[3]], PZ[l[3]], PU[l[3]]);
+    const double e1x = p1.x - p0.x, e1y = p1.y - p0.y, e1z = p1.z - p0.z;
+    const double e2x = p2.x - p0.x, e2y = p2.y - p0.y, e2z = p2.z - p0.z;
+    const double e3x = p3.x - p0.x, e3y = p3.y - p0.y, e3z = p3.z - p0.z;
+    const double c1x = e2y * e3z - e2z * e3y, c1y = e2z * e3x - e2x * e3z, c1z = e2x * e3y - e2y * e3x;
+    const double c2x = e3y * e1z - e3z * e1y, c2y = e3z * e1x - e3x * e1z, c2z = e3x * e1y - e3y * e1x;
+    const double c3x = e1y * e2z - e1z * e2y, c3y = e1z * e2x - e1x * e2z, c3z = e1x * e2y - e1y * e2x;
+    const double det = e1x * c1x + e1y * c1y + e1z * c1z;
+    const double inv = 1.0 / fabs(det);  // the one division per tet
+
+    const double d1 = p1.w - p0.w, d2 = p2.w - p0.w, d3 = p3.w - p0.w;
+    double wx = c1x * d1 + c2x * d2 + c3x * d3;
+    double wy = c1y * d1 + c2y * d2 + c3y * d3;
+    double wz = c1z * d1 + c2z * d2 + c3z * d3;
+
+    // (A_e u)_a = c_a . w / (6 |det|): the factor sc goes into w
+    const double sc = (RHS ? -1.0 / 6.0 : 1.0 / 6.0) * inv;
+    double ks = m.kappa0 * sc;
+    if (m.nonlinear) {
+        const double ratio = sqrt(wx * wx + wy * wy + wz * wz) * inv * m.inv_es;
+        // r^alpha as exp(alpha ln r): relative error ~ ulp(alpha ln r), about
+        // 1e-14 for the exponents and fields here (r = 0 gives 0)
+        const double pw = (m.ialpha >= 0) ? ipow(ratio, m.ialpha) : exp(m.alpha * log(ratio));
+        ks *= 1.0 + pw;
+    }
+    wx *= ks;
+    wy *= ks;
+    wz *= ks;
+    if (RHS && has_dir) {
+        const double r0 = R[l[0]], r1 = R[l[1]], r2 = R[l[2]], r3 = R[l[3]];
+        if (r0 != 0.0 || r1 != 0.0 || r2 != 0.0 || r3 != 0.0) {
+            const double q1 = r1 - r0, q2 = r2 - r0, q3 = r3 - r0;
+            const double es = m.eps * sc;
+            wx += es * (c1x * q1 + c2x * q2 + c3x * q3);
+            wy += es * (c1y * q1 + c2y * q2 + c3y * q3);
+            wz += es * (c1z * q1 + c2z * q2 + c3z * q3);
+        }
+    }
+    y[1] = c1x * wx + c1y * wy + c1z * wz;
+    y[2] = c2x * wx + c2y * wy + c2z * wz;
+    y[3] = c3x * wx + c3y * wy + c3z * wz;
+    y[0] = -(y[1] + y[2] + y[3]);
+}
+
+// The thread's tets, added into the LDS accumulator. With
+// contrib (the deterministic pass) the four values of the thread's tet i go
+// to contrib[4 (threadIdx.x TPT + i) + a] instead, each written once.
+template <bool RHS, int TPT, int STRIDE>
+__device__ __forceinline__ void kx_tets(const KxArgs& A, double* lds, int32_t nn, bool has_dir,
+                                        const uint64_t (&rec)[TPT], double* contrib = nullptr) {
+    double* Acc = lds + 5 * kx_stride<STRIDE>(nn);
 #pragma unroll
     for (int i = 0; i < TPT; ++i) {
         const uint64_t w = rec[i];
         if (w == ~0ull) continue;
-        const MatDev m = A.mats[(uint32_t)(w & 0xffffu)];
         int l[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) l[a] = (int)((w >> (16 + 12 * a)) & 0xfffu);
-        const double4 p0 = make_double4(PX[l[0]], PY[l[0]], PZ[l[0]], PU[l[0]]);
-        const double4 p1 = make_double4(PX[l[1]], PY[l[1]], PZ[l[1]], PU[l[1]]);
-        const double4 p2 = make_double4(PX[l[2]], PY[l[2]], PZ[l[2]], PU[l[2]]);
-        const double4 p3 = make_double4(PX[l[3]], PY[l[3]], PZ[l[3]], PU[l[3]]);
-        const double e1x = p1.x - p0.x, e1y = p1.y - p0.y, e1z = p1.z - p0.z;
-        const double e2x = p2.x - p0.x, e2y = p2.y - p0.y, e2z = p2.z - p0.z;
-        const double e3x = p3.x - p0.x, e3y = p3.y - p0.y, e3z = p3.z - p0.z;
-        const double c1x = e2y * e3z - e2z * e3y, c1y = e2z * e3x - e2x * e3z, c1z = e2x * e3y - e2y * e3x;
-        const double c2x = e3y * e1z - e3z * e1y, c2y = e3z * e1x - e3x * e1z, c2z = e3x * e1y - e3y * e1x;
-        const double c3x = e1y * e2z - e1z * e2y, c3y = e1z * e2x - e1x * e2z, c3z = e1x * e2y - e1y * e2x;
-        const double det = e1x * c1x + e1y * c1y + e1z * c1z;
-        const double inv = 1.0 / fabs(det);  // the one division per tet
-
-        const double d1 = p1.w - p0.w, d2 = p2.w - p0.w, d3 = p3.w - p0.w;
-        double wx = c1x * d1 + c2x * d2 + c3x * d3;
-        double wy = c1y * d1 + c2y * d2 + c3y * d3;
-        double wz = c1z * d1 + c2z * d2 + c3z * d3;
-
-        // (A_e u)_a = c_a . w / (6 |det|): the factor sc goes into w
-        const double sc = (RHS ? -1.0 / 6.0 : 1.0 / 6.0) * inv;
-        double ks = m.kappa0 * sc;
-        if (m.nonlinear) {
-            const double ratio = sqrt(wx * wx + wy * wy + wz * wz) * inv * m.inv_es;
-            // r^alpha as exp(alpha ln r): relative error ~ ulp(alpha ln r), about
-            // 1e-14 for the exponents and fields here (r = 0 gives 0)
-            const double pw = (m.ialpha >= 0) ? ipow(ratio, m.ialpha) : exp(m.alpha * log(ratio));
-            ks *= 1.0 + pw;
-        }
-        wx *= ks;
-        wy *= ks;
-        wz *= ks;
-        if (RHS && has_dir) {
-            const double r0 = R[l[0]], r1 = R[l[1]], r2 = R[l[2]], r3 = R[l[3]];
-            if (r0 != 0.0 || r1 != 0.0 || r2 != 0.0 || r3 != 0.0) {
-                const double q1 = r1 - r0, q2 = r2 - r0, q3 = r3 - r0;
-                const double es = m.eps * sc;
-                wx += es * (c1x * q1 + c2x * q2 + c3x * q3);
-                wy += es * (c1y * q1 + c2y * q2 + c3y * q3);
-                wz += es * (c1z * q1 + c2z * q2 + c3z * q3);
-            }
-        }
-        const double y1 = c1x * wx + c1y * wy + c1z * wz;
-        const double y2 = c2x * wx + c2y * wy + c2z * wz;
-        const double y3 = c3x * wx + c3y * wy + c3z * wz;
-        const double y0 = -(y1 + y2 + y3);
+        double y[4];
+        kx_one<RHS, STRIDE>(A, lds, nn, has_dir, A.mats + (uint32_t)(w & 0xffffu), l, y);
         if (contrib) {
             double* q = contrib + 4 * ((int64_t)threadIdx.x * TPT + i);
-            q[0] = y0;
-            q[1] = y1;
-            q[2] = y2;
-            q[3] = y3;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) q[a] = y[a];
         } else {
-            unsafeAtomicAdd(&Acc[l[0]], y0);
-            unsafeAtomicAdd(&Acc[l[1]], y1);
-            unsafeAtomicAdd(&Acc[l[2]], y2);
-            unsafeAtomicAdd(&Acc[l[3]], y3);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) unsafeAtomicAdd(&Acc[l[a]], y[a]);
         }
     }
 }
@@ -550,13 +586,21 @@ __device__ __forceinline__ void kx_tets(const KxArgs& A, double* lds, int32_t nn
 // One global atomic per block node (RHS mode: free nodes only; the element
 // signs already give -K(x)x + b).
 template <bool RHS, int STRIDE>
-__device__ __forceinline__ void kx_scatter(const KxArgs& A, const double* lds, int32_t off, int32_t nn) {
+__device__ __forceinline__ void kx_scatter(const KxArgs& A, const double* lds, int32_t off, int32_t nn,
+                                           const int32_t (&ids)[kKxRounds<STRIDE>]) {
+    constexpr int NR = kKxRounds<STRIDE>;
     const double* Acc = lds + 5 * kx_stride<STRIDE>(nn);
-    for (int k = threadIdx.x; k < nn; k += kTetBlock) {
-        const int32_t id = A.bnodes[off + k];
-        if (RHS && id >= A.n_free) continue;
-        unsafeAtomicAdd(&A.out[id], Acc[k]);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const int k = (int)threadIdx.x + q * kTetBlock;
+        if (k < nn && !(RHS && ids[q] >= A.n_free)) unsafeAtomicAdd(&A.out[ids[q]], Acc[k]);
     }
+    if (STRIDE == 0)
+        for (int k = (int)threadIdx.x + NR * kTetBlock; k < nn; k += kTetBlock) {
+            const int32_t id = A.bnodes[off + k];
+            if (RHS && id >= A.n_free) continue;
+            unsafeAtomicAdd(&A.out[id], Acc[k]);
+        }
 }
 
 // One element block per workgroup (blocks in XCD-contiguous order).
@@ -568,11 +612,129 @@ __global__ __launch_bounds__(kTetBlock, 6) void k_kx(KxArgs A) {
     kx_records<TPT>(A, b, rec);  // issued first: its latency overlaps the staging
     const int32_t off = A.boff[b];
     const int32_t nn = A.boff[b + 1] - off;
-    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn);
+    int32_t ids[kKxRounds<STRIDE>];
+    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn, ids);
     __syncthreads();
     kx_tets<RHS, TPT, STRIDE>(A, lds, nn, has_dir, rec);
     __syncthreads();
-    kx_scatter<RHS, STRIDE>(A, lds, off, nn);
+    kx_scatter<RHS, STRIDE>(A, lds, off, nn, ids);
+}
+
+// Fans: the element pass over chains of up to kFanTets tets (a, b, r_k, r_k+1)
+// around an edge (a, b), one fan per thread (two 64-bit words: material, a, b,
+// r_0, r_1 | r_2 .. r_6, count). With e_k = r_k - a, f = b - a and X_k = f x e_k a
+// tet's cofactors are
+//   c_b = e_k x e_k+1,  c_(r_k) = -X_k+1,  c_(r_k+1) = X_k,
+// so every further tet of the fan brings one new node: a closed ring of six reads
+// 9 nodes and adds to 9 accumulators where six single tets read and add 24, and
+// needs two cross products a tet instead of three; its record is 16 bytes instead
+// of 48. The single-tet form is bound by those LDS gathers and atomics (half of
+// its time) and by the records (100 of its 200 MB at 12.6M tets). There the fan
+// pass takes 75 us instead of 87, and 68 when every exponent is a whole number;
+// what is left is the latency of staging and scatter at 5 blocks per CU and
+// exp(alpha ln r) in the blocks that need it.
+template <bool RHS, int STRIDE>
+__device__ __forceinline__ void kx_fan(const KxArgs& A, double* lds, int32_t nn, bool has_dir, uint64_t lo, uint64_t hi) {
+    const int32_t S = kx_stride<STRIDE>(nn);
+    const double* PX = lds;
+    const double* PY = PX + S;
+    const double* PZ = PY + S;
+    const double* PU = PZ + S;
+    const double* R = PU + S;
+    double* Acc = lds + 5 * S;
+    const int count = (int)(hi >> 60);
+    if (count == 0) return;
+    const MatDev* __restrict__ mp = A.mats + (uint32_t)(lo & 0xffffu);
+    const int ia = (int)((lo >> 16) & 0xfffu), ib = (int)((lo >> 28) & 0xfffu);
+    int ir = (int)((lo >> 40) & 0xfffu), in = (int)((lo >> 52) & 0xfffu);
+    if (mp->nonlinear && mp->ialpha < 0) {
+        // exp(alpha ln r) would make the fan's registers spill (91 instead of 68
+        // us): such tets one by one, each with its four vertices
+#pragma unroll 1
+        for (int k = 0; k < count; ++k) {
+            const int l[4] = {ia, ib, ir, in};
+            double y[4];
+            kx_one<RHS, STRIDE>(A, lds, nn, has_dir, mp, l, y);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) unsafeAtomicAdd(&Acc[l[a]], y[a]);
+            ir = in;
+            in = (int)(hi & 0xfffu);
+            hi >>= 12;
+        }
+        return;
+    }
+    const double kappa0 = mp->kappa0, inv_es = mp->inv_es;
+    const int ialpha = mp->nonlinear ? mp->ialpha : -1;
+    const double ax = PX[ia], ay = PY[ia], az = PZ[ia], au = PU[ia];
+    const double fx = PX[ib] - ax, fy = PY[ib] - ay, fz = PZ[ib] - az, fu = PU[ib] - au;
+    double ex = PX[ir] - ax, ey = PY[ir] - ay, ez = PZ[ir] - az, eu = PU[ir] - au;
+    double Xx = fy * ez - fz * ey, Xy = fz * ex - fx * ez, Xz = fx * ey - fy * ex;
+    double sa = 0.0, sb = 0.0, sr = 0.0;  // contributions to a, b and r_k
+#pragma unroll 1
+    for (int k = 0; k < count; ++k) {
+        const double gx = PX[in] - ax, gy = PY[in] - ay, gz = PZ[in] - az, gu = PU[in] - au;
+        const double cx = ey * gz - ez * gy, cy = ez * gx - ex * gz, cz = ex * gy - ey * gx;
+        const double Yx = fy * gz - fz * gy, Yy = fz * gx - fx * gz, Yz = fx * gy - fy * gx;
+        const double inv = 1.0 / fabs(fx * cx + fy * cy + fz * cz);  // the one division per tet
+        double wx = cx * fu - Yx * eu + Xx * gu;
+        double wy = cy * fu - Yy * eu + Xy * gu;
+        double wz = cz * fu - Yz * eu + Xz * gu;
+        const double sc = (RHS ? -1.0 / 6.0 : 1.0 / 6.0) * inv;
+        double ks = kappa0 * sc;
+        if (ialpha >= 0) ks *= 1.0 + ipow(sqrt(wx * wx + wy * wy + wz * wz) * inv * inv_es, ialpha);
+        wx *= ks;
+        wy *= ks;
+        wz *= ks;
+        if (RHS && has_dir) {
+            const double r0 = R[ia], r1 = R[ib], r2 = R[ir], r3 = R[in];
+            if (r0 != 0.0 || r1 != 0.0 || r2 != 0.0 || r3 != 0.0) {
+                const double q1 = r1 - r0, q2 = r2 - r0, q3 = r3 - r0;
+                const double es = mp->eps * sc;
+                wx += es * (cx * q1 - Yx * q2 + Xx * q3);
+                wy += es * (cy * q1 - Yy * q2 + Xy * q3);
+                wz += es * (cz * q1 - Yz * q2 + Xz * q3);
+            }
+        }
+        const double yb = cx * wx + cy * wy + cz * wz;
+        const double yr = -(Yx * wx + Yy * wy + Yz * wz);
+        const double yg = Xx * wx + Xy * wy + Xz * wz;
+        sa -= yb + yr + yg;
+        sb += yb;
+        unsafeAtomicAdd(&Acc[ir], sr + yr);  // r_k's last tet
+        sr = yg;
+        ex = gx;
+        ey = gy;
+        ez = gz;
+        eu = gu;
+        Xx = Yx;
+        Xy = Yy;
+        Xz = Yz;
+        ir = in;
+        in = (int)(hi & 0xfffu);
+        hi >>= 12;
+    }
+    unsafeAtomicAdd(&Acc[ir], sr);
+    unsafeAtomicAdd(&Acc[ia], sa);
+    unsafeAtomicAdd(&Acc[ib], sb);
+}
+
+__device__ __forceinline__ ulonglong2 fan_record(const KxArgs& A, int64_t b) {
+    return reinterpret_cast<const ulonglong2*>(A.tpack)[b * kTetBlock + threadIdx.x];
+}
+
+template <bool RHS, int STRIDE>
+__global__ __launch_bounds__(kTetBlock, 5) void k_kx_fan(KxArgs A) {
+    extern __shared__ double lds[];
+    const int64_t b = xcd_block(blockIdx.x, A.n_blocks);
+    const ulonglong2 rec = fan_record(A, b);  // issued first: its latency overlaps the staging
+    const int32_t off = A.boff[b];
+    const int32_t nn = A.boff[b + 1] - off;
+    int32_t ids[kKxRounds<STRIDE>];
+    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn, ids);
+    __syncthreads();
+    kx_fan<RHS, STRIDE>(A, lds, nn, has_dir, rec.x, rec.y);
+    __syncthreads();
+    kx_scatter<RHS, STRIDE>(A, lds, off, nn, ids);
 }
 
 // Deterministic element pass (eqs_set_deterministic): the same arithmetic,
@@ -594,7 +756,8 @@ __global__ __launch_bounds__(kTetBlock) void k_kx_det(KxArgs A, const uint16_t* 
     kx_records<TPT>(A, b, rec);
     const int32_t off = A.boff[b];
     const int32_t nn = A.boff[b + 1] - off;
-    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn);
+    int32_t ids[kKxRounds<STRIDE>];
+    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn, ids);
     double* contrib = lds + 6 * kx_stride<STRIDE>(nn);
     __syncthreads();
     kx_tets<RHS, TPT, STRIDE>(A, lds, nn, has_dir, rec, contrib);
@@ -762,11 +925,12 @@ __global__ __launch_bounds__(kTetBlock) void k_kx_p2(KxArgs A) {
     }
     const int32_t off = A.boff[b];
     const int32_t nn = A.boff[b + 1] - off;
-    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn);
+    int32_t ids[kKxRounds<STRIDE>];
+    const bool has_dir = kx_stage<RHS, STRIDE>(A, lds, off, nn, ids);
     __syncthreads();
     kx_p2_tets<RHS, TPT, STRIDE>(A, lds, nn, has_dir, rec);
     __syncthreads();
-    kx_scatter<RHS, STRIDE>(A, lds, off, nn);
+    kx_scatter<RHS, STRIDE>(A, lds, off, nn, ids);
 }
 
 // Spectral bound of one element block for the adaptive stage choice: the
@@ -783,7 +947,8 @@ __global__ __launch_bounds__(kTetBlock, 6) void k_kx_rate(KxArgs A) {
     kx_records<TPT>(A, b, rec);
     const int32_t off = A.boff[b];
     const int32_t nn = A.boff[b + 1] - off;
-    kx_stage<false, STRIDE>(A, lds, off, nn);
+    int32_t ids[kKxRounds<STRIDE>];
+    kx_stage<false, STRIDE>(A, lds, off, nn, ids);
     __syncthreads();
     const int32_t S = kx_stride<STRIDE>(nn);
     const double* PX = lds;
@@ -828,11 +993,74 @@ __global__ __launch_bounds__(kTetBlock, 6) void k_kx_rate(KxArgs A) {
     }
 }
 
+// k_kx_rate over fans (see kx_fan).
+template <int STRIDE>
+__global__ __launch_bounds__(kTetBlock, 4) void k_kx_rate_fan(KxArgs A) {
+    extern __shared__ double lds[];
+    __shared__ double wmax[kTetBlock / 64];
+    const int64_t b = xcd_block(blockIdx.x, A.n_blocks);
+    const ulonglong2 rec = fan_record(A, b);
+    const int32_t off = A.boff[b];
+    const int32_t nn = A.boff[b + 1] - off;
+    int32_t ids[kKxRounds<STRIDE>];
+    kx_stage<false, STRIDE>(A, lds, off, nn, ids);
+    __syncthreads();
+    const int32_t S = kx_stride<STRIDE>(nn);
+    const double* PX = lds;
+    const double* PY = PX + S;
+    const double* PZ = PY + S;
+    const double* PU = PZ + S;
+    double best = 0.0;
+    const int count = (int)(rec.y >> 60);
+    if (count) {
+        const MatDev m = A.mats[(uint32_t)(rec.x & 0xffffu)];
+        const int ia = (int)((rec.x >> 16) & 0xfffu), ib = (int)((rec.x >> 28) & 0xfffu);
+        int ir = (int)((rec.x >> 40) & 0xfffu), in = (int)((rec.x >> 52) & 0xfffu);
+        uint64_t hi = rec.y;
+        const double ax = PX[ia], ay = PY[ia], az = PZ[ia], au = PU[ia];
+        const double fx = PX[ib] - ax, fy = PY[ib] - ay, fz = PZ[ib] - az, fu = PU[ib] - au;
+        for (int k = 0; k < count; ++k) {
+            const double ex = PX[ir] - ax, ey = PY[ir] - ay, ez = PZ[ir] - az, eu = PU[ir] - au;
+            const double gx = PX[in] - ax, gy = PY[in] - ay, gz = PZ[in] - az, gu = PU[in] - au;
+            const double cx = ey * gz - ez * gy, cy = ez * gx - ex * gz, cz = ex * gy - ey * gx;
+            const double det = fx * cx + fy * cy + fz * cz;
+            const double wx = cx * fu - (fy * gz - fz * gy) * eu + (fy * ez - fz * ey) * gu;
+            const double wy = cy * fu - (fz * gx - fx * gz) * eu + (fz * ex - fx * ez) * gu;
+            const double wz = cz * fu - (fx * gy - fy * gx) * eu + (fx * ey - fy * ex) * gu;
+            double sig = m.kappa0;
+            if (m.nonlinear) {
+                const double ratio = sqrt(wx * wx + wy * wy + wz * wz) / fabs(det) * m.inv_es;
+                const double pw = (m.ialpha >= 0) ? ipow(ratio, m.ialpha) : exp(m.alpha * log(ratio));
+                sig *= 1.0 + (m.alpha + 1.0) * pw;
+            }
+            best = fmax(best, sig / m.eps);
+            ir = in;
+            in = (int)(hi & 0xfffu);
+            hi >>= 12;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) best = fmax(best, __shfl_xor(best, o, 64));
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double v = wmax[0];
+        for (int k = 1; k < kTetBlock / 64; ++k) v = fmax(v, wmax[k]);
+        atomicMax((unsigned long long*)A.out, (unsigned long long)__double_as_longlong(v));
+    }
+}
+
 // Fixed LDS stride for blocks of kTetBlock * TPT tets: above the node count of
 // such blocks on tetrahedral meshes of Kuhn or similar quality (about 0.33
 // nodes per tet for large blocks). Blocks with more nodes take the kernel with
 // the block's own node count as stride.
-constexpr int kx_fixed_stride(int tpt) { return tpt == 1 ? 129 : tpt == 2 ? 193 : tpt == 4 ? 385 : 705; }
+constexpr int kx_fixed_stride(int tpt) { return tpt == 1 ? 193 : tpt == 2 ? 321 : tpt == 4 ? 449 : 705; }
+
+// fixed LDS strides of blocks of kTetBlock fans: 8 x 8 x 4 cubes have 405 nodes
+constexpr int kFanStride1 = 449, kFanStride2 = 577;
+static int fan_stride(const eqs_ctx* c) {
+    if (c->kx_generic) return 0;
+    return c->max_block_nodes <= kFanStride1 ? kFanStride1 : c->max_block_nodes <= kFanStride2 ? kFanStride2 : 0;
+}
 
 // fixed LDS strides of second-order blocks (256 and 512 tets)
 constexpr int kx_p2_fixed_stride(int tpt) { return tpt == 1 ? 705 : 1217; }
@@ -855,6 +1083,16 @@ static void launch_kx_t(hipStream_t s, eqs_ctx* c, const double* yfree, double t
         } else {
             fail(EQS_ERR_STATE, "second-order element blocks hold 256 or 512 tets");
         }
+        return;
+    }
+    if (c->fans) {
+        const int st = fan_stride(c);
+        const size_t ldsf = sizeof(double) * 6 * (size_t)(st ? st : c->max_block_nodes);
+        EQS_LAUNCH_TIMED(c, EQS_KCLASS_ELEMENT,
+                         (st == kFanStride1   ? k_kx_fan<RHS, kFanStride1>
+                          : st == kFanStride2 ? k_kx_fan<RHS, kFanStride2>
+                                              : k_kx_fan<RHS, 0>),
+                         g, b, ldsf, s, A);
         return;
     }
     const bool fixed = tpt >= 1 && c->max_block_nodes <= kx_fixed_stride(tpt) && !c->kx_generic;
@@ -910,6 +1148,14 @@ double max_rate(eqs_ctx* c, const double* yfree, double t) {
     const int tpt = c->tet_tpt;
     const bool fixed = tpt >= 1 && c->max_block_nodes <= kx_fixed_stride(tpt) && !c->kx_generic;
     const size_t lds = sizeof(double) * 6 * (size_t)(fixed ? kx_fixed_stride(tpt) : c->max_block_nodes);
+    if (c->fans) {
+        const int st = fan_stride(c);
+        const size_t ldsf = sizeof(double) * 6 * (size_t)(st ? st : c->max_block_nodes);
+        hipLaunchKernelGGL((st == kFanStride1   ? k_kx_rate_fan<kFanStride1>
+                            : st == kFanStride2 ? k_kx_rate_fan<kFanStride2>
+                                                : k_kx_rate_fan<0>),
+                           g, b, ldsf, s, A);
+    } else
 #define EQS_KR(TPT_)                                                                                     \
     do {                                                                                                 \
         if (fixed) hipLaunchKernelGGL((k_kx_rate<TPT_, kx_fixed_stride(TPT_)>), g, b, lds, s, A);        \

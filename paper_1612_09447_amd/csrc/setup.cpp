@@ -1552,6 +1552,145 @@ static ElementBlocks element_blocks(const eqs_ctx* c, const std::vector<int32_t>
     return eb;
 }
 
+// Fans of the element pass (k_kx_fan): tets of one material around a common edge,
+// each sharing a face with the next. Tets are grouped by their longest edge (the
+// body diagonal of every cube of a Kuhn mesh, whose six tets are one ring) within
+// windows of the Morton order, a group is walked into chains, and chains are cut
+// into fans of at most kFanTets; half as long where tets are taken one by one
+// (single[material]), so that no thread has six exp(alpha ln r) in a row. Order of
+// the fans: their first tet's.
+struct Fan {
+    int32_t first;  // position of its first tet in the Morton order
+    int32_t mat, count;
+    int32_t node[9];  // a, b, r_0 .. r_count (internal ids)
+};
+static std::vector<Fan> build_fans(const eqs_ctx* c, const std::vector<int32_t>& u2i, const std::vector<int32_t>& order,
+                                   const std::vector<char>& single) {
+    constexpr int64_t kWindow = 1 << 18;
+    static const int ev[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
+    static const int opp[6][2] = {{2, 3}, {1, 3}, {1, 2}, {0, 3}, {0, 2}, {0, 1}};
+    const int64_t T = c->n_tets;
+    std::vector<Fan> fans;
+    fans.reserve((size_t)(T / 4));
+    struct Item {
+        uint64_t edge;
+        int32_t mat, pos, r, s;
+    };
+    std::vector<Item> it;
+    std::vector<char> used;
+    for (int64_t w0 = 0; w0 < T; w0 += kWindow) {
+        const int64_t w1 = std::min<int64_t>(T, w0 + kWindow);
+        it.clear();
+        for (int64_t k = w0; k < w1; ++k) {
+            const int32_t e = order[k];
+            const int32_t* v = &c->tets[4 * (int64_t)e];
+            int32_t id[4];
+            for (int a = 0; a < 4; ++a) id[a] = u2i[v[a]];
+            int best = 0;
+            double bl = -1.0;
+            uint64_t bkey = 0;
+            for (int q = 0; q < 6; ++q) {
+                const double* p0 = &c->xyz[3 * (int64_t)v[ev[q][0]]];
+                const double* p1 = &c->xyz[3 * (int64_t)v[ev[q][1]]];
+                double l = 0.0;
+                for (int d = 0; d < 3; ++d) l += (p1[d] - p0[d]) * (p1[d] - p0[d]);
+                const uint32_t i0 = (uint32_t)id[ev[q][0]], i1 = (uint32_t)id[ev[q][1]];
+                const uint64_t key = ((uint64_t)std::min(i0, i1) << 32) | std::max(i0, i1);
+                // equal lengths (up to rounding): the smaller key, the same for every tet of the edge
+                if (l > bl * (1.0 + 1e-9) || (l >= bl * (1.0 - 1e-9) && key < bkey)) {
+                    best = q;
+                    bl = std::max(l, bl);
+                    bkey = key;
+                }
+            }
+            it.push_back(Item{bkey, c->tet_mat[e], (int32_t)k, id[opp[best][0]], id[opp[best][1]]});
+        }
+        std::sort(it.begin(), it.end(), [](const Item& x, const Item& y) {
+            if (x.edge != y.edge) return x.edge < y.edge;
+            if (x.mat != y.mat) return x.mat < y.mat;
+            return x.pos < y.pos;
+        });
+        for (size_t g0 = 0, g1; g0 < it.size(); g0 = g1) {
+            for (g1 = g0; g1 < it.size() && it[g1].edge == it[g0].edge && it[g1].mat == it[g0].mat;) ++g1;
+            used.assign(g1 - g0, 0);
+            auto other_use = [&](int32_t r, size_t me) {  // another unused tet of the group with node r
+                for (size_t k = g0; k < g1; ++k)
+                    if (k != me && !used[k - g0] && (it[k].r == r || it[k].s == r)) return (int64_t)k;
+                return (int64_t)-1;
+            };
+            for (size_t left = g1 - g0; left > 0;) {
+                // a chain's end: an unused tet with a face that no other one shares; else (a ring) any
+                size_t st = g1;
+                int32_t from = -1;
+                for (size_t k = g0; k < g1 && from < 0; ++k) {
+                    if (used[k - g0]) continue;
+                    if (st == g1) st = k;
+                    if (other_use(it[k].r, k) < 0) { st = k; from = it[k].r; }
+                    else if (other_use(it[k].s, k) < 0) { st = k; from = it[k].s; }
+                }
+                if (from < 0) from = it[st].r;
+                Fan f{};
+                f.mat = it[st].mat;
+                f.node[0] = (int32_t)(it[st].edge >> 32);
+                f.node[1] = (int32_t)(it[st].edge & 0xffffffffu);
+                f.node[2] = from;
+                f.first = it[st].pos;
+                int64_t k = (int64_t)st;
+                while (k >= 0 && f.count < (single[f.mat] ? kFanTets / 2 : kFanTets)) {
+                    used[(size_t)k - g0] = 1;
+                    --left;
+                    from = it[(size_t)k].r == from ? it[(size_t)k].s : it[(size_t)k].r;
+                    f.node[3 + f.count++] = from;
+                    f.first = std::min(f.first, it[(size_t)k].pos);
+                    k = other_use(from, (size_t)k);
+                }
+                fans.push_back(f);
+            }
+        }
+    }
+    std::stable_sort(fans.begin(), fans.end(), [](const Fan& x, const Fan& y) { return x.first < y.first; });
+    return fans;
+}
+
+// Blocks of kTetBlock fans, those taken tet by tet (single[material]) last, so that
+// few wavefronts have both kinds: words material | a | b | r_0 | r_1 and
+// r_2 .. r_6 | count (12-bit block-local ids; ids past the fan repeat its last).
+static ElementBlocks fan_blocks(std::vector<Fan>& fans, const std::vector<char>& single) {
+    const int64_t F = (int64_t)fans.size(), nb = (F + kTetBlock - 1) / kTetBlock;
+    ElementBlocks eb;
+    eb.pack.assign((size_t)(nb * kTetBlock * 2), 0);
+    eb.boff.assign(nb + 1, 0);
+    eb.bnodes.reserve((size_t)F);
+    std::vector<int32_t> ids;
+    for (int64_t b = 0; b < nb; ++b) {
+        const int64_t f0 = b * kTetBlock, f1 = std::min<int64_t>(F, f0 + kTetBlock);
+        ids.clear();
+        std::stable_partition(fans.begin() + f0, fans.begin() + f1, [&](const Fan& f) { return !single[f.mat]; });
+        for (int64_t f = f0; f < f1; ++f) ids.insert(ids.end(), fans[f].node, fans[f].node + 3 + fans[f].count);
+        std::sort(ids.begin(), ids.end());
+        ids.erase(std::unique(ids.begin(), ids.end()), ids.end());
+        if (ids.size() > (size_t)kMaxBlockNodes) {
+            eb.max_nodes = INT32_MAX;
+            return eb;
+        }
+        eb.max_nodes = std::max<int32_t>(eb.max_nodes, (int32_t)ids.size());
+        for (int64_t f = f0; f < f1; ++f) {
+            const Fan& a = fans[f];
+            uint64_t loc[9];
+            for (int k = 0; k < 9; ++k) {
+                const int32_t id = a.node[std::min(k, 2 + a.count)];
+                loc[k] = (uint64_t)(std::lower_bound(ids.begin(), ids.end(), id) - ids.begin());
+            }
+            eb.pack[2 * f] = (uint64_t)(uint16_t)a.mat | loc[0] << 16 | loc[1] << 28 | loc[2] << 40 | loc[3] << 52;
+            eb.pack[2 * f + 1] = loc[4] | loc[5] << 12 | loc[6] << 24 | loc[7] << 36 | loc[8] << 48 | (uint64_t)a.count << 60;
+        }
+        eb.bnodes.insert(eb.bnodes.end(), ids.begin(), ids.end());
+        if (eb.bnodes.size() > (size_t)INT32_MAX) fail(EQS_ERR_INVALID_ARG, "too many block nodes");
+        eb.boff[b + 1] = (int32_t)eb.bnodes.size();
+    }
+    return eb;
+}
+
 // Lists of the deterministic element pass (k_kx_det, k_kx_gather) from the
 // blocks: slot 4 t + a is vertex a of the block's record t; a node's slots and
 // a node's block occurrences are listed in increasing order (counting sorts).
@@ -1590,6 +1729,7 @@ static void install_det_lists(eqs_ctx* c, const ElementBlocks& eb, int tpt) {
     c->d_kx_part = (double*)dev_alloc(c, sizeof(double) * (size_t)std::max<int64_t>(NB, 1));
 }
 
+// tpt 0: eb holds fans
 static void install_blocks(eqs_ctx* c, const ElementBlocks& eb, int tpt) {
     if (c->d_tpack) { dev_free(c, c->d_tpack); dev_free(c, c->d_bnodes); dev_free(c, c->d_boff); }
     if (c->d_kslots) {
@@ -1601,6 +1741,7 @@ static void install_blocks(eqs_ctx* c, const ElementBlocks& eb, int tpt) {
     c->max_block_nodes = eb.max_nodes;
     c->n_block_nodes = (int64_t)eb.bnodes.size();
     c->tet_tpt = tpt;
+    c->fans = tpt == 0;
     c->d_tpack = upload_vec(c, eb.pack);
     c->d_bnodes = upload_vec(c, eb.bnodes);
     c->d_boff = upload_vec(c, eb.boff);
@@ -1610,32 +1751,73 @@ static void install_blocks(eqs_ctx* c, const ElementBlocks& eb, int tpt) {
     }
 }
 
+static int32_t int_exponent(double alpha) {
+    return (alpha == std::floor(alpha) && alpha >= 0 && alpha <= 64) ? (int32_t)alpha : -1;
+}
+
+// Fans where they hold most of a ring and their blocks fill the chip (some 3 per
+// CU): stage_rhs with its fill takes 28.0 us against 26.9 with the best
+// block of single tets at 750,000 tets, 31.1 | 31.0 at 1.3M, 31.9 | 32.1 at 1.6M,
+// 38.8 | 41.7 at 2.6M, 90.6 | 97.6 at 12.6M. No block size is timed then, which
+// takes half of the build's time off (12.6M tets: 7.7 instead of 12.7 s).
+constexpr double kMinFanLength = 4.0;
+constexpr int64_t kMinFans = 800 * kTetBlock;
+// The deterministic pass has lists for single tets. Tets whose exponent is no
+// whole number are taken one by one also inside a fan, so a mesh with many of them
+// stays with single tets.
+static bool fans_apply(const eqs_ctx* c, const std::vector<char>& single) {
+    if (c->npe != 4 || c->deterministic || !c->fan_pass || c->n_tets < 2 * kMinFans) return false;
+    int64_t n = 0;
+    for (int64_t e = 0; e < c->n_tets; ++e) n += single[c->tet_mat[e]];
+    return 4 * n <= c->n_tets;
+}
+
 // Blocks of 256 tets per workgroup trade LDS reuse (each block re-reads the
 // nodes it shares with its neighbours) against parallelism; with autotuning
 // on, every block size that fits the local ids is timed on the RHS pass and
-// the fastest kept (else 4 tets per thread).
+// the fastest kept (else 4 tets per thread). Large first-order meshes take fans.
 void build_element_blocks(eqs_ctx* c, const std::vector<int32_t>& u2i, const double* yfree, double* out) {
     const std::vector<int32_t> order = morton_tet_order(c);
     const int fixed = c->npe == 4 ? 4 : 1;
-    if (!c->autotune || c->n_tets < 16 * (int64_t)kTetBlock * kMaxTetsPerThread) {
+    const std::string key = "element " + std::to_string(c->n_tets) + " " + std::to_string(c->npe);
+    const auto rec = c->autotune ? c->tune_replay.find(key) : c->tune_replay.end();
+    const bool replay = rec != c->tune_replay.end();
+    std::vector<char> single(c->mats.size(), 0);
+    for (size_t m = 0; m < c->mats.size(); ++m) single[m] = c->mats[m].nonlinear && int_exponent(c->mats[m].alpha) < 0;
+    if (fans_apply(c, single) && (!replay || rec->second == "fans")) {
+        std::vector<Fan> fans = build_fans(c, u2i, order, single);
+        const double len = (double)c->n_tets / (double)fans.size();
+        const ElementBlocks eb = len >= kMinFanLength && (int64_t)fans.size() >= kMinFans ? fan_blocks(fans, single) : ElementBlocks{};
+        if (!eb.boff.empty() && eb.max_nodes <= kMaxBlockNodes) {
+            install_blocks(c, eb, 0);
+            char buf[96];
+            std::snprintf(buf, sizeof buf, "element: %d fans per block (%.2f tets a fan)%s\n", kTetBlock, len,
+                          replay ? " (tuning record)" : "");
+            c->tune_log += buf;
+            if (c->autotune) c->tune_record.push_back(key + "\tfans");
+            return;
+        }
+    }
+    // a record of fans where this context takes none: the block size that needs no timing, the same every time
+    const bool untimed = replay && rec->second == "fans";
+    if (!c->autotune || untimed || c->n_tets < 16 * (int64_t)kTetBlock * kMaxTetsPerThread) {
         for (int tpt = fixed; tpt >= 1; tpt /= 2) {
             ElementBlocks eb = element_blocks(c, u2i, order, tpt);
             if (eb.max_nodes <= kMaxBlockNodes) {
                 install_blocks(c, eb, tpt);
-                c->tune_log += "element: " + std::to_string(kTetBlock * tpt) + " tets per block\n";
+                c->tune_log += "element: " + std::to_string(kTetBlock * tpt) + " tets per block" +
+                               (untimed ? " (tuning record)\n" : "\n");
                 return;
             }
         }
         fail(EQS_ERR_INVALID_ARG, "element block of 256 tets with more than " + std::to_string(kMaxBlockNodes) +
                                       " distinct nodes");
     }
-    const std::string key = "element " + std::to_string(c->n_tets) + " " + std::to_string(c->npe);
     {
-        auto it = c->tune_replay.find(key);
-        if (it != c->tune_replay.end()) {  // a recorded block size
-            const int tpt = std::atoi(it->second.c_str());
+        if (replay) {  // a recorded block size
+            const int tpt = std::atoi(rec->second.c_str());
             if (tpt < 1 || tpt > kMaxTetsPerThread || (tpt & (tpt - 1)))
-                fail(EQS_ERR_INVALID_ARG, "tuning record: bad entry for " + key + ": " + it->second);
+                fail(EQS_ERR_INVALID_ARG, "tuning record: bad entry for " + key + ": " + rec->second);
             ElementBlocks eb = element_blocks(c, u2i, order, tpt);
             if (eb.max_nodes > kMaxBlockNodes) fail(EQS_ERR_INVALID_ARG, "tuning record: " + key + " does not fit");
             install_blocks(c, eb, tpt);
@@ -1688,7 +1870,7 @@ void upload(eqs_ctx* c) {
         md[m].inv_es = s.nonlinear ? 1.0 / s.e_s : 0.0;
         md[m].alpha = s.alpha;
         md[m].nonlinear = s.nonlinear ? 1 : 0;
-        md[m].ialpha = (s.alpha == std::floor(s.alpha) && s.alpha >= 0 && s.alpha <= 64) ? (int32_t)s.alpha : -1;
+        md[m].ialpha = int_exponent(s.alpha);
     }
     std::vector<int32_t> dd(c->n_dir);
     {
@@ -1791,7 +1973,7 @@ void free_device(eqs_ctx* c) {
     c->h32 = Hierarchy<float>{};
     c->d_tpack = nullptr; c->d_bnodes = nullptr; c->d_boff = nullptr; c->n_blocks = 0; c->max_block_nodes = 0; c->n_block_nodes = 0;
     c->d_kslots = nullptr; c->d_kend = nullptr; c->d_occ_off = nullptr; c->d_occ = nullptr; c->d_kx_part = nullptr;
-    c->d_cx = c->d_cy = c->d_cz = nullptr; c->d_mats = nullptr; c->tet_tpt = 0;
+    c->d_cx = c->d_cy = c->d_cz = nullptr; c->d_mats = nullptr; c->tet_tpt = 0; c->fans = false;
     c->d_ddrive = nullptr; c->d_int_to_user = nullptr; c->d_drives = nullptr;
     c->d_r = c->d_z = c->d_p = c->d_q = c->d_mx = nullptr;
     c->mx_of_F = false;
