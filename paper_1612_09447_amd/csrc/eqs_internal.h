@@ -487,8 +487,12 @@ void vcycle(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* r, double*
 // folded hierarchy with its bottom at level 1 qualifies (rows and nonzeros of
 // M, unknowns of level 1, nonzeros of Q_0), and the solve, whose outcome is in
 // the pinned scalars and summary once the stream is idle. Its iterations are
-// bounded by kSmallMaxit per launch (longer budgets take the launches).
-constexpr int64_t kSmallBytes = 1 << 20;
+// bounded by kSmallMaxit per launch (longer budgets take the launches). One CU
+// reads the operators every iteration: a step of 8 stages took 0.77 ms instead of
+// 2.35 at 567 rows (FP64), 1.78 | 2.38 at 1,089, 2.27 | 2.37 at 1,440 (702 KB an
+// iteration), 2.80 | 2.47 at 1,859 (1,020 KB); in FP32 2.14 | 2.49 at 1,859 (636 KB)
+// and 2.62 | 2.42 at 2,352 (910 KB).
+constexpr int64_t kSmallBytes = 768 << 10;
 constexpr int32_t kSmallMaxit = 20000;
 bool small_solve_fits(const eqs_ctx* c, int64_t n, int64_t nnz, int64_t n1, int64_t nnz_q);
 void small_solve(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int32_t maxit, double rtol, double* mx_out);

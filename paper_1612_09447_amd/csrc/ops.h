@@ -74,26 +74,39 @@ struct DiaOp {
     __device__ __forceinline__ bool live(int64_t g) const { return g < n; }
     __device__ __forceinline__ int32_t row(int64_t g) const { return (int32_t)g; }
     __device__ __forceinline__ int32_t rows() const { return n; }
-    template <typename F>
-    __device__ __forceinline__ T sum(int64_t, int32_t row, const InstMap& m, int32_t inst, F f) const {
+    // the row's values in column order, and their product
+    __device__ __forceinline__ void values(int32_t row, const InstMap& m, int32_t inst, T (&v)[2 * K + 1]) const {
         const int32_t r0 = m.rows1 >= 0 ? 0 : m.row_off[inst];
-        T v[2 * K + 1], x[2 * K + 1];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int32_t d = offs ? offs[inst * K + k] : off[k];
-            const int32_t jl = row - d >= r0 ? row - d : row, ju = row + d < n ? row + d : row;
-            const T lo = val[(int64_t)(k + 1) * n + jl];
+            const T lo = val[(int64_t)(k + 1) * n + (row - d >= r0 ? row - d : row)];
             v[K - 1 - k] = row - d >= r0 ? lo : T(0);
-            x[K - 1 - k] = (T)f(jl);
             v[K + 1 + k] = val[(int64_t)(k + 1) * n + row];
-            x[K + 1 + k] = (T)f(ju);
         }
         v[K] = val[row];
+    }
+    template <typename F>
+    __device__ __forceinline__ T product(int32_t row, const InstMap& m, int32_t inst, const T (&v)[2 * K + 1], F f) const {
+        const int32_t r0 = m.rows1 >= 0 ? 0 : m.row_off[inst];
+        T x[2 * K + 1];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t d = offs ? offs[inst * K + k] : off[k];
+            x[K - 1 - k] = (T)f(row - d >= r0 ? row - d : row);
+            x[K + 1 + k] = (T)f(row + d < n ? row + d : row);
+        }
         x[K] = (T)f(row);
         T acc = T(0);
 #pragma unroll
         for (int e = 0; e < 2 * K + 1; ++e) acc += v[e] == T(0) ? T(0) : v[e] * x[e];
         return acc;
+    }
+    template <typename F>
+    __device__ __forceinline__ T sum(int64_t, int32_t row, const InstMap& m, int32_t inst, F f) const {
+        T v[2 * K + 1];
+        values(row, m, inst, v);
+        return product(row, m, inst, v, f);
     }
 };
 template <typename T, int K>

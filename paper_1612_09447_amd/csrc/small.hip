@@ -9,10 +9,15 @@
 // in registers, so that an iteration is five phases between barriers:
 //   b_1 = Q^T r,  x_1 = B b_1,  z = G r + Q x_1 (with r.z, r.z_old),
 //   q = M z + beta q, p = z + beta p (with p.q),  x += alpha p, r -= alpha q.
-// The operators (the folded cycle of upload_folded with the dense bottom at
-// level 1) are read through one CU every iteration; small_solve_fits keeps them
-// to what that costs less than the launches. The steps, decisions and tolerances
-// are those of the launches in kernels.hip.
+// What bounds it is latency: of the loads of operators from the L2 (about 0.3 us
+// each, rows' extents before their entries) and of the sums over the workgroup. So
+// the operators of the folded cycle (upload_folded with the dense bottom at level
+// 1) are copied to LDS once where they fit (Stage), rows by diagonals are held in
+// registers, and sums go through lanes by DPP instead of through LDS: at 567 rows
+// 71 us a solve of 10 iterations instead of 115. Larger operators are read through
+// one CU every iteration; small_solve_fits keeps them to what that costs less than
+// the launches. The steps, decisions and tolerances are those of the launches in
+// kernels.hip.
 #include <hip/hip_runtime.h>
 
 #include "ops.h"
@@ -20,8 +25,11 @@
 namespace eqs {
 
 constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / 64;
-constexpr int kSmallRows = 3;  // rows per thread at most
+constexpr int kSmallRows = 2;  // rows per thread at most
 constexpr int kSmallLanes = 16;  // lanes of a coarse row
+
+// Arrays copied to LDS: none, Q^T and B, or Q^T, B, Q and w.
+enum Stage { kStageNone, kStageCoarse, kStageAll };
 
 template <typename T>
 struct SmallArgs {
@@ -38,7 +46,39 @@ struct SmallArgs {
     int32_t maxit, flexible, force;
     PcgScalars* host;
     PcgSummary* host_sum;
+    int32_t rt_nnz, q_stored;
 };
+
+// Copies an array to LDS and returns where; at: the next free byte (16-aligned).
+template <typename V>
+__device__ __forceinline__ const V* small_copy(const V* src, int32_t count, char* lds, int32_t& at) {
+    const int32_t bytes = count * (int32_t)sizeof(V), quads = bytes / 16;
+    char* dst = lds + at;
+#pragma unroll 4
+    for (int32_t k = threadIdx.x; k < quads; k += kSmallThreads)
+        reinterpret_cast<int4*>(dst)[k] = reinterpret_cast<const int4*>(src)[k];
+    const int32_t k = quads * (16 / (int32_t)sizeof(V)) + (int32_t)threadIdx.x;  // fewer than 16 bytes are left
+    if (k < count) reinterpret_cast<V*>(dst)[k] = src[k];
+    at += (bytes + 15) & ~15;
+    return reinterpret_cast<const V*>(dst);
+}
+
+// v + v of the lane the DPP control names (0 where there is none): row_shr by 1, 2,
+// 4 and 8 add up each row of 16 lanes in its last lane, row_bcast 15 and 31 the rows.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {  // in lane 63
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);
+    return dpp_add<0x143, 0xc>(v);
+}
 
 // Sums of K values per thread over the workgroup, in a fixed order, for every
 // thread. red: 2 x 3 x kSmallWaves doubles, used in halves by turns, so that one
@@ -50,19 +90,46 @@ __device__ __forceinline__ void small_sums(double (&v)[K], double* red, int& tur
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-        if (lane == 0) h[k * kSmallWaves + wave] = v[k];
+        const double t = wave_total(v[k]);
+        if (lane == 63) h[k * kSmallWaves + wave] = t;
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        double t = h[k * kSmallWaves + (lane & (kSmallWaves - 1))];
-        for (int off = kSmallWaves / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, kSmallWaves);
-        v[k] = t;
+        double t[kSmallWaves];  // the same addresses for every lane: broadcasts
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) t[w] = h[k * kSmallWaves + w];
+#pragma unroll
+        for (int o = kSmallWaves / 2; o > 0; o >>= 1)
+#pragma unroll
+            for (int w = 0; w < o; ++w) t[w] += t[w + o];
+        v[k] = t[0];
     }
 }
 
-template <typename T, int R, typename OpM, typename OpA>
+// The values of a thread's rows of an operator: held in registers where that is
+// cheap (by diagonals, one row of 7), else read at every product.
+template <typename Op, int R>
+struct SmallRows {
+    __device__ __forceinline__ void load(const Op&, int, int32_t, const InstMap&) {}
+    template <typename F>
+    __device__ __forceinline__ auto sum(const Op& op, int, int64_t g, int32_t row, const InstMap& m, F f) const {
+        return op.sum(g, row, m, 0, f);
+    }
+};
+template <typename T>
+struct SmallRows<DiaOp<T, 3>, 1> {
+    T v[7];
+    __device__ __forceinline__ void load(const DiaOp<T, 3>& op, int, int32_t row, const InstMap& m) {
+        op.values(row, m, 0, v);
+    }
+    template <typename F>
+    __device__ __forceinline__ T sum(const DiaOp<T, 3>& op, int, int64_t, int32_t row, const InstMap& m, F f) const {
+        return op.product(row, m, 0, v, f);
+    }
+};
+
+template <typename T, int R, int STAGE, typename OpM, typename OpA>
 __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, OpM M, OpA A) {
     extern __shared__ double lds[];
     double* rl = lds;                  // r
@@ -72,6 +139,24 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
     T* x1 = b1 + a.n1;
     const int tid = threadIdx.x;
     int turn = 0;
+    CsrView<T> Rt = a.Rt;
+    SellView<T> Q = a.Q;
+    const T* B = a.B;
+    const T* w = a.w;
+    if (STAGE != kStageNone) {
+        char* base = reinterpret_cast<char*>(lds);
+        int32_t at = (int32_t)((reinterpret_cast<char*>(x1 + a.n1) - base + 15) & ~15);
+        Rt.rp = small_copy(a.Rt.rp, a.n1 + 1, base, at);
+        Rt.d16 = small_copy(a.Rt.d16, a.rt_nnz, base, at);
+        Rt.val = small_copy(a.Rt.val, a.rt_nnz, base, at);
+        B = small_copy(a.B, a.n1 * a.n1, base, at);
+        if (STAGE == kStageAll) {
+            Q.sptr = small_copy(a.Q.sptr, a.Q.n_slices + 1, base, at);
+            Q.d16 = small_copy(a.Q.d16, a.q_stored, base, at);
+            Q.val = small_copy(a.Q.val, a.q_stored, base, at);
+            w = small_copy(a.w, a.n, base, at);
+        }
+    }
     // the rows of this thread in M's order; they own x, p, q and r's updates
     int32_t row[R];
     bool own[R];
@@ -89,6 +174,17 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
         f[u] = own[u] ? a.rhs[row[u]] : 0.0;
         p[u] = q[u] = 0.0;
     }
+    // and in Q's order, which form z
+    int32_t rowz[R];
+    SmallRows<OpM, R> mrows;
+    SmallRows<OpA, R> arows;
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int64_t g = u * kSmallThreads + tid;
+        rowz[u] = g < (int64_t)a.Q.n_slices * 64 ? sell_perm_row<1>(a.Q.perm, g) : a.n;
+        if (M.live(g)) mrows.load(M, u, row[u], a.m);
+        if (rowz[u] < a.n) arows.load(A, u, rowz[u], a.m);
+    }
     double bb = 0.0, rr = 0.0, tol2 = 0.0, relres = 0.0;
     // r = rhs - M x into rl; rr and bb
     auto residual = [&](bool store_mx) {
@@ -102,7 +198,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
         for (int u = 0; u < R; ++u) {
             const int64_t g = u * kSmallThreads + tid;
             if (!M.live(g)) continue;
-            const double mx = M.sum(g, row[u], a.m, 0, [&](int32_t j) { return zl[j]; });
+            const double mx = mrows.sum(M, u, g, row[u], a.m, [&](int32_t j) { return zl[j]; });
             if (!own[u]) continue;
             const double r = f[u] - mx;
             rl[row[u]] = r;
@@ -144,7 +240,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
             for (int32_t i0 = 0; i0 < a.n1; i0 += kSmallThreads / kSmallLanes) {
                 const int32_t i = i0 + tid / kSmallLanes;
                 if (i < a.n1) {  // whole lane groups leave together
-                    const T v = csr_row<kSmallLanes>(a.Rt, i, tid % kSmallLanes, [&](int32_t j) { return (T)rl[j]; });
+                    const T v = csr_row<kSmallLanes>(Rt, i, tid % kSmallLanes, [&](int32_t j) { return (T)rl[j]; });
                     if (tid % kSmallLanes == 0) b1[i] = v;
                 }
             }
@@ -153,7 +249,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
             for (int32_t i0 = 0; i0 < a.n1; i0 += kSmallThreads / kSmallLanes) {
                 const int32_t i = i0 + tid / kSmallLanes;
                 if (i < a.n1) {
-                    const T* b = a.B + (int64_t)i * a.n1;
+                    const T* b = B + (int64_t)i * a.n1;
                     T acc = T(0);
                     for (int32_t k0 = tid % kSmallLanes; k0 < a.n1; k0 += 8 * kSmallLanes) {
                         T t[8];
@@ -176,15 +272,15 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
             for (int u = 0; u < R; ++u) {
                 const int64_t g = u * kSmallThreads + tid;
                 if (g >= (int64_t)a.Q.n_slices * 64) continue;
-                const int32_t i = sell_perm_row<1>(a.Q.perm, g);
+                const int32_t i = rowz[u];
                 const bool in = i < a.n;
                 const double ri = in ? rl[i] : 0.0, zo = in ? zl[i] : 0.0;
-                const T wi = in ? a.w[i] : T(0);
-                const T qx = sell_accum<1>(a.Q, g, i, [&](int32_t j) { return x1[j]; });
+                const T wi = in ? w[i] : T(0);
+                const T qx = sell_accum<1>(Q, g, i, [&](int32_t j) { return x1[j]; });
                 T ar = T(0);
                 if (A.live(g)) {
-                    if constexpr (OpA::kScaled) ar = A.sum(g, i, a.m, 0, [&](int32_t j) { return (T)rl[j]; });
-                    else ar = A.sum(g, i, a.m, 0, [&](int32_t j) { return a.w[j] * (T)rl[j]; });
+                    if constexpr (OpA::kScaled) ar = arows.sum(A, u, g, i, a.m, [&](int32_t j) { return (T)rl[j]; });
+                    else ar = arows.sum(A, u, g, i, a.m, [&](int32_t j) { return w[j] * (T)rl[j]; });
                 }
                 if (in) {
                     const T v = wi * (T(2) * (T)ri - ar) + qx;
@@ -207,7 +303,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
             for (int u = 0; u < R; ++u) {
                 const int64_t g = u * kSmallThreads + tid;
                 if (!M.live(g)) continue;
-                const double mz = M.sum(g, row[u], a.m, 0, [&](int32_t j) { return zl[j]; });
+                const double mz = mrows.sum(M, u, g, row[u], a.m, [&](int32_t j) { return zl[j]; });
                 if (!own[u]) continue;
                 const double zi = zl[row[u]];
                 p[u] = fresh ? zi : zi + beta * p[u];
@@ -279,6 +375,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_solve(SmallArgs<T> a, O
     }
 }
 
+constexpr size_t kSmallLds = 160 * 1024;  // of a CU
 static size_t small_lds(const eqs_ctx* c, int64_t n, int64_t n1) {
     return sizeof(double) * (size_t)(2 * n + 6 * kSmallWaves) +
            (c->amg.precision == EQS_PREC_FP32 ? sizeof(float) : sizeof(double)) * (size_t)(2 * n1);
@@ -297,9 +394,19 @@ static void launch(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* rhs
     Level<T>& l1 = h.lv[1];
     const InstMap m{nullptr, nullptr, 1, (int32_t)c->n_free, 1, 1};
     const SmallArgs<T> a{m, cview(l0.R), view(l0.Q.sell), l1.dense_inv, l0.w, l0.n, l1.n, rhs, x, mx_out, rtol, maxit,
-                         c->amg.flexible, c->test_reject_first ? 1 : 0, c->d_hscal, c->d_hsum};
-    const size_t lds = small_lds(c, l0.n, l1.n);
+                         c->amg.flexible, c->test_reject_first ? 1 : 0, c->d_hscal, c->d_hsum, (int32_t)l0.R.nnz,
+                         (int32_t)l0.Q.sell.stored};
     const int R = (l0.n + kSmallThreads - 1) / kSmallThreads;
+    const auto pad = [](size_t b) { return (b + 15) & ~(size_t)15; };
+    const size_t base = pad(small_lds(c, l0.n, l1.n));
+    const size_t coarse = pad(4 * (size_t)(l1.n + 1)) + pad(2 * (size_t)a.rt_nnz) + pad(sizeof(T) * (size_t)a.rt_nnz) +
+                          pad(sizeof(T) * (size_t)l1.n * l1.n);
+    const size_t fine = pad(4 * (size_t)(l0.Q.sell.n_slices + 1)) + pad(2 * (size_t)a.q_stored) +
+                        pad(sizeof(T) * (size_t)a.q_stored) + pad(sizeof(T) * (size_t)l0.n);
+    const bool d16 = a.Rt.d16 && a.Q.d16;
+    const int stage = !d16 ? kStageNone : base + coarse + fine <= kSmallLds ? kStageAll
+                                      : base + coarse <= kSmallLds          ? kStageCoarse : kStageNone;
+    const size_t lds = base + (stage != kStageNone ? coarse : 0) + (stage == kStageAll ? fine : 0);
     using OpT = double;
     EQS_WITH_OP(c->Mdia, view(c->M), {
         using OpM = std::decay_t<decltype(op)>;
@@ -307,7 +414,13 @@ static void launch(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* rhs
         OpA oa;
         if constexpr (OpA::kScaled) oa = OpA{sview(l0)};
         else oa = dia_op<T, OpA::kDiagonals>(l0.D);
-        auto k = R == 1 ? k_small_solve<T, 1, OpM, OpA> : R == 2 ? k_small_solve<T, 2, OpM, OpA> : k_small_solve<T, 3, OpM, OpA>;
+        const auto pick = [&](auto st) {
+            constexpr int S = decltype(st)::value;
+            return R == 1 ? k_small_solve<T, 1, S, OpM, OpA> : k_small_solve<T, 2, S, OpM, OpA>;
+        };
+        auto k = stage == kStageAll      ? pick(std::integral_constant<int, kStageAll>{})
+                 : stage == kStageCoarse ? pick(std::integral_constant<int, kStageCoarse>{})
+                                         : pick(std::integral_constant<int, kStageNone>{});
         hipLaunchKernelGGL(k, dim3(1), dim3(kSmallThreads), lds, s, a, op, oa);
     });
 }
