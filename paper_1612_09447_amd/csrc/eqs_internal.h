@@ -610,10 +610,11 @@ void prof_release(eqs_ctx* c);
 // NULL): receives M y for the returned y.
 // before_sync (may be NULL): queued work the caller wants behind the residual
 // check, called each time before the host waits for that check (again after a
-// restart, so it acts on the final solution).
+// restart, so it acts on the final solution). started (may be NULL): called once,
+// with the first iteration queued.
 int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit, eqs_solve_stats* st,
             const double* mx_in = nullptr, double* mx_out = nullptr,
-            const std::function<void()>* before_sync = nullptr);
+            const std::function<void()>* before_sync = nullptr, const std::function<void()>* started = nullptr);
 int rkc_step(eqs_ctx* c, double t, double dt, int32_t s, double* x_user, double rtol, int32_t maxit,
              eqs_step_stats* st);
 void apply_preconditioner(eqs_ctx* c, const double* r, double* z);

@@ -94,7 +94,8 @@ void release_graphs(eqs_ctx* c) {
 // disagree restart from them. Aggregated stats: max iterations, worst status,
 // max relres; per-instance results are in c->inst_iters / c->inst_relres.
 int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit, eqs_solve_stats* st,
-            const double* mx_in, double* mx_out, const std::function<void()>* before_sync) {
+            const double* mx_in, double* mx_out, const std::function<void()>* before_sync,
+            const std::function<void()>* started) {
     const Range range("eqs: CG solve of M");
     hipStream_t s = c->stream;
     const int prec = c->amg.precision;
@@ -103,6 +104,7 @@ int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit
     if (small) {
         small_solve(s, c, rhs, y, maxit, rtol, mx_out);
         check_launch();
+        if (started) (*started)();
         if (before_sync) {
             EQS_HIP(hipEventRecord(c->ev[0], s));
             (*before_sync)();
@@ -136,6 +138,7 @@ int solve_M(eqs_ctx* c, const double* rhs, double* y, double rtol, int32_t maxit
         bool checked = false;
         run_iteration(c, y, prec);
         EQS_HIP(hipEventRecord(c->ev[0], s));
+        if (started && restarts == 0) (*started)();
         for (int64_t k = 0;; ++k) {
             const bool last = (k + 1) * G > (int64_t)maxit + 2;  // the device stops itself at maxit
             bool ahead = !last;
@@ -240,20 +243,16 @@ int rkc_step(eqs_ctx* c, double t, double dt, int32_t s, double* x_user, double 
     int rc = EQS_OK;
     const double* Ycur = c->d_Y0;
     const double* Yprev = c->d_Y0;
-    bool rhs_zeroed = false;  // the last combination cleared d_rhs for this stage's element pass
-    bool rhs_ready = false;   // this stage's element pass already ran (queued behind the last solve)
-    // With the plain start vector the host queues the rest of the stage (F_0
-    // copy, combination) and the next stage's element pass behind the residual
-    // check that ends each solve, before it waits for that check: the GPU then
-    // works through the host's round trip. The combination writes a third
-    // buffer (no operand is overwritten) and the next element pass writes
-    // d_rhs_alt, so a restart of the solve only has to queue them again.
-    const bool early = c->guess.p.kind == EQS_GUESS_PREVIOUS;
+    // The host queues the rest of the stage (F_0 copy, combination) and the next
+    // stage's element pass behind the residual check that ends each solve, before
+    // it waits for that check: the GPU then works through the host's round trip.
+    // The combination writes a third buffer (no operand is overwritten) and the
+    // next element pass writes d_rhs_alt, so a restart of the solve only has to
+    // queue them again.
     double* const ybuf[3] = {c->d_Ya, c->d_Yb, c->d_Yc};
     for (int j = 0; j < s; ++j) {
         const Range stage("eqs: RKC stage");
-        const double tj = t + cc[j] * dt;
-        if (!rhs_ready) launch_kx(q, true, c, Ycur, tj, c->d_rhs, rhs_zeroed);
+        if (j == 0) launch_kx(q, true, c, Ycur, t + cc[0] * dt, c->d_rhs);  // later stages': see rest
         check_launch();
         // start vector: F_{j-1} (held in d_F), zero, or an estimator's vector
         const int kind = c->guess.p.kind;
@@ -262,7 +261,6 @@ int rkc_step(eqs_ctx* c, double t, double dt, int32_t s, double* x_user, double 
         } else if (kind == EQS_GUESS_GALERKIN || kind == EQS_GUESS_MLP || kind == EQS_GUESS_MOR) {
             const int u = guess_stage(c);
             if (u == 1) S.guess_used++;
-            guess_train(c);  // MLP: overlaps the solve below
         }
         double* out = ybuf[0];
         for (double* b : ybuf)
@@ -272,10 +270,10 @@ int rkc_step(eqs_ctx* c, double t, double dt, int32_t s, double* x_user, double 
             }
         const bool next = j + 1 < s;
         // the rest of the stage: F_0, Y_{j+1} (clearing the next element pass's
-        // output), and with `early` that pass itself
+        // output) and that pass
         auto rest = [&]() {
             if (j == 0) launch_copy(q, c->d_F0, c->d_F, NF);
-            double* zero = next ? (early ? c->d_rhs_alt : c->d_rhs) : nullptr;
+            double* zero = next ? c->d_rhs_alt : nullptr;
             if (j == 0) {
                 launch_rkc_first(c, q, out, c->d_Y0, c->d_F0, mut[1] * dt, NF, zero);
             } else {
@@ -283,16 +281,19 @@ int rkc_step(eqs_ctx* c, double t, double dt, int32_t s, double* x_user, double 
                 launch_rkc_combine(c, q, out, c->d_Y0, Ycur, Yprev, c->d_F, c->d_F0, 1.0 - mu[k] - nu[k], mu[k],
                                    nu[k], mut[k] * dt, gmt[k] * dt, NF, zero);
             }
-            if (early && next) launch_kx(q, true, c, out, t + cc[j + 1] * dt, c->d_rhs_alt, true);
+            if (next) launch_kx(q, true, c, out, t + cc[j + 1] * dt, c->d_rhs_alt, true);
         };
         const std::function<void()> rest_fn = rest;
+        // the network's training, prepared by the host while the GPU has the solve's
+        // first iterations to work on
+        const std::function<void()> train_fn = [&]() { guess_train(c); };
         // F_j = M^{-1} r_j. Started from F_{j-1} itself, the start residual
         // reuses M F_{j-1} from the check that ended the previous solve.
         eqs_solve_stats ss{};
         const bool reuse = kind == EQS_GUESS_PREVIOUS && c->mx_of_F;
         c->mx_of_F = false;
         const int src = solve_M(c, c->d_rhs, c->d_F, rtol, maxit, &ss, reuse ? c->d_mx : nullptr, c->d_mx,
-                                early ? &rest_fn : nullptr);
+                                &rest_fn, kind == EQS_GUESS_MLP ? &train_fn : nullptr);
         c->mx_of_F = src == EQS_OK || src == EQS_ERR_NOT_CONVERGED;
         if (kind == EQS_GUESS_GALERKIN || kind == EQS_GUESS_MLP || kind == EQS_GUESS_MOR) guess_after_solve(c, ss.iters);
         c->stage_iters.push_back(ss.iters);
@@ -308,11 +309,7 @@ int rkc_step(eqs_ctx* c, double t, double dt, int32_t s, double* x_user, double 
             c->have_Flast = false;
             return src;
         }
-        if (!early) rest();
-        check_launch();
-        if (early && next) std::swap(c->d_rhs, c->d_rhs_alt);  // the next stage's RHS is ready
-        rhs_ready = early && next;
-        rhs_zeroed = !early && next;
+        if (next) std::swap(c->d_rhs, c->d_rhs_alt);  // the next stage's RHS is ready
         Yprev = Ycur;
         Ycur = out;
     }
