@@ -192,8 +192,8 @@ __global__ void k_sum_rows(const double* __restrict__ part, int64_t stride, int 
     __shared__ double sh[4];
     double x = 0.0;
     for (int i = threadIdx.x; i < nb; i += blockDim.x) x += part[blockIdx.x * stride + i];
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = x;
+    x = wave_total(x);
+    if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = x;
     __syncthreads();
     if (threadIdx.x == 0) out[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }

@@ -62,10 +62,9 @@ __device__ __forceinline__ T vec_load(const T* p) {
 template <int K>
 __device__ __forceinline__ void block_sums(double (&v)[K], double* sh) {
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_down(v[k], off, 64);
+    for (int k = 0; k < K; ++k) v[k] = wave_total(v[k]);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if (lane == 0)
+    if (lane == 63)
 #pragma unroll
         for (int k = 0; k < K; ++k) sh[nw * k + wid] = v[k];
     __syncthreads();
@@ -174,11 +173,7 @@ __device__ __forceinline__ void wave_range_sums(const double* const (&parts)[NP]
             for (int p = 0; p < NP; ++p) acc[p] += (b + 64 * u <= hi) ? t[p][u] : 0.0;
     }
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-        double v = acc[p];
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        out[p] = v;
-    }
+    for (int p = 0; p < NP; ++p) out[p] = wave_sum(acc[p]);
 }
 
 constexpr int kFinWaves = kFin / 64;
@@ -287,8 +282,8 @@ __device__ __forceinline__ void pro_sum(const ProParts<NP, U>& P, double* sh, do
         double v = P.h[p];
 #pragma unroll
         for (int u = 0; u < U; ++u) v += P.t[p][u];
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) sh[nw * p + wave] = v;
+        v = wave_total(v);
+        if (lane == 63) sh[nw * p + wave] = v;
     }
     __syncthreads();
 #pragma unroll
@@ -1555,6 +1550,13 @@ static void launch_postsmooth(hipStream_t s, eqs_ctx* c, int cls, const Level<T>
     }
 }
 
+// Some 50 us on one wavefront: the launches behind it queue up meanwhile and then
+// run back to back. (Timed without it, kernels shorter than the host's 4.5 us a
+// launch all look alike, and layouts were picked by noise.)
+__global__ void k_delay() {
+    for (int k = 0; k < 15; ++k) __builtin_amdgcn_s_sleep(127);
+}
+
 // Time per product y = A x (ms) for the layout tuner: the median over `reps`
 // rounds (after one warm-up round) of kBatch back-to-back launches between two
 // events, divided by kBatch. A single launch between events carries the
@@ -1569,6 +1571,7 @@ double time_mv(eqs_ctx* c, const SpMat<T>& A, const T* x, T* y, int reps) {
     EQS_HIP(hipEventCreate(&e1));
     std::vector<float> ms;
     for (int r = 0; r < reps + 1; ++r) {
+        hipLaunchKernelGGL(k_delay, dim3(1), dim3(64), 0, c->stream);
         EQS_HIP(hipEventRecord(e0, c->stream));
         for (int k = 0; k < kBatch; ++k) launch_mv<T, T>(c->stream, c, -1, -1, A, x, y, 0, MV_PLAIN);
         EQS_HIP(hipEventRecord(e1, c->stream));
@@ -1633,9 +1636,8 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_restrict(const T* __r
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc += (j0 + u * kCoarseThreads < nf) ? t[u] : T(0);
     }
-    double v = (double)acc;
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    const double v = wave_total((double)acc);
+    if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0 && i < n) {
         double t = 0.0;
@@ -1975,6 +1977,17 @@ struct DotParts {
 };
 __device__ __forceinline__ void store_dots(const DotParts& D, const double (&v)[4], bool one, bool second,
                                            int32_t bound, double* sh, int64_t B) {
+    if (one) {  // one barrier for all four
+        double t[4] = {v[0], v[1], v[2], v[3]};
+        block_sums<4>(t, sh);
+        if (threadIdx.x == 0) {
+            D.pq[B] = t[0];
+            D.rq[B] = t[1];
+            D.qq[B] = t[2];
+            D.rr[B] = t[3];
+        }
+        return;
+    }
     double* const a[2] = {D.pq, D.rq};
     const double va[2] = {v[0], v[1]};
     store_pairs<2>(a, va, one, second, bound, sh, B);

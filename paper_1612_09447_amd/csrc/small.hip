@@ -63,23 +63,6 @@ __device__ __forceinline__ const V* small_copy(const V* src, int32_t count, char
     return reinterpret_cast<const V*>(dst);
 }
 
-// v + v of the lane the DPP control names (0 where there is none): row_shr by 1, 2,
-// 4 and 8 add up each row of 16 lanes in its last lane, row_bcast 15 and 31 the rows.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
-    return v + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_total(double v) {  // in lane 63
-    v = dpp_add<0x111, 0xf>(v);
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);
-    return dpp_add<0x143, 0xc>(v);
-}
-
 // Sums of K values per thread over the workgroup, in a fixed order, for every
 // thread. red: 2 x 3 x kSmallWaves doubles, used in halves by turns, so that one
 // barrier per call is enough (the next use of a half is a barrier away).
