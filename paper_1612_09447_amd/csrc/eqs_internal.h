@@ -71,7 +71,8 @@ struct Sell {
     int64_t stored = 0;         // padded entries
     int32_t* sptr = nullptr;    // [n_slices + 1]
     int32_t* col = nullptr;     // [stored] absolute column ids, or
-    int16_t* d16 = nullptr;     // [stored] column - offset_base(row) when every entry allows
+    int16_t* d16 = nullptr;     // [stored] column - offset_base(row) when every entry allows, or (pbase)
+    int32_t* pbase = nullptr;   // [stored / 128] column - pbase[pair] of its pair of entries
     T* val = nullptr;           // [stored]
     uint8_t* perm = nullptr;    // [n_slices * 64 / lanes] row order within 256-thread windows, or NULL
     int32_t xcd = 0;            // 1: products walk row blocks in the XCD order (row_block in sell.h)
@@ -445,7 +446,8 @@ void free_device(eqs_ctx* c);
 // sorted: rows longest first within 256-thread windows; key (may be NULL): the
 // matrix whose row lengths sort them instead (two operators then share an order)
 template <typename T>
-Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted = false, const Csr<double>* key = nullptr);
+Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted = false, const Csr<double>* key = nullptr,
+                int32_t split = 0);
 template <typename T>
 SpMat<T> to_spmat(eqs_ctx* c, const Csr<double>& A);
 

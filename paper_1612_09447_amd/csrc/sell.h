@@ -9,7 +9,12 @@
 // combined by cross-lane shuffles.
 // Column ids are either absolute (col, 32-bit) or, when every stored entry
 // lies within 32767 of offset_base(row), 16-bit offsets from it (d16): 6
-// instead of 8 bytes per FP32 entry, 10 instead of 12 per FP64 entry.
+// instead of 8 bytes per FP32 entry, 10 instead of 12 per FP64 entry. Where rows
+// reach further (the transfers of large meshes: several planes of nodes), the
+// offsets are from a base of each pair of entries (pbase), whose 128 columns lie
+// close together: rows of a slice are neighbours (2.1M rows,
+// FP32: the first restriction 20.5 -> 17.8 us, [G Q] 23.2 -> 21.2; they read 6 bytes
+// an entry instead of 8).
 // Padding entries carry value 0 and an in-range column.
 #pragma once
 
@@ -99,11 +104,12 @@ struct SellView {
     int32_t n_rows, n_slices, n_cols;
     const uint8_t* __restrict__ perm;  // row order within each 256-thread window, or NULL (see sell_perm_row)
     int32_t xcd;                       // block order of its products (see row_block)
+    const int32_t* __restrict__ pbase; // d16 is relative to it, pair by pair, when set
 };
 
 template <typename T>
 static inline SellView<T> view(const Sell<T>& A) {
-    return SellView<T>{A.sptr, A.col, A.d16, A.val, A.n_rows, A.n_slices, A.n_cols, A.perm, A.xcd};
+    return SellView<T>{A.sptr, A.col, A.d16, A.val, A.n_rows, A.n_slices, A.n_cols, A.perm, A.xcd, A.pbase};
 }
 
 // With a row order (perm), the rows served by one 256-thread window (4
@@ -139,7 +145,16 @@ template <int N, typename T, typename F>
 __device__ __forceinline__ T sell_pairs(const SellView<T>& A, int64_t at, int32_t base, F f, T acc) {
     Pair<T> v[N];
     Pair<int32_t> j[N];
-    if (A.d16) {
+    if (A.pbase) {
+        const int32_t* pb = A.pbase + __builtin_amdgcn_readfirstlane((int32_t)(at >> 7));
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            v[u] = load_pair(A.val + at + 128 * u);
+            const Pair<int16_t> d = load_pair(A.d16 + at + 128 * u);
+            const int32_t b = pb[u];
+            j[u] = Pair<int32_t>{b + d.a, b + d.b};
+        }
+    } else if (A.d16) {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             v[u] = load_pair(A.val + at + 128 * u);

@@ -605,6 +605,7 @@ static void visit_sell(Sell<T>& S, const std::function<void(void**)>& f) {
     f((void**)&S.sptr);
     f((void**)&S.col);
     f((void**)&S.d16);
+    f((void**)&S.pbase);
     f((void**)&S.val);
     f((void**)&S.perm);
 }
@@ -753,7 +754,7 @@ static T* upload_vec(eqs_ctx* c, const std::vector<T>& v) {
 }
 
 template <typename T>
-Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const Csr<double>* key) {
+Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const Csr<double>* key, int32_t split) {
     if (lanes != 1 && lanes != 2 && lanes != 4 && lanes != 8) fail(EQS_ERR_STATE, "SELL lanes per row must be 1, 2, 4 or 8");
     const int32_t rows_per = kSlice / lanes;  // rows of one slice
     const int32_t window = 4 * rows_per;      // rows of one 256-thread window
@@ -775,39 +776,56 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const 
             std::stable_sort(pos2row.begin() + w0, pos2row.begin() + w1,
                              [&](int32_t a, int32_t b) { return key_len(a) > key_len(b); });
         }
-    std::vector<int32_t> sptr(S.n_slices + 1, 0);
-    for (int32_t s = 0; s < S.n_slices; ++s) {
-        int32_t w = 0;  // entries per lane
-        for (int32_t k = s * rows_per; k < (s + 1) * rows_per; ++k) w = std::max(w, (len(pos2row[k]) + lanes - 1) / lanes);
-        w = (w + 1) & ~1;  // whole pairs
-        int64_t next = (int64_t)sptr[s] + (int64_t)w * kSlice;
-        if (next > INT32_MAX) fail(EQS_ERR_INVALID_ARG, "matrix too large for SELL offsets");
-        sptr[s + 1] = (int32_t)next;
-    }
-    S.stored = sptr[S.n_slices];
     // lane l of slice s serves the row at position s * rows_per + l / lanes and
-    // holds the row's entries l % lanes + lanes * k, k = 0 .. w-1
-    std::vector<int32_t> col(S.stored, 0);
-    std::vector<T> val(S.stored, T(0));
-    for (int32_t s = 0; s < S.n_slices; ++s) {
-        const int32_t w = (sptr[s + 1] - sptr[s]) / kSlice;
-        for (int32_t l = 0; l < kSlice; ++l) {
-            const int32_t r = pos2row[(size_t)(s * rows_per + l / lanes)], part = l % lanes;
-            int32_t pad_col = 0;
-            const int32_t n = len(r);
-            if (n > 0) pad_col = A.col[A.ptr[r] + n - 1];
-            for (int32_t k = 0; k < w; ++k) {
-                const int64_t at = sptr[s] + (int64_t)(k >> 1) * 2 * kSlice + 2 * l + (k & 1);
-                const int32_t e = k * lanes + part;
-                if (e < n) {
-                    col[at] = A.col[A.ptr[r] + e];
-                    val[at] = (T)A.val[A.ptr[r] + e];
-                } else {
-                    col[at] = pad_col;
+    // holds the row's entries l % lanes + lanes * k, k = 0 .. w-1; columns from
+    // `at_col` on begin at a pair of their own in all rows of a slice
+    std::vector<int32_t> sptr, col;
+    std::vector<T> val;
+    auto lay_out = [&](int32_t at_col) {
+        auto first_len = [&](int32_t r) {  // entries before at_col
+            if (r >= A.n_rows) return 0;
+            if (at_col >= A.n_cols) return len(r);
+            return (int32_t)(std::lower_bound(A.col.begin() + A.ptr[r], A.col.begin() + A.ptr[r + 1], at_col) -
+                             (A.col.begin() + A.ptr[r]));
+        };
+        auto lane_pairs = [&](int32_t n) { return ((n + lanes - 1) / lanes + 1) / 2; };
+        sptr.assign(S.n_slices + 1, 0);
+        std::vector<int32_t> w1((size_t)S.n_slices, 0);  // pairs before at_col
+        for (int32_t s = 0; s < S.n_slices; ++s) {
+            int32_t p1 = 0, p2 = 0;
+            for (int32_t k = s * rows_per; k < (s + 1) * rows_per; ++k) {
+                const int32_t n1 = first_len(pos2row[k]);
+                p1 = std::max(p1, lane_pairs(n1));
+                p2 = std::max(p2, lane_pairs(len(pos2row[k]) - n1));
+            }
+            w1[(size_t)s] = p1;
+            const int64_t next = (int64_t)sptr[s] + (int64_t)(p1 + p2) * 2 * kSlice;
+            if (next > INT32_MAX) fail(EQS_ERR_INVALID_ARG, "matrix too large for SELL offsets");
+            sptr[s + 1] = (int32_t)next;
+        }
+        S.stored = sptr[S.n_slices];
+        col.assign(S.stored, 0);
+        val.assign(S.stored, T(0));
+        for (int32_t s = 0; s < S.n_slices; ++s) {
+            const int32_t w = (sptr[s + 1] - sptr[s]) / kSlice, wa = 2 * w1[(size_t)s];
+            for (int32_t l = 0; l < kSlice; ++l) {
+                const int32_t r = pos2row[(size_t)(s * rows_per + l / lanes)], part = l % lanes;
+                const int32_t n = len(r), n1 = first_len(r);
+                for (int32_t k = 0; k < w; ++k) {
+                    const int64_t at = sptr[s] + (int64_t)(k >> 1) * 2 * kSlice + 2 * l + (k & 1);
+                    const bool one = k < wa;
+                    const int32_t e = one ? k * lanes + part : n1 + (k - wa) * lanes + part, end = one ? n1 : n;
+                    if (e < end) {
+                        col[at] = A.col[A.ptr[r] + e];
+                        val[at] = (T)A.val[A.ptr[r] + e];
+                    } else {  // the part's last column, or the row's
+                        col[at] = end > (one ? 0 : n1) ? A.col[A.ptr[r] + end - 1] : n > 0 ? A.col[A.ptr[r] + n - 1] : 0;
+                    }
                 }
             }
         }
-    }
+    };
+    lay_out(A.n_cols);
     // 16-bit offsets from offset_base(row) when every stored column allows
     // (padding of rows past n_rows points at the last column)
     bool fits = c->index16 && A.n_cols > 0;
@@ -831,6 +849,43 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const 
             }
         }
     }
+    // else from a base of each pair of entries (of one slice), when no 128 columns
+    // of a pair span more than 65535
+    std::vector<int32_t> pbase;
+    auto by_pairs = [&]() {
+        const int64_t np = S.stored / (2 * kSlice);
+        pbase.assign((size_t)np, 0);
+        d16.resize((size_t)S.stored);
+        for (int32_t s = 0; s < S.n_slices; ++s) {
+            // lanes of rows that are there: their padding keeps the row's own column (0 times
+            // another row's operand is not 0 where that is no number)
+            const int32_t rows = std::min(rows_per, (int32_t)std::max(0, A.n_rows - s * rows_per));
+            const bool whole = rows == rows_per;
+            for (int64_t q = sptr[s] / (2 * kSlice); q < sptr[s + 1] / (2 * kSlice); ++q) {
+                const int32_t* p = &col[(size_t)q * 2 * kSlice];
+                int32_t lo = INT32_MAX, hi = 0;
+                for (int e = 0; e < 2 * kSlice; ++e)
+                    if (whole || pos2row[(size_t)(s * rows_per + (e / 2) / lanes)] < A.n_rows) {
+                        lo = std::min(lo, p[e]);
+                        hi = std::max(hi, p[e]);
+                    }
+                if (hi - lo > 65535) return false;
+                pbase[(size_t)q] = lo + 32768;
+                for (int e = 0; e < 2 * kSlice; ++e)
+                    d16[(size_t)q * 2 * kSlice + e] = (int16_t)(std::min(std::max(p[e], lo), hi) - lo - 32768);
+            }
+        }
+        return true;
+    };
+    if (!fits && c->index16 && A.n_cols > 0) {
+        fits = by_pairs();
+        if (!fits && split > 0 && split < A.n_cols) {
+            lay_out(split);
+            fits = by_pairs();
+            if (!fits) lay_out(A.n_cols);
+        }
+        if (fits) S.pbase = upload_vec(c, pbase);
+    }
     S.sptr = upload_vec(c, sptr);
     if (fits) S.d16 = upload_vec(c, d16);
     else S.col = upload_vec(c, col);
@@ -843,8 +898,8 @@ Sell<T> to_sell(eqs_ctx* c, const Csr<double>& A, int lanes, bool sorted, const 
     return S;
 }
 
-template Sell<double> to_sell<double>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*);
-template Sell<float> to_sell<float>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*);
+template Sell<double> to_sell<double>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*, int32_t);
+template Sell<float> to_sell<float>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*, int32_t);
 
 // CSR column ids: 16-bit offsets from offset_base(row) when every entry
 // allows, else absolute.
@@ -1008,6 +1063,7 @@ static void free_spmat(eqs_ctx* c, SpMat<T>& S) {
     dev_free(c, S.sell.sptr);
     dev_free(c, S.sell.col);
     dev_free(c, S.sell.d16);
+    dev_free(c, S.sell.pbase);
     dev_free(c, S.sell.val);
     dev_free(c, S.sell.perm);
     dev_free(c, S.rowptr);
@@ -1027,7 +1083,7 @@ static void free_spmat(eqs_ctx* c, SpMat<T>& S) {
 // keep the fastest.
 template <typename T>
 static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, bool sell_only = false,
-                             bool allow_sorted = false) {
+                             bool allow_sorted = false, int32_t split = 0) {
     if (sell_only) {  // the finest operator: its post-smoothing kernel writes per-block CG partials
         SpMat<T> S;
         S.n_rows = A.n_rows; S.n_cols = A.n_cols; S.nnz = A.nnz();
@@ -1056,7 +1112,7 @@ static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, 
         } else {
             S.n_rows = A.n_rows; S.n_cols = A.n_cols; S.nnz = A.nnz();
             S.fmt = FMT_SELL;
-            S.sell = to_sell<T>(c, A, c->force_layout, c->force_sorted && allow_sorted);
+            S.sell = to_sell<T>(c, A, c->force_layout, c->force_sorted && allow_sorted, nullptr, split);
             S.sell.unroll = c->force_unroll;
         }
         c->tune_log += std::string(what) + ": layout set by EQS_LAYOUT\n";
@@ -1091,7 +1147,7 @@ static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, 
                        (U == 4 || U == 8 || U == 16)) {
                 S.n_rows = A.n_rows; S.n_cols = A.n_cols; S.nnz = A.nnz();
                 S.fmt = FMT_SELL;
-                S.sell = to_sell<T>(c, A, L, sorted != 0 && allow_sorted);
+                S.sell = to_sell<T>(c, A, L, sorted != 0 && allow_sorted, nullptr, split);
                 S.sell.unroll = U;
             } else {
                 fail(EQS_ERR_INVALID_ARG, "tuning record: bad entry for " + key + ": " + it->second);
@@ -1132,7 +1188,7 @@ static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, 
             SpMat<T> S;
             S.n_rows = A.n_rows; S.n_cols = A.n_cols; S.nnz = A.nnz();
             S.fmt = FMT_SELL;
-            S.sell = to_sell<T>(c, A, L, sorted != 0);
+            S.sell = to_sell<T>(c, A, L, sorted != 0, nullptr, split);
             // the group size, timed on the product (the coarse smoothing kernels
             // take the same; the finest level's keep 8)
             {
@@ -1156,7 +1212,7 @@ static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, 
                 S.sell.unroll = best_u;
             }
             consider(S, std::string("sell64") + (L > 1 ? "x" + std::to_string(L) : "") + (sorted ? "s" : "") +
-                            (S.sell.d16 ? "/i16" : "") + (S.sell.unroll != 8 ? "/u" + std::to_string(S.sell.unroll) : ""));
+                            (S.sell.pbase ? "/p16" : S.sell.d16 ? "/i16" : "") + (S.sell.unroll != 8 ? "/u" + std::to_string(S.sell.unroll) : ""));
         }
     }
     for (int L = (mean <= 8.0 ? 1 : 2); L <= 64; L *= 2) {
@@ -1213,6 +1269,7 @@ static T* scaled_values(eqs_ctx* c, const SpMat<T>& S, const Csr<double>& A, con
         dev_free(c, t.sptr);
         dev_free(c, t.col);
         dev_free(c, t.d16);
+        dev_free(c, t.pbase);
         dev_free(c, t.perm);
         return t.val;
     }
@@ -1422,7 +1479,7 @@ static void upload_folded(eqs_ctx* c, const AmgHost& ah, Hierarchy<T>& h) {
                 }
                 GQ.ptr[(size_t)i + 1] = (int32_t)GQ.col.size();
             }
-            lv.GQ = tuned_spmat<T>(c, GQ, ("[G Q]" + id).c_str(), false, true);
+            lv.GQ = tuned_spmat<T>(c, GQ, ("[G Q]" + id).c_str(), false, true, GQ.n_rows);
         }
         if (l == t - 1 && merged) continue;
         if (h.small) {

@@ -175,3 +175,27 @@ def test_reductions_by_the_next_kernel_or_by_finalisers(n):
     with context(case, EQS_PREC_FP32) as c:
         its = [solve(c, o, rhs, x0, classes)[0] for classes in ((), ("finalise",), ("spmv_M",))]
     assert max(its) - min(its) <= 1, its
+
+
+@pytest.mark.parametrize("precision", [EQS_PREC_FP64, EQS_PREC_FP32])
+def test_columns_from_a_base_per_pair(precision, monkeypatch):
+    """[G Q] on level 1 of 61^3 cells, whose columns 33,000 rows apart fit no offset
+    from the row: from pairs' bases, in every number of lanes a row, and as 32-bit
+    columns (EQS_INDEX16=0). The same entries in the same lanes, so sums differ by
+    their order only where the two parts of a row begin at a pair of their own."""
+    case = eqsgen.case_c1(n=61, seed=1)
+    z = []
+    rng = np.random.default_rng(6)
+    for layout, index16 in [("1", "1"), ("2", "1"), ("4", "1"), ("8", "1"), ("1", "0"), ("4", "0")]:
+        monkeypatch.setenv("EQS_LAYOUT", "sell" + layout)
+        monkeypatch.setenv("EQS_INDEX16", index16)
+        with context(case, precision) as c:
+            n = c.info()["n_free"]
+            if not z:
+                r = rng.standard_normal(n)
+            out = torch.zeros(n, dtype=torch.float64, device=DEV)
+            c.apply_preconditioner(T(r), out)
+            z.append(out.cpu().numpy())
+    tol = 1e-13 if precision == EQS_PREC_FP64 else 2e-6  # some 50 terms of 2^-53, 2^-24 each
+    for v in z[1:]:
+        assert np.linalg.norm(v - z[0]) <= tol * np.linalg.norm(z[0])
