@@ -25,6 +25,7 @@ import argparse
 import json
 import os
 import platform
+import re
 import sys
 import time
 
@@ -50,12 +51,14 @@ def element_bytes(info):
 
 
 def spmv_bytes(info, nnz):
-    # CG product q = M z + beta q, p = z + beta p on the free DOF: value (8 B)
-    # and column id (4 B) per stored nonzero, slice offsets, z read, p and q
-    # read and written. With 16-bit column offsets the kernel reads 10 B per
-    # nonzero, not 12.
+    # CG product q = M z + beta q, p = z + beta p on the free DOF, with the dots
+    # p.q, r.q, q.q, r.r: z and r read, p and q read and written. Where M is stored
+    # by its K upper diagonals, K + 1 values (8 B) per row; else value (8 B) and
+    # column id (4 B) per stored nonzero and slice offsets (with 16-bit column
+    # offsets the kernel reads 10 B per nonzero, not 12).
     n = info["n_free"]
-    return 12 * nnz + 4 * (n // 64 + 1) + 8 * n + 32 * n
+    m = re.search(r"in CG (\d+) upper diagonals", info["layout"])
+    return (8 * (int(m.group(1)) + 1) * n if m else 12 * nnz + 4 * (n // 64 + 1)) + 48 * n
 
 
 def copy_probe(mib=512, reps=20):
@@ -107,7 +110,7 @@ def read_probe(mib=1024, reps=20):
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "c2_hbm_traffic.txt")
-TRAFFIC_SOURCES = [os.path.join(ROOT, "paper_1612_09447_amd", "csrc", f) for f in ("kernels.hip", "sell.h")]
+TRAFFIC_SOURCES = [os.path.join(ROOT, "paper_1612_09447_amd", "csrc", f) for f in ("kernels.hip", "ops.h", "sell.h")]
 
 
 def kernel_source_hash():
@@ -170,14 +173,16 @@ def cpu_model():
 
 
 # kernel classes timed one launch at a time (each launch is one kernel)
-SINGLE_KERNEL_CLASSES = ("element", "spmv_M", "presmooth0", "postsmooth0", "restrict0", "prolong0", "postsmooth1",
+# (the folded cycle's prolongation is part of the launch counted as postsmooth0)
+SINGLE_KERNEL_CLASSES = ("element", "spmv_M", "presmooth0", "postsmooth0", "restrict0", "postsmooth1",
                          "cg_update", "rkc_combine")
-# classes spanning several kernels (bracketed by events on the stream)
-MULTI_KERNEL_CLASSES = ("vcycle", "vcoarse", "finalise")
+# classes spanning several kernels (bracketed by events on the stream); not the
+# finalisers, which a solve only launches when they are timed
+MULTI_KERNEL_CLASSES = ("vcycle", "vcoarse")
 ALL_CLASSES = SINGLE_KERNEL_CLASSES + MULTI_KERNEL_CLASSES
-KERNEL_NAMES = {"element": "k_kx<true> (element pass)", "spmv_M": "k_pcg_spmv", "presmooth0": "k_presmooth_res (finest)",
-                "postsmooth0": "k_postsmooth (finest)", "restrict0": "k_restrict (finest level, R0)",
-                "prolong0": "k_prolong (finest level, P0)", "postsmooth1": "k_postsmooth (level 1)",
+KERNEL_NAMES = {"element": "k_kx_fan / k_kx (element pass)", "spmv_M": "k_pcg_spmv", "presmooth0": "k_presmooth_u (finest)",
+                "postsmooth0": "k_post_fold (finest)", "restrict0": "k_restrict (finest level, R0)",
+                "postsmooth1": "[G Q] product (level 1)",
                 "cg_update": "k_pcg_update",
                 "rkc_combine": "k_rkc_first / k_rkc_combine"}
 
@@ -189,7 +194,7 @@ def class_bytes(info, s_stages):
     n = info["n_free"]
     w = 4 if info["precision"] == 1 else 8
     rows, nnz = info["level_rows"], info["level_nnz"]
-    pn, rn = info["level_p_nnz"], info["level_r_nnz"]
+    rn = info["level_r_nnz"]
     n0 = rows[0]
     out = {
         "element": element_bytes(info),
@@ -198,20 +203,23 @@ def class_bytes(info, s_stages):
         # Y_j from Y_0, Y_{j-1}, Y_{j-2}, F_{j-1}, F_0 (the first stage: Y_0, F_0),
         # the next stage's element-pass output cleared (not after the last)
         "rkc_combine": (32 + 56 * (s_stages - 2) + 48) * n // s_stages,
-        # x = w D^-1 r, res = r - A w D^-1 r: operator, r (FP64), dinv, x, res
-        "presmooth0": (w + 4) * nnz[0] + 4 * (n0 // 64 + 1) + n0 * (8 + 3 * w),
-        # z = x + w D^-1 (r - A x) with r.z and r.z_old: operator, x gathered,
-        # dinv, r (FP64), z_old read, z written
-        "postsmooth0": (w + 4) * nnz[0] + 4 * (n0 // 64 + 1) + n0 * (2 * w + 24),
     }
-    if len(rows) > 1:
-        n1 = rows[1]
-        out["restrict0"] = (w + 4) * rn[0] + 4 * (n1 + 1) + w * n0 + w * n1  # R0, res read, b_1 written
-        out["prolong0"] = (w + 4) * pn[0] + 4 * (n0 + 1) + w * n1 + 2 * w * n0  # P0, x_1 read, x_0 updated
-    if len(rows) > 2:
-        n1 = rows[1]
-        # level 1: out = x + w D^-1 (b - A x): operator, x gathered, dinv, b, out (hierarchy precision)
-        out["postsmooth1"] = (w + 4) * nnz[1] + 4 * (n1 // 64 + 1) + n1 * 4 * w
+    # the folded cycle's operators, from the set-up's description
+    text = info["layout"]
+    dia = re.search(r"A0: (\d+) upper diagonals", text)
+    a0 = w * (int(dia.group(1)) + 1) * n0 if dia else (w + 4) * nnz[0] + 4 * (n0 // 64 + 1)
+    q0 = re.search(r"Q0: \d+ x \d+, (\d+) nonzeros", text)
+    if q0 and "R0(I-AwD^-1)" not in text:
+        # res = r - A w D^-1 r, u = w D^-1 (r + res): operator, r (FP64), w D^-1, res, u
+        out["presmooth0"] = a0 + n0 * (8 + 3 * w)
+        # z = u + Q x_1 with r.z and r.z_old: Q, x_1, u, r and z_old (FP64) read, z written
+        out["postsmooth0"] = (w + 4) * int(q0.group(1)) + 4 * (n0 // 64 + 1) + w * rows[1] + n0 * (w + 24)
+        out["restrict0"] = (w + 4) * rn[0] + 4 * (rows[1] + 1) + w * n0 + w * rows[1]  # R0, res read, b_1 written
+    gq = re.search(r"\[G Q\]1: (\d+) x (\d+), ([\d.]+) nnz/row", text)
+    if gq:
+        # level 1: out = [G Q] [b; x_2]
+        r1, c1 = int(gq.group(1)), int(gq.group(2))
+        out["postsmooth1"] = int((w + 4) * r1 * float(gq.group(3))) + 4 * (r1 // 64 + 1) + w * (r1 + c1)
     return out
 
 
@@ -274,6 +282,7 @@ def run_gpu(case, precision, steps, warmup, rtol, prof_steps=0, guess="previous"
     if guess != "mlp":
         ctx.set_guess(guess)
     info = ctx.info()
+    info["layout"] = ctx.describe()
     assert info["device_bytes"] == 0
     setup_s = time.perf_counter() - t0
     log(f"[bench] setup precision={precision} guess={guess}: {setup_s:.1f}s\n" + ctx.describe())
@@ -581,7 +590,7 @@ def main():
     if prof:
         rooflines = {}
         for k, nbytes in per_class_bytes.items():
-            if not prof[k]["launches"]:
+            if k not in prof or not prof[k]["launches"]:
                 continue
             a = nbytes / (prof[k]["avg_ms"] * 1e-3) / 1e9
             rooflines[k] = {"kernel": KERNEL_NAMES[k], "achieved": round(a, 1), "frac": round(a / HBM_PEAK_GBS, 4),

@@ -208,7 +208,7 @@ int eqs_set_deterministic(eqs_ctx *ctx, int32_t on);
  * graph of `iters` CG iterations, 1..EQS_MAX_GRAPH_ITERS [1]. Iterations that
  * a launch holds past convergence change nothing: their preconditioner cycle
  * runs (its kernels do not test the stop flag, which would cost every one of
- * them a wait), and their SpMV, update and scalar kernels return at entry.
+ * them a wait), their SpMV returns at entry and their update writes nothing.
  * So a large value gives a graph spanning the whole solve at the price of
  * those cycles, a small one lets the host stop at convergence. Results do not
  * depend on it. Takes effect at the next solve; EQS_ERR_INVALID_ARG outside
@@ -502,15 +502,16 @@ enum {
     EQS_KCLASS_ELEMENT = 0,     /* fused element pass: K(x)x / stage right-hand side */
     EQS_KCLASS_SPMV_M = 1,      /* CG product q = M z + beta q (FP64 SpMV on M) */
     EQS_KCLASS_PRESMOOTH0 = 2,  /* finest-level Jacobi pre-smoothing + residual */
-    EQS_KCLASS_POSTSMOOTH0 = 3, /* finest-level Jacobi post-smoothing (+ r.z) */
+    EQS_KCLASS_POSTSMOOTH0 = 3, /* finest-level Jacobi post-smoothing (+ r.z); folded cycle: G r + Q x_1 */
     EQS_KCLASS_VCYCLE = 4,      /* one whole V-cycle */
     EQS_KCLASS_CG_UPDATE = 5,   /* x += alpha p, r -= alpha q (+ |r|^2) */
     EQS_KCLASS_RKC_COMBINE = 6, /* RKC stage combination */
     EQS_KCLASS_RESTRICT0 = 7,   /* finest restriction b_1 = R_0 res (one product) */
-    EQS_KCLASS_PROLONG0 = 8,    /* finest prolongation x_0 += P_0 x_1 (one product) */
+    EQS_KCLASS_PROLONG0 = 8,    /* finest prolongation x_0 += P_0 x_1 (one product; folded: the launch of class 3) */
     EQS_KCLASS_VCOARSE = 9,     /* all V-cycle work below the finest level (several kernels) */
-    EQS_KCLASS_FINALISE = 10,   /* the one-block CG finalisers (three launches per iteration) */
-    EQS_KCLASS_POSTSMOOTH1 = 11, /* level-1 Jacobi post-smoothing (when level 1 is not folded) */
+    EQS_KCLASS_FINALISE = 10,   /* the CG finalisers, which a solve runs where this class is timed (else the
+                                   next kernel takes the sums where it can); three counts per iteration */
+    EQS_KCLASS_POSTSMOOTH1 = 11, /* level-1 post-smoothing (folded cycle: the level-1 product with [G Q]) */
     EQS_KCLASS_COUNT = 12
 };
 

@@ -7,9 +7,11 @@
 //   xyz    double4[n_nodes]     x, y, z, 0 (one 32-byte record per node)
 //   mats   MatDev [n_mat]       eps (absolute), kappa0, 1/e_s, alpha, flags
 //   ddrive int32  [n_dir]       drive id of Dirichlet node n_free + k
-//   M      SELL-64 FP64         M restricted to the free nodes
-//   AMG    per level: SELL-64 A_l, P_l, R_l = P_l^T (FP64 or FP32), 1/diag,
-//          work vectors; a dense inverse at the coarsest level
+//   M      SELL-64 FP64         M restricted to the free nodes; in CG by diagonals
+//          where it has few of them
+//   AMG    per level (FP64 or FP32): Q_l^T and [G Q]_l (the finest level: A_0,
+//          Q_0), a dense operator at the bottom; unfolded: A_l, P_l, R_l = P_l^T,
+//          1/diag, a dense inverse at the coarsest level; work vectors
 //
 // SELL-64: rows are cut into slices of 64 consecutive rows (one wavefront);
 // slice s stores width_s = max row length of its rows, rounded up to even, in
@@ -164,7 +166,7 @@ struct PcgStep {
     int32_t pad;
 };
 
-// Summary of all instances' CG states (written by the finalisers).
+// Summary of all instances' CG states (written by the update or the finalisers).
 struct PcgSummary {
     int32_t all_done;
     int32_t n_active;
@@ -340,7 +342,7 @@ struct eqs_ctx {
     eqs::PcgScalars* d_scal = nullptr;   // [n_inst]
     eqs::PcgStep* d_step = nullptr;      // [n_inst]
     eqs::PcgSummary* d_sum = nullptr;
-    eqs::PcgScalars* h_scal = nullptr;   // pinned host mirror of d_scal, written by the finalisers
+    eqs::PcgScalars* h_scal = nullptr;   // pinned host mirror of d_scal, written with the summary
     eqs::PcgScalars* d_hscal = nullptr;  // its device-side address
     eqs::PcgSummary* h_sum = nullptr;    // pinned host mirror of the summary
     eqs::PcgSummary* d_hsum = nullptr;

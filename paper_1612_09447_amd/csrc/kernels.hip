@@ -8,10 +8,11 @@
 //  * SELL and CSR sparse products with fused epilogues for CG on M and for
 //    the smoothed-aggregation V-cycle (damped Jacobi, restriction,
 //    prolongation, dense coarsest solve), including the folded operators the
-//    host forms at set-up (a restriction with the pre-smoother inside, the two
-//    lowest levels as one dense and one sparse product).
-//  * CG vector updates with block partial sums; one-block finalisers turn the
-//    partials into the CG scalars, kept in device memory.
+//    host forms at set-up (two products per level, one dense operator at the
+//    bottom).
+//  * CG vector updates with block partial sums, which the next kernel (or, for
+//    large batches, a finaliser launch) turns into the CG scalars, kept in device
+//    memory.
 //  * RKC stage combination (the paper's ref. [9]).
 #include <algorithm>
 #include <cmath>

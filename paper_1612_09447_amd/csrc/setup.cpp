@@ -1992,9 +1992,12 @@ void upload(eqs_ctx* c) {
     guess_alloc_scratch(c);  // eqs_galerkin_start's dot scratch
     launch_fill(c->stream, c->d_Y0, 0.0, NF);
     build_element_blocks(c, u2i, c->d_Y0, c->d_rhs);
-    if (!c->tune_file.empty() && c->tune_replay.empty() && !c->tune_record.empty()) {
+    if (!c->tune_file.empty() && c->tune_replay.empty() && c->autotune) {
         FILE* f = std::fopen(c->tune_file.c_str(), "w");
         if (!f) fail(EQS_ERR_INVALID_ARG, "tuning record: cannot write " + c->tune_file);
+        // a line without a tab is no entry: a build that timed nothing leaves a record all the
+        // same, and the next one that does replaces it
+        if (c->tune_record.empty()) std::fprintf(f, "# every layout of this build follows from sizes\n");
         for (const std::string& ln : c->tune_record) std::fprintf(f, "%s\n", ln.c_str());
         std::fclose(f);
     }

@@ -4,9 +4,10 @@
 // pass (Sec. III) plus one M-solve.
 //
 // CG keeps all scalars on the device. The host enqueues iteration k+1 before
-// it waits for iteration k, and reads only a "done" flag that the
-// convergence finaliser writes to pinned host memory, so the GPU never idles
-// between iterations; once done, further kernels exit at entry.
+// it waits for iteration k, and reads only the summary that the update of the
+// first rows (or the last finaliser) writes to pinned host memory, so the GPU
+// never idles between iterations; once done, further iterations change nothing.
+// Small single systems solve in one launch (small.hip).
 #include <algorithm>
 #include <cmath>
 #include <functional>
