@@ -67,3 +67,30 @@ def test_fans_match_oracle_and_single_tets(n, whole, shuffled, generic, monkeypa
             st, steps = c.rkc_adaptive(0.0, 4 * case.tau, full, 1e-10, 1e-6, 1e-4, case.tau)
             got.append([q["s"] for q in steps])
     assert got[0] == got[1]
+
+
+def test_fans_in_a_tuning_record(tmp_path, monkeypatch):
+    """The record names fans and replays them; a context that takes none (the
+    deterministic pass) takes a block size without timing, the same every time; a
+    record of a block size is followed where fans would be taken."""
+    case = eqsgen.case_c1(n=59, seed=4)
+    rec = tmp_path / "tune.txt"
+    monkeypatch.setenv("EQS_TUNE_FILE", str(rec))
+    for k in range(2):
+        with make_ctx(case, monkeypatch, True) as c:
+            assert c.describe().count("fans per block") == 1
+            assert ("fans) (tuning record)" in c.describe().replace("a fan)", "a fans)")) == (k == 1)
+    line = [ln for ln in rec.read_text().splitlines() if ln.startswith("element ")]
+    assert len(line) == 1 and line[0].endswith("\tfans")
+    c = Context(0, torch.cuda.current_stream(DEV))
+    c.setup_case(case, precision=EQS_PREC_FP32, deterministic=True)
+    assert "element: 1024 tets per block (tuning record)" in c.describe()
+    c.close()
+    rec.write_text(rec.read_text().replace("\tfans", "\t2"))
+    with make_ctx(case, monkeypatch, False) as c:
+        assert "element: 512 tets per block (tuning record)" in c.describe()
+    monkeypatch.setenv("EQS_FANS", "1")
+    c = Context(0, torch.cuda.current_stream(DEV))
+    c.setup_case(case, precision=EQS_PREC_FP32)
+    assert "element: 512 tets per block (tuning record)" in c.describe()
+    c.close()

@@ -199,3 +199,31 @@ def test_columns_from_a_base_per_pair(precision, monkeypatch):
     tol = 1e-13 if precision == EQS_PREC_FP64 else 2e-6  # some 50 terms of 2^-53, 2^-24 each
     for v in z[1:]:
         assert np.linalg.norm(v - z[0]) <= tol * np.linalg.norm(z[0])
+
+
+@pytest.mark.parametrize("graph_iters", [1, 3])
+@pytest.mark.parametrize("n", [8, 23, 47])
+def test_captured_iterations_match_plain_launches(n, graph_iters):
+    """On a stream of its own a context replays captured iterations; on the null
+    stream it launches them one by one. Several solves in a row, each against the
+    true residual, and steps in between."""
+    case = eqsgen.case_c1(n=n, seed=1)
+    o = EqsOracle(case, dense_limit=0)
+    rng = np.random.default_rng(8)
+    rhs = [o.M_II @ rng.standard_normal(o.n_free) for _ in range(3)]
+    out = []
+    for stream in (torch.cuda.current_stream(DEV), torch.cuda.Stream(DEV)):
+        with torch.cuda.stream(stream):
+            c = Context(0, stream)
+            c.setup_case(case, precision=EQS_PREC_FP32)
+            c.set_graph_iters(graph_iters)
+            x = torch.zeros(case.n_nodes, dtype=torch.float64, device=DEV)
+            its = []
+            for k, b in enumerate(rhs):
+                its.append(solve(c, o, b, np.zeros(o.n_free))[0])
+                c.rkc_step(k * case.tau, case.tau, 8, x, 1e-12)
+            stream.synchronize()
+            out.append((its, x.cpu().numpy()))
+            c.close()
+    assert max(abs(p - q) for p, q in zip(out[0][0], out[1][0])) <= 1
+    assert np.linalg.norm(out[0][1] - out[1][1]) <= 1e-9 * np.linalg.norm(out[0][1])
