@@ -114,7 +114,8 @@ struct SpMat {
     int32_t n_rows = 0, n_cols = 0;
     int32_t* rowptr = nullptr;  // CSR
     int32_t* col = nullptr;     // absolute column ids, or
-    int16_t* d16 = nullptr;     // offsets from offset_base(row) when every entry allows
+    int16_t* d16 = nullptr;     // offsets from offset_base(row) when every entry allows, or (rbase)
+    int32_t* rbase = nullptr;   // from the row's own base
     T* val = nullptr;
     int64_t nnz = 0;
 };

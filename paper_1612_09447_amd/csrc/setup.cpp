@@ -615,6 +615,7 @@ static void visit_spmat(SpMat<T>& A, const std::function<void(void**)>& f) {
     f((void**)&A.rowptr);
     f((void**)&A.col);
     f((void**)&A.d16);
+    f((void**)&A.rbase);
     f((void**)&A.val);
 }
 template <typename T>
@@ -902,7 +903,7 @@ template Sell<double> to_sell<double>(eqs_ctx*, const Csr<double>&, int, bool, c
 template Sell<float> to_sell<float>(eqs_ctx*, const Csr<double>&, int, bool, const Csr<double>*, int32_t);
 
 // CSR column ids: 16-bit offsets from offset_base(row) when every entry
-// allows, else absolute.
+// allows, else from a base of the row's own, else absolute.
 template <typename T>
 static void upload_csr_cols(eqs_ctx* c, SpMat<T>& S, const Csr<double>& A) {
     bool fits = c->index16 && A.n_cols > 0;
@@ -920,6 +921,18 @@ static void upload_csr_cols(eqs_ctx* c, SpMat<T>& S, const Csr<double>& A) {
                 d16[k] = (int16_t)d;
             }
         }
+    }
+    if (!fits && c->index16 && A.n_cols > 0) {  // from a base of each row, where no row spans more than 65535
+        std::vector<int32_t> rbase((size_t)A.n_rows, 0);
+        fits = true;
+        for (int32_t r = 0; r < A.n_rows && fits; ++r) {
+            if (A.ptr[r] == A.ptr[r + 1]) continue;
+            const auto mm = std::minmax_element(A.col.begin() + A.ptr[r], A.col.begin() + A.ptr[r + 1]);
+            fits = *mm.second - *mm.first <= 65535;
+            rbase[(size_t)r] = *mm.first + 32768;
+            for (int32_t k = A.ptr[r]; k < A.ptr[r + 1] && fits; ++k) d16[(size_t)k] = (int16_t)(A.col[k] - rbase[(size_t)r]);
+        }
+        if (fits) S.rbase = upload_vec(c, rbase);
     }
     if (fits) S.d16 = upload_vec(c, d16);
     else S.col = upload_vec(c, A.col);
@@ -1069,6 +1082,7 @@ static void free_spmat(eqs_ctx* c, SpMat<T>& S) {
     dev_free(c, S.rowptr);
     dev_free(c, S.col);
     dev_free(c, S.d16);
+    dev_free(c, S.rbase);
     dev_free(c, S.val);
     S = SpMat<T>{};
 }
@@ -1226,7 +1240,7 @@ static SpMat<T> tuned_spmat(eqs_ctx* c, const Csr<double>& A, const char* what, 
         S.rowptr = upload_vec(c, A.ptr);
         upload_csr_cols(c, S, A);
         S.val = upload_vec(c, v);
-        consider(S, std::string("csr") + std::to_string(L) + (S.d16 ? "/i16" : ""));
+        consider(S, std::string("csr") + std::to_string(L) + (S.rbase ? "/r16" : S.d16 ? "/i16" : ""));
     }
     dev_free(c, x);
     dev_free(c, y);

@@ -386,7 +386,7 @@ static void launch(hipStream_t s, eqs_ctx* c, Hierarchy<T>& h, const double* rhs
                           pad(sizeof(T) * (size_t)l1.n * l1.n);
     const size_t fine = pad(4 * (size_t)(l0.Q.sell.n_slices + 1)) + pad(2 * (size_t)a.q_stored) +
                         pad(sizeof(T) * (size_t)a.q_stored) + pad(sizeof(T) * (size_t)l0.n);
-    const bool d16 = a.Rt.d16 && a.Q.d16 && !a.Q.pbase;
+    const bool d16 = a.Rt.d16 && a.Q.d16 && !a.Q.pbase && !a.Rt.rbase;
     const int stage = !d16 ? kStageNone : base + coarse + fine <= kSmallLds ? kStageAll
                                       : base + coarse <= kSmallLds          ? kStageCoarse : kStageNone;
     const size_t lds = base + (stage != kStageNone ? coarse : 0) + (stage == kStageAll ? fine : 0);
