@@ -2017,10 +2017,14 @@ __global__ __launch_bounds__(256, PRO ? 4 : kSparseWaves) void k_pcg_spmv(
     const int64_t B = op.block();
     int32_t lo, bound;
     block_instances(m, lo, bound, B);
-    if (stop && *stop) {  // past convergence: nothing to do here, and nothing for the update
+    if (stop && *stop) {  // past convergence: nothing to do here, and nothing for the update but x = 0 (bb)
         if (PRO && threadIdx.x == 0) {
-            if (ONE ? B == 0 : (m.row_off[lo] >> 8) == B) step[lo].done = 1;
-            if (!ONE && lo + 1 < m.n_inst && (bound >> 8) == B) step[lo + 1].done = 1;
+            auto finished = [&](int32_t i) {
+                step[i].done = 1;
+                step[i].bb = scal[i].bb;  // this solve's: the record may be an earlier one's
+            };
+            if (ONE ? B == 0 : (m.row_off[lo] >> 8) == B) finished(lo);
+            if (!ONE && lo + 1 < m.n_inst && (bound >> 8) == B) finished(lo + 1);
         }
         return;
     }

@@ -1984,6 +1984,7 @@ void upload(eqs_ctx* c) {
     c->d_partials = vec(12 * c->max_blocks);
     c->d_scal = (PcgScalars*)dev_alloc(c, sizeof(PcgScalars) * (size_t)c->n_inst);
     c->d_step = (PcgStep*)dev_alloc(c, sizeof(PcgStep) * (size_t)c->n_inst);
+    EQS_HIP(hipMemset(c->d_step, 0, sizeof(PcgStep) * (size_t)c->n_inst));
     c->d_sum = (PcgSummary*)dev_alloc(c, sizeof(PcgSummary));
     EQS_HIP(hipMemset(c->d_sum, 0, sizeof(PcgSummary)));
     c->d_force = (int32_t*)dev_alloc(c, sizeof(int32_t));
