@@ -242,7 +242,7 @@ __device__ __forceinline__ void for_each_instance_sum(const double* const (&part
 // pro_blocks(kProBig) workgroups. (1024-thread workgroups instead: the update at
 // 2.1M rows 127 us instead of 20, their registers spill.)
 constexpr int pro_blocks(int u) { return 256 * u + 1; }
-constexpr int kProSmall = 5, kProBig = 9;  // loads per thread and array (the update of a large system: 4)
+constexpr int kProSmall = 5, kProBig = 9, kProUpdate = 4;  // loads per thread and array (the last: update of a large system)
 template <int NP, int U>
 struct ProParts {
     double t[NP][U], h[NP];
@@ -2526,8 +2526,7 @@ void pcg_true_residual(hipStream_t s, eqs_ctx* c, const double* rhs, const doubl
 void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int precision) {
     (void)rhs;
     using OpT = double;
-    const PartShape ps = part_shape(c), ps_spmv = part_shape(c, true);
-    const bool big = ps.grid > (unsigned)pro_blocks(kProSmall);
+    const PartShape ps_spmv = part_shape(c, true);
     // With one iteration per graph the SpMV does not test the stop flag either (the V-cycle never does; see
     // vcycle): an iteration past convergence is rarely launched (the host waits once the residuals extrapolate to
     // rtol), and it writes only partials and p and q (x and r are guarded by the instance's state). With several
@@ -2541,8 +2540,12 @@ void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int 
     const InstMap im = inst_map(c), im_spmv = inst_map(c, true), im_upd = inst_map(c, true, true);
     const bool one = im.rows1 >= 0;
     const DotParts D{part(c, 2), part(c, 3), part(c, 4), part(c, 5)};
-    // the consumers reduce (pro_load); the finalisers' own time is only seen with launches of their own
-    const bool pro = ps.grid <= (unsigned)pro_blocks(one ? kProBig : kProSmall) && !(c->prof_mask & (1u << EQS_KCLASS_FINALISE));
+    // the consumers reduce where their loads cover the partials they read (the plain cycle's one row per thread leaves
+    // the update up to 2305 of them); the finalisers' own time is only seen with launches of their own
+    const bool big = one && im_spmv.nparts > pro_blocks(kProSmall);
+    const bool pro = im_spmv.nparts <= pro_blocks(big ? kProBig : kProSmall) &&
+                     im_upd.nparts <= pro_blocks(big ? kProUpdate : kProSmall) &&
+                     !(c->prof_mask & (1u << EQS_KCLASS_FINALISE));
     const dim3 fg(fin_grid(c));
     if (!pro)
         EQS_LAUNCH_TIMED(c, EQS_KCLASS_FINALISE, one ? k_fin_beta<true> : k_fin_beta<false>, fg, dim3(kFin), 0, s,
@@ -2568,7 +2571,7 @@ void pcg_iteration(hipStream_t s, eqs_ctx* c, const double* rhs, double* x, int 
     }
     EQS_LAUNCH_TIMED(c, EQS_KCLASS_CG_UPDATE,
                      (pro ? (!one  ? k_pcg_update<false, kProSmall>
-                             : big ? k_pcg_update<true, 4>
+                             : big ? k_pcg_update<true, kProUpdate>
                                    : k_pcg_update<true, kProSmall>)
                           : (one ? k_pcg_update<true, 0> : k_pcg_update<false, 0>)),
                      dim3(ps_spmv.grid), dim3(kBlock), 0, s, im_upd, x, c->d_r, c->d_p, c->d_q, c->n_free, D, c->d_scal, c->d_step,

@@ -103,3 +103,28 @@ def test_solves_without_an_iteration(make, precision, graph_iters, own_stream, c
                     assert float(torch.linalg.vector_norm((part - r)[a:b])) <= (RTOL + 1e-13) * float(
                         torch.linalg.vector_norm(part[a:b]))
             stream.synchronize()
+
+
+@pytest.mark.parametrize("n", [68, 69, 83, 84])
+def test_plain_cycle_on_many_row_blocks(n, monkeypatch):
+    """The plain cycle takes one row per thread whatever the size: 1,247, 1,302, 2,261
+    and 2,343 row blocks, on both sides of the counts up to which the next kernel
+    sums them (1,281 and 2,305). Solved to the true residual, in as many iterations
+    as with finaliser launches, up to the one that rounding can cost."""
+    monkeypatch.setenv("EQS_FOLD", "0")
+    monkeypatch.setenv("EQS_AUTOTUNE", "0")
+    with Context(0, torch.cuda.current_stream(DEV)) as c:
+        c.setup_case(eqsgen.case_c1(n=n, seed=1), precision=EQS_PREC_FP32)
+        rng = np.random.default_rng(10)
+        xs = torch.as_tensor(rng.standard_normal(c.info()["n_free"]), device=DEV)
+        rhs, r, its = torch.empty_like(xs), torch.empty_like(xs), []
+        c.apply_M(xs, rhs)
+        for classes in ((), ("finalise",)):
+            y = torch.zeros_like(xs)
+            c.profile_enable(classes)
+            its.append(c.solve_M(rhs, y, RTOL, maxit=200)["iters"])
+            c.profile_enable(())
+            c.apply_M(y, r)
+            res = float(torch.linalg.vector_norm(rhs - r) / torch.linalg.vector_norm(rhs))
+            assert res <= RTOL + 1e-13, res
+    assert abs(its[0] - its[1]) <= 1, its
