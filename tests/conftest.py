@@ -24,6 +24,11 @@ def pytest_configure(config):
                                        "started in the background when the test is selected")
 
 
+def pytest_collection_modifyitems(items):
+    """The sanitizer driver's runs go last: where one does not end, the other files have run."""
+    items.sort(key=lambda item: "test_gpu_sanitize" in item.nodeid)
+
+
 def pytest_collection_finish(session):
     """Start the oracle reference runs that the selected tests need, so that
     they compute while the tests before them run."""

@@ -14,9 +14,13 @@
 // Prints "SANITIZE OK <mode>" and exits 0 when every check held; a check that
 // fails exits 1, and a sanitizer finding aborts the process.
 #include <hip/hip_runtime.h>
+#include <sanitizer/common_interface_defs.h>
+#include <unistd.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
+#include <csignal>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -49,10 +53,28 @@ void check(bool ok, const char* what, int line) {
     } while (0)
 #define HIPOK(call) check((call) == hipSuccess, #call, __LINE__)
 
-// progress line before each part, so that the log names the part a failure is in
+// progress line before each part with the seconds since the start, so that the log
+// names the part a failure is in and tells a slow run from one that stopped
+const char* g_part = "start";
 void part(const char* name) {
-    std::printf("[sanitize] %s\n", name);
+    static const auto t0 = std::chrono::steady_clock::now();
+    g_part = name;
+    std::printf("[sanitize] %6.2f s  %s\n", std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count(),
+                name);
     std::fflush(stdout);
+}
+
+// A run that does not end by itself says where its host code is and exits, before
+// the caller's limit kills it without a word: with the main thread's stack, a wait
+// for the GPU, a loop of the library and the leak check at exit can be told apart.
+constexpr unsigned kLimitSeconds = 100;  // the callers' limits are 110 and 120
+extern "C" void on_limit(int) {
+    static const char msg[] = "[sanitize] no end within the limit; the main thread is in part: ";
+    (void)!write(2, msg, sizeof msg - 1);
+    (void)!write(2, g_part, std::strlen(g_part));
+    (void)!write(2, "\n", 1);
+    __sanitizer_print_stack_trace();
+    _exit(97);
 }
 
 // ------------------------------------------------------------- inputs
@@ -798,12 +820,16 @@ void run_abi() {
 
 int main(int argc, char** argv) {
     const std::string mode = argc > 1 ? argv[1] : "";
+    std::signal(SIGALRM, on_limit);
+    alarm(kLimitSeconds);
     if (mode == "host") run_host();
     else if (mode == "abi") run_abi();
     else {
         std::fprintf(stderr, "usage: %s host|abi\n", argv[0]);
         return 2;
     }
+    part("end of the checks");
     std::printf("SANITIZE OK %s (%d checks)\n", mode.c_str(), g_checks);
+    std::fflush(stdout);  // ahead of the leak check at exit
     return 0;
 }

@@ -43,7 +43,12 @@ def run(mode, timeout, extra_env=None):
         if k.startswith("EQS_"):
             del env[k]
     env.update(extra_env or {})
-    r = subprocess.run([b.SAN_EXE, mode], capture_output=True, text=True, timeout=timeout, env=env)
+    try:
+        r = subprocess.run([b.SAN_EXE, mode], capture_output=True, text=True, timeout=timeout, env=env)
+    except subprocess.TimeoutExpired as e:  # what it had printed names the part it was in
+        for o in (e.stdout, e.stderr):
+            print((o or b"")[-6000:].decode(errors="replace") if not isinstance(o, str) else o[-6000:], flush=True)
+        raise
     out = r.stdout + r.stderr
     print(out[-6000:], flush=True)
     assert "ERROR: AddressSanitizer" not in out and "ERROR: LeakSanitizer" not in out, "AddressSanitizer finding"
