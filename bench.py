@@ -42,23 +42,40 @@ def log(*a):
 
 
 def element_bytes(info):
-    # algorithmic bytes of one element pass: per tet its connectivity (4 x 4 B)
-    # and material id (4 B); per node its coordinates (24 B), potential (8 B)
-    # and result (8 B), each array touched once. The library's packed tet
-    # records need 8 B instead of 20; re-reads of nodes shared between element
-    # blocks and the block node lists are overhead, not counted.
-    return info["n_tets"] * 20 + info["n_nodes"] * (24 + 8 + 8)
+    # bytes of one element pass, each stored array once: the blocks' records (16 B
+    # per fan of up to six tets, else 8 B per first-order and 16 B per second-order
+    # tet) and node lists (4 B); per node its coordinates (24 B), potential (8 B)
+    # and result (8 B). Re-reads of nodes shared between blocks are overhead, not
+    # counted.
+    m = re.search(r"element blocks (\d+) of (up to )?(\d+) tets, block nodes (\d+)", info["layout"])
+    blocks, block_nodes = int(m.group(1)), int(m.group(4))
+    record = 16 * 256 if m.group(2) else (16 if "(10 nodes each)" in info["layout"] else 8) * int(m.group(3))
+    return blocks * record + 4 * (block_nodes + blocks + 1) + info["n_nodes"] * (24 + 8 + 8)
 
 
 def spmv_bytes(info, nnz):
     # CG product q = M z + beta q, p = z + beta p on the free DOF, with the dots
     # p.q, r.q, q.q, r.r: z and r read, p and q read and written. Where M is stored
     # by its K upper diagonals, K + 1 values (8 B) per row; else value (8 B) and
-    # column id (4 B) per stored nonzero and slice offsets (with 16-bit column
-    # offsets the kernel reads 10 B per nonzero, not 12).
+    # column (2 or 4 B) per nonzero and slice offsets.
     n = info["n_free"]
-    m = re.search(r"in CG (\d+) upper diagonals", info["layout"])
-    return (8 * (int(m.group(1)) + 1) * n if m else 12 * nnz + 4 * (n // 64 + 1)) + 48 * n
+    text = info["layout"]
+    m = re.search(r"in CG (\d+) upper diagonals", text)
+    col = 2 if re.search(r"^M: .*16-bit column offsets", text, re.M) else 4
+    return (8 * (int(m.group(1)) + 1) * n if m else (8 + col) * nnz + 4 * (n // 64 + 1)) + 48 * n
+
+
+def operator_bytes(info, name, rows, nnz, w):
+    """Bytes of a tuned operator as stored: w-byte values, 2-byte columns where its
+    line in the set-up's description says so (/i16; /p16, with 4 bytes per 64 pairs;
+    /r16, with 4 per row), else 4-byte ones, and its row or slice offsets. None
+    where the line does not say (a layout taken from a record or a switch)."""
+    m = re.search(rf"^{re.escape(name)}: .* -> (sell64(?:x(\d))?|csr)[^/ ]*(?:/([ipr]16))?", info["layout"], re.M)
+    if not m:
+        return None
+    ptr = 4 * (rows + 1) if m.group(1) == "csr" else 4 * (rows * int(m.group(2) or 1) // 64 + 1)
+    base = {"p16": nnz // 32, "r16": 4 * rows}.get(m.group(3), 0)
+    return (w + (2 if m.group(3) else 4)) * nnz + base + ptr
 
 
 def copy_probe(mib=512, reps=20):
@@ -189,8 +206,9 @@ KERNEL_NAMES = {"element": "k_kx_fan / k_kx (element pass)", "spmv_M": "k_pcg_sp
 
 def class_bytes(info, s_stages):
     """Algorithmic bytes per launch of every single-kernel class: each array
-    the kernel must touch, once, at its own width (4 B per index; hierarchy
-    values 4 B in the FP32 form, 8 B in FP64; CG vectors 8 B)."""
+    the kernel must touch, once, at the width it is stored in (hierarchy values
+    4 B in the FP32 form, 8 B in FP64; CG vectors 8 B; columns as the set-up's
+    description says); padding entries are not counted."""
     n = info["n_free"]
     w = 4 if info["precision"] == 1 else 8
     rows, nnz = info["level_rows"], info["level_nnz"]
@@ -207,19 +225,25 @@ def class_bytes(info, s_stages):
     # the folded cycle's operators, from the set-up's description
     text = info["layout"]
     dia = re.search(r"A0: (\d+) upper diagonals", text)
-    a0 = w * (int(dia.group(1)) + 1) * n0 if dia else (w + 4) * nnz[0] + 4 * (n0 // 64 + 1)
-    q0 = re.search(r"Q0: \d+ x \d+, (\d+) nonzeros", text)
+    col = 2 if re.search(r"^A0: .*16-bit column offsets", text, re.M) else 4
+    a0 = w * (int(dia.group(1)) + 1) * n0 if dia else (w + col) * nnz[0] + 4 * (n0 // 64 + 1)
+    q0 = re.search(r"^Q0: \d+ x \d+, (\d+) nonzeros.*?(16|32)-bit", text, re.M)
     if q0 and "R0(I-AwD^-1)" not in text:
         # res = r - A w D^-1 r, u = w D^-1 (r + res): operator, r (FP64), w D^-1, res, u
         out["presmooth0"] = a0 + n0 * (8 + 3 * w)
         # z = u + Q x_1 with r.z and r.z_old: Q, x_1, u, r and z_old (FP64) read, z written
-        out["postsmooth0"] = (w + 4) * int(q0.group(1)) + 4 * (n0 // 64 + 1) + w * rows[1] + n0 * (w + 24)
-        out["restrict0"] = (w + 4) * rn[0] + 4 * (rows[1] + 1) + w * n0 + w * rows[1]  # R0, res read, b_1 written
-    gq = re.search(r"\[G Q\]1: (\d+) x (\d+), ([\d.]+) nnz/row", text)
+        out["postsmooth0"] = ((w + int(q0.group(2)) // 8) * int(q0.group(1)) + 4 * (n0 // 64 + 1) + w * rows[1]
+                              + n0 * (w + 24))
+        r0 = operator_bytes(info, "R0", rows[1], rn[0], w)
+        if r0:
+            out["restrict0"] = r0 + w * n0 + w * rows[1]  # R0, res read, b_1 written
+    gq = re.search(r"^\[G Q\]1: (\d+) x (\d+), ([\d.]+) nnz/row", text, re.M)
     if gq:
         # level 1: out = [G Q] [b; x_2]
         r1, c1 = int(gq.group(1)), int(gq.group(2))
-        out["postsmooth1"] = int((w + 4) * r1 * float(gq.group(3))) + 4 * (r1 // 64 + 1) + w * (r1 + c1)
+        g1 = operator_bytes(info, "[G Q]1", r1, int(r1 * float(gq.group(3))), w)
+        if g1:
+            out["postsmooth1"] = g1 + w * (r1 + c1)
     return out
 
 
@@ -411,9 +435,7 @@ def run_p2(n, steps, warmup, prof_steps=1):
            "mean_cg_iters_per_stage": round(sum(r["iters"]) / len(r["iters"]), 2), "amg_levels": info["level_rows"]}
     if r["prof"]:
         el = r["prof"]["element"]
-        # per tet its ten node ids (40 B) and material (4 B); per node 24 B
-        # coordinates, 8 B potential, 8 B result
-        nbytes = info["n_tets"] * 44 + info["n_nodes"] * 40
+        nbytes = element_bytes(info)
         a = nbytes / (el["avg_ms"] * 1e-3) / 1e9
         out["element_pass"] = {"avg_launch_us": round(el["avg_ms"] * 1e3, 2), "bytes_per_launch": nbytes,
                                "achieved_GBs": round(a, 1), "frac": round(a / HBM_PEAK_GBS, 4)}
@@ -427,7 +449,7 @@ def run_p2(n, steps, warmup, prof_steps=1):
 def run_batched(steps, warmup, graph_iters=(1, 64)):
     """The batched workload: 64 independent instances (n in {16..48}^3) packed
     into one context, RKC(8) steps of all of them together, timed once per
-    launch granularity in `graph_iters` (CG iterations per captured graph: 1,
+    launch granularity in `graph_iters` (CG iterations queued at a time: 1,
     and one that spans a whole stage solve), each from rest over the same
     steps."""
     import torch
@@ -467,7 +489,7 @@ def run_batched(steps, warmup, graph_iters=(1, 64)):
                    "cg_iters_per_instance_stage": {"min": round(float(res["iters"].min()) / (steps * s), 2),
                                                    "max": round(float(res["iters"].max()) / (steps * s), 2)}}
         finals[g] = torch.cat(xs)
-        log(f"[bench] batched, {g} CG iterations per graph: {runs[g]['stages_per_s_aggregate']} instance-stages/s")
+        log(f"[bench] batched, {g} CG iterations per launch: {runs[g]['stages_per_s_aggregate']} instance-stages/s")
     b.close()
     g0 = graph_iters[0]
     best = max(runs, key=lambda g: runs[g]["stages_per_s_aggregate"])
@@ -517,14 +539,16 @@ def main():
     ap.add_argument("--prof-steps", type=int, default=3, help="instrumented steps after the timed ones")
     ap.add_argument("--guess", default="previous", choices=["previous", "zero", "galerkin", "mor", "mlp"])
     ap.add_argument("--mlp-seed", type=int, default=4, help="seed of the start-vector network's initial weights")
-    ap.add_argument("--graphs", type=int, default=1, help="replay CG iterations as a captured HIP graph")
+    ap.add_argument("--graphs", type=int, default=1,
+                    help="replay CG iterations as a captured HIP graph where the context's stream allows it (the "
+                         "null stream, which this run uses, launches them one by one)")
     ap.add_argument("--flexible", type=int, default=0, help="CG beta: 0 default, 1 Polak-Ribiere, 2 Fletcher-Reeves")
-    ap.add_argument("--graph-iters", type=int, default=1, help="CG iterations per captured graph launch")
+    ap.add_argument("--graph-iters", type=int, default=1, help="CG iterations per launch")
     ap.add_argument("--metrics-jsonl", default="",
                     help="append one JSON line per timed step of the main run to this file")
     ap.add_argument("--c3-steps", type=int, default=5, help="also time the 64-instance batched workload (0: skip)")
     ap.add_argument("--c3-graph-iters", default="1,64",
-                    help="CG iterations per graph launch for the batched workload, one timed run each (comma list)")
+                    help="CG iterations per launch for the batched workload, one timed run each (comma list)")
     ap.add_argument("--mlp-batch", type=int, default=256, help="network training pairs per stage (<= 256)")
     ap.add_argument("--mlp-warmup", type=int, default=64,
                     help="training pairs collected before the network's start vector is used")
@@ -677,8 +701,9 @@ def main():
             "start_vector": args.guess,
             "guess_used": r["used"],
             "guess_fallbacks": r["fallbacks"],
-            "graphs": bool(args.graphs),
-            "cg_iters_per_graph_launch": args.graph_iters,
+            # captured iterations need a stream of the caller's own: on the null stream they are launched one by one
+            "graphs": bool(args.graphs) and torch.cuda.current_stream().cuda_stream != 0,
+            "cg_iters_per_launch": args.graph_iters,
             "mean_cg_iters_per_stage": round(sum(r["iters"]) / len(r["iters"]), 2),
             "cg_iters_per_stage": stage_iter_stats(r["stage_iters"]),
             "amg_levels": info["level_rows"],
