@@ -139,8 +139,7 @@ struct DriveDev {
 struct PcgScalars {
     double bb;       // |rhs|^2
     double rr;       // |r|^2
-    double rho;      // r.z of the current iteration
-    double rho_old;  // r.z of the previous iteration
+    double rho;      // r.z of the latest iteration
     double beta;
     double alpha;
     double tol2;     // (rtol |rhs|)^2
@@ -366,7 +365,7 @@ struct eqs_ctx {
     bool fan_pass = true;   // the element pass may walk fans of tets
     bool small = true;      // small systems solve in one launch
     bool diagonals = true;  // matrices of few diagonals are stored by them
-    bool fold = true;       // fold pre-smoothers into restrictions and the lowest two levels into two products
+    bool fold = true;       // V-cycles by folded operators (upload_folded in setup.cpp)
     int force_layout = -1;      // >= 1: SELL with that many lanes per row, 0: CSR, for every coarse operator
     bool force_sorted = false;  // with force_layout >= 1: sorted rows where allowed
     int force_unroll = 8;       // with force_layout >= 1: group size of the coarse operators (see Sell::unroll)

@@ -625,10 +625,12 @@ __global__ __launch_bounds__(kTetBlock, 6) void k_kx(KxArgs A) {
 // 9 nodes and adds to 9 accumulators where six single tets read and add 24, and
 // needs two cross products a tet instead of three; its record is 16 bytes instead
 // of 48. The single-tet form is bound by those LDS gathers and atomics (half of
-// its time) and by the records (100 of its 200 MB at 12.6M tets). There the fan
-// pass takes 75 us instead of 87, and 68 when every exponent is a whole number;
-// what is left is the latency of staging and scatter at 5 blocks per CU and
-// exp(alpha ln r) in the blocks that need it.
+// its time) and by the records (100 of its 200 MB at 12.6M tets). Launched back to
+// back there, the fan pass takes 75 us and the single-tet form 78 (83 with its
+// nodes staged round by round); with whole exponents only, 69. Between the other
+// kernels of a step, with cold caches, it takes 81 to 85. What is left is the
+// latency of staging and scatter at 5 blocks per CU and exp(alpha ln r) in the
+// blocks that need it.
 template <bool RHS, int STRIDE>
 __device__ __forceinline__ void kx_fan(const KxArgs& A, double* lds, int32_t nn, bool has_dir, uint64_t lo, uint64_t hi) {
     const int32_t S = kx_stride<STRIDE>(nn);
@@ -2258,7 +2260,7 @@ __device__ __forceinline__ void single_instance_sums(const double* const (&parts
 // force (may be NULL): a one-shot flag for tests of the restart path; when
 // set, this check treats every instance as not yet converged (it then
 // continues from its true residual) and clears the flag. ONE: a single
-// instance (its scalars handled field by field, as in k_fin_conv).
+// instance (its scalars handled field by field, as in k_fin_step).
 template <bool ONE>
 __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, InstMap m, const double* __restrict__ prr,
                                                      const double* __restrict__ pbb, double rtol, int32_t maxit,
@@ -2272,7 +2274,7 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
         const int32_t all_done = vec_load(&sum->all_done);
         const int32_t force_raw = vec_load(force ? (const int32_t*)force : &sum->all_done);
         const PcgScalars* p = s;
-        double rho = vec_load(&p->rho), rho_old = vec_load(&p->rho_old), alpha = vec_load(&p->alpha);
+        double rho = vec_load(&p->rho), alpha = vec_load(&p->alpha);
         double tol2 = vec_load(&p->tol2), rr = vec_load(&p->rr), relres = vec_load(&p->relres);
         double beta = vec_load(&p->beta), bb = vec_load(&p->bb);
         int32_t it = vec_load(&p->it), mx = vec_load(&p->maxit), done = vec_load(&p->done);
@@ -2285,7 +2287,7 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
         if (threadIdx.x != 0 || skip) return;  // skip pairs with k_pcg_residual's when_done
         if (forced) *force = 0;
         if (mode == 0) {
-            rho = rho_old = alpha = 0.0;
+            rho = alpha = 0.0;
             it = 0;
             mx = maxit;
             flex = flexible;
@@ -2313,7 +2315,6 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
         h.bb = bb;
         h.rr = rr;
         h.rho = rho;
-        h.rho_old = rho_old;
         h.beta = beta;
         h.alpha = alpha;
         h.tol2 = tol2;
@@ -2346,7 +2347,6 @@ __global__ __launch_bounds__(kFin) void k_fin_start(PcgScalars* __restrict__ s, 
                 mx = maxit;
                 tol2 = rtol * rtol * bb;
                 p->rho = 0.0;
-                p->rho_old = 0.0;
                 p->alpha = 0.0;
                 p->it = 0;
                 p->maxit = maxit;

@@ -57,9 +57,10 @@ struct SellOp {
 // values and operands are one round of independent, contiguous loads instead of
 // three dependent ones, and half of the values come from the cache (the lower
 // triangle is the upper one of an earlier row): 32 B of matrix a row in FP64
-// instead of 70, 16 instead of 42 in FP32. At 2.1M rows the CG SpMV takes 35
-// us instead of 46 and the pre-smoother 16 instead of 27. Terms are added in
-// column order; an absent entry (zero) adds nothing whatever its operand.
+// instead of 70, 16 instead of 42 in FP32. At 2.1M rows, in traces of steps on one
+// card, the CG SpMV takes 40 us instead of 51 and the pre-smoother 21 instead of
+// 27.5. Terms are added in column order; an absent entry (zero) adds nothing
+// whatever its operand.
 template <typename T, int K>
 struct DiaOp {
     static constexpr bool kScaled = false;

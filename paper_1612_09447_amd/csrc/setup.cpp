@@ -1829,7 +1829,7 @@ static int32_t int_exponent(double alpha) {
 // Fans where they hold most of a ring and their blocks fill the chip (some 3 per
 // CU): stage_rhs with its fill takes 28.0 us against 26.9 with the best
 // block of single tets at 750,000 tets, 31.1 | 31.0 at 1.3M, 31.9 | 32.1 at 1.6M,
-// 38.8 | 41.7 at 2.6M, 90.6 | 97.6 at 12.6M. No block size is timed then, which
+// 38.8 | 41.7 at 2.6M, 89.3 | 93.2 at 12.6M. No block size is timed then, which
 // takes half of the build's time off (12.6M tets: 7.7 instead of 12.7 s).
 constexpr double kMinFanLength = 4.0;
 constexpr int64_t kMinFans = 800 * kTetBlock;
